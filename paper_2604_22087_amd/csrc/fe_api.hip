@@ -391,12 +391,14 @@ int fe_set_materials(fe_problem* p, const uint8_t* phase, int n_phases, const in
     free_dev(p->scale);
     p->scale = nullptr;
   }
-  const int comps = nh ? 10 : (j2 ? 6 : 0);
+  const int comps = nh ? 10 : (j2 ? J2_TANGENT_WORDS : 0);
   if (comps) {
     free_dev(p->tangent);
     p->tangent = nullptr;
-    int st = alloc(&p->tangent, rs * comps * 8 * p->n_el);
+    const size_t words = (size_t)comps * 8 * (size_t)p->n_el;
+    int st = alloc(&p->tangent, rs * (words + TANGENT_PAD));
     if (st) return st;
+    HIPCHK(launch_fill(p, static_cast<char*>(p->tangent) + rs * words, TANGENT_PAD, 0.0, S(stream)));
   }
   p->mat = m;
   p->model_set = j2 ? MS_J2 : (nh ? MS_NH : MS_LINEAR);

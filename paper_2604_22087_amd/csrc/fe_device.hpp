@@ -156,19 +156,18 @@ __device__ __forceinline__ void j2_update(const T H[3][3], const T epn[6], T an,
   S[0][1] = S[1][0] = theta * s01;
 }
 
-// Compact J2 tangent -> (lam', mu', beta, N): D = lam' 1x1 + 2 mu' I_sym - beta N x N.
+// First word r of the compact J2 tangent -> (lam', mu', beta): D = lam' 1x1 + 2 mu' I_sym - beta N x N.
 template <typename T>
-__device__ __forceinline__ void j2_tangent_coeffs(const T tan[6], T K, T G, T Hh, T& lp, T& mp, T& beta,
-                                                  T N[6]) {
-  const T r = tan[0];
-  if (r < 0) {
-    mp = G;
-    beta = 0;
-  } else {
-    mp = G * (1 - 3 * G * r);
-    beta = 6 * G * G * (1 / (3 * G + Hh) - r);
-  }
+__device__ __forceinline__ void j2_tangent_coeffs(T r, T K, T G, T Hh, T& lp, T& mp, T& beta) {
+  const T i3 = 1 / (3 * G + Hh);  // (element constant: outside the branch it is formed once)
+  mp = r < 0 ? G : G * (1 - 3 * G * r);
+  beta = r < 0 ? T(0) : 6 * G * G * (i3 - r);
   lp = K - T(2.0 / 3.0) * mp;
+}
+
+template <typename T>
+__device__ __forceinline__ void j2_tangent_coeffs(const T tan[6], T K, T G, T Hh, T& lp, T& mp, T& beta, T N[6]) {
+  j2_tangent_coeffs(tan[0], K, G, Hh, lp, mp, beta);
   N[0] = tan[1];
   N[1] = tan[2];
   N[2] = -(tan[1] + tan[2]);
@@ -180,18 +179,16 @@ __device__ __forceinline__ void j2_tangent_coeffs(const T tan[6], T K, T G, T Hh
 // Linearised J2 stress  D : sym(H).
 template <typename T>
 __device__ __forceinline__ void j2_apply(const T H[3][3], T lp, T mp, T beta, const T N[6], T S[3][3]) {
-  const T e12 = T(0.5) * (H[1][2] + H[2][1]);
-  const T e02 = T(0.5) * (H[0][2] + H[2][0]);
-  const T e01 = T(0.5) * (H[0][1] + H[1][0]);
-  const T tr = H[0][0] + H[1][1] + H[2][2];
-  const T ne = N[0] * H[0][0] + N[1] * H[1][1] + N[2] * H[2][2] + 2 * (N[3] * e12 + N[4] * e02 + N[5] * e01);
-  const T bn = beta * ne;
-  S[0][0] = lp * tr + 2 * mp * H[0][0] - bn * N[0];
-  S[1][1] = lp * tr + 2 * mp * H[1][1] - bn * N[1];
-  S[2][2] = lp * tr + 2 * mp * H[2][2] - bn * N[2];
-  S[1][2] = S[2][1] = 2 * mp * e12 - bn * N[3];
-  S[0][2] = S[2][0] = 2 * mp * e02 - bn * N[4];
-  S[0][1] = S[1][0] = 2 * mp * e01 - bn * N[5];
+  const T g12 = H[1][2] + H[2][1], g02 = H[0][2] + H[2][0], g01 = H[0][1] + H[1][0];
+  const T ltr = lp * (H[0][0] + H[1][1] + H[2][2]);
+  const T bn = beta * (N[0] * H[0][0] + N[1] * H[1][1] + N[2] * H[2][2] + N[3] * g12 + N[4] * g02 + N[5] * g01);
+  const T m2 = 2 * mp;
+  S[0][0] = ltr + m2 * H[0][0] - bn * N[0];
+  S[1][1] = ltr + m2 * H[1][1] - bn * N[1];
+  S[2][2] = ltr + m2 * H[2][2] - bn * N[2];
+  S[1][2] = S[2][1] = mp * g12 - bn * N[3];
+  S[0][2] = S[2][0] = mp * g02 - bn * N[4];
+  S[0][1] = S[1][0] = mp * g01 - bn * N[5];
 }
 
 // ---- learned surrogate at a plastic-trial J2 point ----------------------------------

@@ -30,7 +30,7 @@ struct Phases {
 };
 
 // Which constitutive models a launch has to handle (selects a kernel instance).
-enum ModelSet { MS_LINEAR = 0, MS_J2 = 1, MS_NH = 2 };
+enum ModelSet { MS_LINEAR = 0, MS_J2 = 1, MS_NH = 2, MS_SUR = 3 };  // MS_SUR: J2 with surrogate points (element kernel)
 
 enum SurMode { SUR_OFF = 0, SUR_CAPTURE = 1, SUR_CLASSIFY = 2, SUR_CONSUME = 3 };
 constexpr float SUR_FLAG = -2.0f;  // first stored-tangent word of a point whose tangent comes from the surrogate
@@ -118,6 +118,11 @@ struct BicgCtrl {
 };
 constexpr int BICG_GRID = 512;       // workgroups of the BiCGStab vector kernels (= partial slots)
 
+// words of the compact J2 tangent per Gauss point; the stored array is followed by TANGENT_PAD zero
+// words, which the operator reads at elastic points
+constexpr int J2_TANGENT_WORDS = 6;
+constexpr int TANGENT_PAD = 8;
+
 struct ElemArgs {
   int n;
   double h;
@@ -190,7 +195,7 @@ struct fe_problem {
   uint8_t* phase = nullptr;   // [n_el]
   void* scale = nullptr;      // real [n_el] or null
   uint8_t* mask = nullptr;    // [n_dof] or null
-  void* tangent = nullptr;    // J2 compact tangent [6][8][n_el]
+  void* tangent = nullptr;    // stored linearisation [6 (J2) or 10 (Neo-Hookean)][8][n_el], then TANGENT_PAD zeros
   bool lin_valid = false;
   // solver workspace
   void* w_r = nullptr;

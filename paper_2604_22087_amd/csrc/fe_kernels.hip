@@ -1,18 +1,21 @@
 // HIP kernels of libfe for gfx950 (MI355X).
 //
-// Element kernels work on bricks of TX x TY x TZ = 16 x 4 x 4 elements, one
-// element per lane, 256 lanes per workgroup:
-//   1. the brick's (TX+1)(TY+1)(TZ+1) nodal values are staged in LDS with
-//      coalesced row loads (each node is then read from LDS by up to 8 lanes);
-//   2. each lane forms the displacement gradient at its 8 Gauss points by sum
-//      factorisation of the trilinear basis (the x-derivative at a Gauss point
-//      only depends on its (y,z) position, so 9 bilinear interpolations of
-//      nodal differences give all 72 gradient entries);
-//   3. the constitutive law turns each gradient into a stress, which is pushed
-//      back to the nodes by the transposed factorisation;
+// Element kernels work on bricks of TX x TY x TZ = 16 x 4 x 4 elements, two lanes per element
+// (lane half r takes the four Gauss points of reference layer z = r), 512 lanes per workgroup:
+//   1. the brick's (TX+1)(TY+1)(TZ+1) nodal values are staged in LDS, one wave per node row
+//      (the row's address and its place in the brick are scalars, the lane is the offset);
+//   2. each lane forms the displacement gradient at its 4 Gauss points by sum factorisation of
+//      the trilinear basis (an x-derivative only depends on the point's (y,z) position, so 24
+//      interpolated nodal differences give all 36 gradient entries);
+//   3. the constitutive law turns each gradient into a stress, which is pushed back to the
+//      nodes by the transposed factorisation; the two halves of an element exchange their
+//      shares in registers (v_permlane32_swap), after which half r holds the four nodes k = r;
 //   4. nodal forces are summed into LDS in FP64 by workgroup-scope LDS atomic adds;
 //      nodes owned by the brick alone are stored, nodes on the brick's faces are
 //      added with hardware FP atomics.
+// What bounds them is latency more than bytes (staging loads, then a serial chain of points), so
+// the split aims at waves in flight: one lane per element needs 231 registers for its 72 table
+// entries (two waves per SIMD, the FP64 J2 residual spilled), half an element fits in 128.
 // Bricks are numbered so that consecutive bricks land on one XCD (workgroups
 // are dealt round-robin over the 8 XCDs), keeping shared face nodes in one L2.
 #include "fe_internal.hpp"
@@ -27,8 +30,11 @@ LaunchEvents& launch_events() {
 
 constexpr int TX = 16, TY = 4, TZ = 4;
 constexpr int NX = TX + 1, NY = TY + 1, NZ = TZ + 1, NN = NX * NY * NZ;
-constexpr int EBLOCK = TX * TY * TZ;
-static_assert(EBLOCK == 256, "one element per lane");
+constexpr int EBLOCK = 2 * TX * TY * TZ;     // two lanes per element
+constexpr int EWAVES = EBLOCK / 64;
+constexpr int ROWW = 3 * NX, NROWS = NY * NZ;  // a brick's node rows (along x): words per row, rows
+constexpr int ROW_IT = (NROWS + EWAVES - 1) / EWAVES;
+static_assert(TX == 16 && TY == 4 && EBLOCK == 512 && ROWW <= 64, "lane layout of the element kernel");
 
 // CG direction step of iteration k (see the CG section below); false when the
 // iteration stops (block 0 records the status).
@@ -89,91 +95,128 @@ template <typename T> __device__ __forceinline__ void interp2(const T D[2][2], T
   G[1][1] = b * t01 + a * t11;
 }
 
-// Gradient tables of a nodal field U[k][j][i][c] (node (i,j,k) of the brick element):
-// du_c/dx at Gauss point (p,q,r) = Gx[r][q][c], du_c/dy = Gy[r][p][c], du_c/dz = Gz[q][p][c].
-template <typename T>
-__device__ __forceinline__ void gradients(const T U[2][2][2][3], T inv_h, T Gx[2][2][3], T Gy[2][2][3],
-                                          T Gz[2][2][3]) {
+// Gradient tables of the Gauss layer r of a nodal field u(k, j, i, c) (node (i,j,k) of the brick
+// element), times h: at point (p,q) of the layer h du_c/dx = x[q][c], h du_c/dy = y[p][c],
+// h du_c/dz = z[q][p][c].  w0, w1: the layer's weights of the nodes k = 0, 1.  Nodal differences
+// are taken first (a large rigid part cancels before anything is rounded).
+template <typename T> struct HalfGrad {
+  T x[2][3], y[2][3], z[2][2][3];
+};
+
+template <typename T, typename F>
+__device__ __forceinline__ void half_gradients(F&& u, T w0, T w1, HalfGrad<T>& g) {
+  const T a = T(GA), b = T(GB);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
+    T U[2][2][2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) U[k][j][i] = u(k, j, i, c);
+    T e0 = w0 * (U[0][0][1] - U[0][0][0]) + w1 * (U[1][0][1] - U[1][0][0]);
+    T e1 = w0 * (U[0][1][1] - U[0][1][0]) + w1 * (U[1][1][1] - U[1][1][0]);
+    g.x[0][c] = a * e0 + b * e1;
+    g.x[1][c] = b * e0 + a * e1;
+    e0 = w0 * (U[0][1][0] - U[0][0][0]) + w1 * (U[1][1][0] - U[1][0][0]);
+    e1 = w0 * (U[0][1][1] - U[0][0][1]) + w1 * (U[1][1][1] - U[1][0][1]);
+    g.y[0][c] = a * e0 + b * e1;
+    g.y[1][c] = b * e0 + a * e1;
     T D[2][2], G[2][2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) D[k][j] = U[k][j][1][c] - U[k][j][0][c];
-    interp2(D, G);
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) Gx[r][q][c] = G[r][q] * inv_h;
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) D[k][i] = U[k][1][i][c] - U[k][0][i][c];
-    interp2(D, G);
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) Gy[r][p][c] = G[r][p] * inv_h;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) D[j][i] = U[1][j][i][c] - U[0][j][i][c];
+      for (int i = 0; i < 2; ++i) D[j][i] = U[1][j][i] - U[0][j][i];
     interp2(D, G);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) Gz[q][p][c] = G[q][p] * inv_h;
+      for (int p = 0; p < 2; ++p) g.z[q][p][c] = G[q][p];
   }
 }
 
-// Nodal forces F[k][j][i][c] += f * sum over Gauss points of S_cJ dN/dx_J, from the
-// per-direction Gauss-point sums Px[r][q][c] (summed over p), Py[r][p][c], Pz[q][p][c].
+// v of the 32 lower lanes' r = 0 half plus v of the r = 1 half, for node layer k = 0 in the lower
+// and k = 1 in the upper lanes (f0, f1: this half's shares of the two node layers).
+__device__ __forceinline__ float half_sum(float f0, float f1) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(f0), __float_as_uint(f1), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ double half_sum(double f0, double f1) {
+  const unsigned long long a = __double_as_longlong(f0), b = __double_as_longlong(f1);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// Nodal forces of the element: f times the sum over its Gauss points of S_cJ h dN/dx_J, from this
+// half's point sums s.x[q][c] (summed over p), s.y[p][c], s.z[q][p][c] and the other half's (one
+// register exchange per value); F[j][i][c] = force of node (i, j, k = r).
 template <typename T>
-__device__ __forceinline__ void push_back(const T Px[2][2][3], const T Py[2][2][3], const T Pz[2][2][3],
-                                          T f, T F[2][2][2][3]) {
+__device__ __forceinline__ void half_push_back(const HalfGrad<T>& s, T w0, T w1, T f, T F[2][2][3]) {
+  const T a = T(GA), b = T(GB);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    T D[2][2], G[2][2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) D[r][q] = Px[r][q][c];
-    interp2(D, G);  // -> [k][j]
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        F[k][j][1][c] += f * G[k][j];
-        F[k][j][0][c] -= f * G[k][j];
-      }
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int p = 0; p < 2; ++p) D[r][p] = Py[r][p][c];
-    interp2(D, G);  // -> [k][i]
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        F[k][1][i][c] += f * G[k][i];
-        F[k][0][i][c] -= f * G[k][i];
-      }
+    const T x0 = a * s.x[0][c] + b * s.x[1][c], x1 = b * s.x[0][c] + a * s.x[1][c];  // by j
+    const T y0 = a * s.y[0][c] + b * s.y[1][c], y1 = b * s.y[0][c] + a * s.y[1][c];  // by i
+    T D[2][2], Z[2][2];
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) D[q][p] = Pz[q][p][c];
-    interp2(D, G);  // -> [j][i]
+      for (int p = 0; p < 2; ++p) D[q][p] = s.z[q][p][c];
+    interp2(D, Z);  // -> [j][i]
+    const T A[2][2] = {{-x0 - y0, x0 - y1}, {y0 - x1, x1 + y1}};
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        F[1][j][i][c] += f * G[j][i];
-        F[0][j][i][c] -= f * G[j][i];
-      }
+      for (int i = 0; i < 2; ++i)
+        F[j][i][c] = f * half_sum(w0 * A[j][i] - Z[j][i], w1 * A[j][i] + Z[j][i]);
   }
 }
 
+// The brick of a workgroup, its node rows and this lane's word of a row.
+struct Brick {
+  int n, a0, b0, c0;
+  int wave, lane;         // wave index (scalar), lane
+  bool inx, ownx, privx;  // this word is in the mesh; owned / private as far as x decides it
+  int off;                // word offset inside a row, clamped into the mesh
+  int64_t base;           // first word of the node row (a0, b0, c0)
+  int64_t rowy, rowz;     // words between node rows along y and z
+
+  __device__ __forceinline__ Brick(int n_, int tile, int ntx, int nty) : n(n_) {
+    a0 = (tile % ntx) * TX, b0 = ((tile / ntx) % nty) * TY, c0 = (tile / (ntx * nty)) * TZ;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lane = threadIdx.x & 63;
+    const int words = 3 * min(NX, n + 1 - a0);
+    inx = lane < words;
+    off = min(lane, words - 1);
+    const int li = off / 3, gi = a0 + li;
+    ownx = inx && (li < TX || gi == n);
+    privx = inx && (gi == 0 || li >= 1) && (gi == n || li < TX);
+    rowy = 3 * (int64_t)(n + 1);
+    rowz = rowy * (n + 1);
+    base = 3 * (int64_t)a0 + rowy * b0 + rowz * c0;
+  }
+  // node row t of this wave: place in the brick, whether it exists, its first word (all scalar)
+  struct Row {
+    int row, lj, lk;
+    bool live, own, priv;
+    int64_t word;
+  };
+  __device__ __forceinline__ Row row(int t) const {
+    Row r;
+    r.row = wave + t * EWAVES;
+    r.lj = r.row % NY;
+    r.lk = r.row / NY;
+    const int gj = b0 + r.lj, gk = c0 + r.lk;
+    r.live = r.row < NROWS && gj <= n && gk <= n;
+    r.own = (r.lj < TY || gj == n) && (r.lk < TZ || gk == n);
+    r.priv = (gj == 0 || r.lj >= 1) && (gj == n || r.lj < TY) && (gk == 0 || r.lk >= 1) && (gk == n || r.lk < TZ);
+    r.word = base + rowy * r.lj + rowz * r.lk;
+    return r;
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Single-reduction CG, staging of a brick's nodes for launch j (see ElemArgs): every lane
@@ -184,140 +227,109 @@ __device__ __forceinline__ void push_back(const T Px[2][2][3], const T Py[2][2][
 // owner also stores s_{j-1}, r_j, p_{j-1} = u_{j-1} + beta p_{j-2}, x_j = x_{j-1} + alpha p_{j-1},
 // zeroes the w buffer of launch j+1 and adds its shares of (r_j, u_j) and ||r_j||^2.
 // u_j goes to s_x (0 on constrained dofs, whose value goes to s_b), s_y is cleared.
-constexpr int STAGE_IT = (NN * 3 + EBLOCK - 1) / EBLOCK;
-
 template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[3], double (*sh)[EBLOCK / 64],
+__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[2], double (*sh)[EWAVES],
                                            T& alpha_out, T& beta_out);
 
-template <typename T, bool NEED_L, bool BLK, typename Acc, typename Early>
-__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, int n, int a0, int b0, int c0,
-                                               double (*sh)[EBLOCK / 64], T* s_x, Acc* s_y, T* s_b, T* s_l,
-                                               unsigned char* s_fx, double& g, double& rr, Early&& early) {
-  static_assert(CGS_SLOTS == EBLOCK, "one reduction slot per lane");
+// (the node's three components sit in adjacent lanes of the row: node-block Jacobi fetches the
+// other two by lane exchange)
+template <typename T, bool BLK, typename Acc, typename Early>
+__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& br, double (*sh)[EWAVES], T* s_x,
+                                               Acc* s_y, T* s_b, unsigned& fixed, double& g, double& rr,
+                                               Early&& early) {
+  static_assert(2 * CGS_SLOTS == EBLOCK, "lanes per reduction slot");
   // the previous launch's slot sums are requested before the staging loads (loads return in
   // order), so the scalar reduction overlaps the staging traffic
-  double acc_v[3] = {0, 0, 0};
+  double acc_v[2] = {0, 0};
   const bool prev = a.cg_j > 0;
   if (prev) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) acc_v[k] = a.cg_acc_in[k * CGS_SLOTS + threadIdx.x];
+    acc_v[0] = a.cg_acc_in[threadIdx.x];
+    if (br.wave < EWAVES / 2) acc_v[1] = a.cg_acc_in[EBLOCK + threadIdx.x];
   }
   T alpha = 0, beta = 0;
   const T* __restrict__ RO = static_cast<const T*>(a.cg_rold);
   const T* __restrict__ WO = static_cast<const T*>(a.cg_wold);
   const T* __restrict__ SO = static_cast<const T*>(a.cg_sold);
   const T* __restrict__ M = static_cast<const T*>(a.cg_dinv);
-  const T* __restrict__ XL = static_cast<const T*>(a.xlin);
   T* __restrict__ RN = static_cast<T*>(a.cg_rnew);
   T* __restrict__ SN = static_cast<T*>(a.cg_snew);
   T* __restrict__ P = static_cast<T*>(a.cg_pvec);
   T* __restrict__ X = static_cast<T*>(a.cg_x);
   T* __restrict__ WZ = static_cast<T*>(a.cg_wzero);
   const unsigned char* __restrict__ mask = a.mask;
-  constexpr bool blk = BLK;
   const bool first = a.cg_j == 0;
-  const int64_t np1 = n + 1;
-  // loads in batches of SB rounds (all loads of a batch, then its updates and stores):
-  // FP64 takes all rounds at once, FP32 two batches, which measured faster there
-  constexpr int SB = sizeof(T) == 8 ? STAGE_IT : (STAGE_IT + 1) / 2;
+  const int c = br.off % 3;
+  const int i0 = c == 0 ? 0 : (c == 1 ? 5 : 4), i1 = c == 0 ? 5 : (c == 1 ? 1 : 3), i2 = c == 0 ? 4 : (c == 1 ? 3 : 2);
+  unsigned char mk[ROW_IT];
+  T ro[ROW_IT], wo[ROW_IT], so[ROW_IT], m[ROW_IT][BLK ? 3 : 1], po[ROW_IT], xo[ROW_IT];
 #pragma unroll
-  for (int t0 = 0; t0 < STAGE_IT; t0 += SB) {
-    int64_t dofs[SB];
-    int cs[SB];
-    bool in[SB], own[SB];
-    unsigned char mk[SB];
-    T ro[SB][3], wo[SB][3], so[SB][3], m[SB][3], po[SB], xo[SB], lv[SB];
-#pragma unroll
-    for (int t = 0; t < SB; ++t) {
-      const int i = threadIdx.x + (t0 + t) * EBLOCK;
-      const int c = i % 3, nd = i / 3;
-      const int li = nd % NX, lj = (nd / NX) % NY, lk = nd / (NX * NY);
-      const int gi = a0 + li, gj = b0 + lj, gk = c0 + lk;
-      in[t] = i < NN * 3 && gi <= n && gj <= n && gk <= n;
-      own[t] = in[t] && (min(gi, n - 1) - a0 < TX) && (min(gj, n - 1) - b0 < TY) && (min(gk, n - 1) - c0 < TZ);
-      cs[t] = c;
-      const int64_t dof = in[t] ? 3 * (gi + np1 * (gj + np1 * gk)) + c : 0;
-      dofs[t] = dof;
-      const int64_t b3 = dof - c;
-      if (blk) {  // the node's three components (slot k = component k)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          ro[t][k] = in[t] ? RO[b3 + k] : T(0);
-          wo[t][k] = in[t] && !first ? WO[b3 + k] : T(0);
-          so[t][k] = in[t] && !first ? SO[b3 + k] : T(0);
-        }
-      } else {  // the lane's own component only (slot 0): one coalesced load per vector
-        ro[t][0] = in[t] ? RO[dof] : T(0);
-        wo[t][0] = in[t] && !first ? WO[dof] : T(0);
-        so[t][0] = in[t] && !first ? SO[dof] : T(0);
-        ro[t][1] = ro[t][2] = wo[t][1] = wo[t][2] = so[t][1] = so[t][2] = T(0);
-      }
-      if (blk) {
-        const T* mb = M + 2 * b3;  // 6 entries per node: xx, yy, zz, yz, xz, xy
-        const int i0 = c == 0 ? 0 : (c == 1 ? 5 : 4), i1 = c == 0 ? 5 : (c == 1 ? 1 : 3),
-                  i2 = c == 0 ? 4 : (c == 1 ? 3 : 2);
-        m[t][0] = in[t] ? mb[i0] : T(0);
-        m[t][1] = in[t] ? mb[i1] : T(0);
-        m[t][2] = in[t] ? mb[i2] : T(0);
-      } else {  // (one word: a copy of a register with a load in flight would wait for it)
-        m[t][0] = in[t] ? M[dof] : T(0);
-        m[t][1] = m[t][2] = T(0);
-      }
-      mk[t] = mask ? mask[dof] : (unsigned char)0;  // dof is 0 outside the mesh
-      po[t] = own[t] && !first ? P[dof] : T(0);
-      xo[t] = own[t] && !first ? X[dof] : T(0);
-      lv[t] = NEED_L && in[t] ? XL[dof] : T(0);
+  for (int t = 0; t < ROW_IT; ++t) {
+    ro[t] = wo[t] = so[t] = po[t] = xo[t] = T(0);
+    mk[t] = 0;
+    const Brick::Row r = br.row(t);
+    if (!r.live) continue;
+    const int64_t dof = r.word + br.off;
+    ro[t] = RO[dof];
+    if (!first) {
+      wo[t] = WO[dof];
+      so[t] = SO[dof];
     }
-    if (t0 == 0) {
-      early();
-      if (prev && !cg_scalars<T>(a, acc_v, sh, alpha, beta)) return false;
+    if constexpr (BLK) {
+      const T* mb = M + 2 * (dof - c);  // 6 entries per node: xx, yy, zz, yz, xz, xy
+      m[t][0] = mb[i0];
+      m[t][1] = mb[i1];
+      m[t][2] = mb[i2];
+    } else {
+      m[t][0] = M[dof];
     }
+    if (mask) mk[t] = mask[dof];
+    if (!first && r.own) {
+      po[t] = P[dof];
+      xo[t] = X[dof];
+    }
+  }
+  early();
+  if (prev && !cg_scalars<T>(a, acc_v, sh, alpha, beta)) return false;
 #pragma unroll
-    for (int t = 0; t < SB; ++t) {
-      const int i = threadIdx.x + (t0 + t) * EBLOCK;
-      if (i >= NN * 3) break;
-      const int c = cs[t];
-      int mkv = mk[t];
-      asm volatile("" : "+v"(mkv));  // keeps the flag test here, after every load of the batch was issued
-      const bool fixed = in[t] && mkv != 0;
-      T rn[3], sn[3];
-#pragma unroll
-      for (int k = 0; k < (blk ? 3 : 1); ++k) {
-        sn[k] = wo[t][k] + beta * so[t][k];
-        rn[k] = first ? ro[t][k] : ro[t][k] - alpha * sn[k];
+  for (int t = 0; t < ROW_IT; ++t) {
+    const Brick::Row r = br.row(t);
+    if (!r.live) continue;
+    int mkv = mk[t];
+    asm volatile("" : "+v"(mkv));  // keeps the flag test here, after every load was issued
+    const bool fx = mkv != 0;
+    const T sn = wo[t] + beta * so[t];
+    const T rn = first ? ro[t] : ro[t] - alpha * sn;
+    T u, uo;
+    if constexpr (BLK) {
+      const int l0 = br.off - c;
+      u = m[t][0] * __shfl(rn, l0, 64) + m[t][1] * __shfl(rn, l0 + 1, 64) + m[t][2] * __shfl(rn, l0 + 2, 64);
+      uo = m[t][0] * __shfl(ro[t], l0, 64) + m[t][1] * __shfl(ro[t], l0 + 1, 64) + m[t][2] * __shfl(ro[t], l0 + 2, 64);
+    } else {
+      u = m[t][0] * rn;
+      uo = m[t][0] * ro[t];
+    }
+    if (r.own && br.ownx) {
+      const int64_t dof = r.word + br.off;
+      WZ[dof] = 0;
+      if (!first) {
+        const T pn = uo + beta * po[t];
+        P[dof] = pn;
+        X[dof] = xo[t] + alpha * pn;
+        SN[dof] = sn;
+        RN[dof] = rn;
       }
-      T u, uo;
-      int cc = 0;  // slot of the lane's own component
-      if (blk) {
-        u = m[t][0] * rn[0] + m[t][1] * rn[1] + m[t][2] * rn[2];
-        uo = m[t][0] * ro[t][0] + m[t][1] * ro[t][1] + m[t][2] * ro[t][2];
-        cc = c;
-      } else {
-        u = m[t][0] * rn[0];
-        uo = m[t][0] * ro[t][0];
-      }
-      if (own[t]) {
-        const int64_t dof = dofs[t];
-        WZ[dof] = 0;
-        if (!first) {
-          const T pn = uo + beta * po[t];
-          P[dof] = pn;
-          X[dof] = xo[t] + alpha * pn;
-          SN[dof] = sn[cc];
-          RN[dof] = rn[cc];
-        }
-        g += (double)rn[cc] * (double)u;
-        rr += (double)rn[cc] * (double)rn[cc];
-      }
-      if (fixed) {
+      g += (double)rn * (double)u;
+      rr += (double)rn * (double)rn;
+    }
+    if (br.inx) {
+      const int i = r.row * ROWW + br.lane;
+      if (fx) {
         s_b[i] = u;
         u = 0;
+        fixed |= 1u << t;
       }
-      s_fx[i] = fixed ? 1 : 0;
-      s_x[i] = in[t] ? u : T(0);
+      s_x[i] = u;
       s_y[i] = 0;
-      if (NEED_L) s_l[i] = lv[t];
     }
   }
   return true;
@@ -333,23 +345,23 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, int n, int a0,
 // (g, alpha) of iterate j-1 go to history slot (j-1) & 1 while slot j & 1 is read.
 // Returns false when the iteration stops (every workgroup reaches the same decision).
 template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[3], double (*sh)[EBLOCK / 64],
+__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[2], double (*sh)[EWAVES],
                                            T& alpha_out, T& beta_out) {
   const long j = a.cg_j;
-  double v[3] = {v_in[0], v_in[1], v_in[2]};
+  double v[2] = {v_in[0], v_in[1]};  // waves 0-3: d and rr slots, waves 4-7: g slots
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
+  for (int k = 0; k < 2; ++k)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) sh[k][threadIdx.x >> 6] = v[k];
+    for (int k = 0; k < 2; ++k) sh[k][threadIdx.x >> 6] = v[k];
   __syncthreads();
   double d = 0, g = 0, rr = 0;
-  for (int w = 0; w < EBLOCK / 64; ++w) {
+  for (int w = 0; w < EWAVES / 2; ++w) {
     d += sh[0][w];
-    g += sh[1][w];
-    rr += sh[2][w];
+    g += sh[0][EWAVES / 2 + w];
+    rr += sh[1][w];
   }
   __syncthreads();  // sh is reused by the caller
   const CgCtrl* c = a.ctrl;
@@ -393,23 +405,33 @@ __device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[
 // ---------------------------------------------------------------------------
 // element brick kernel
 
-// (at least two waves per SIMD: some FP64 instances sit at the 256-register edge, where
-// the allocator would otherwise fall back to one wave per SIMD)
+// (waves per SIMD asked of the compiler; the lane split leaves every instance but the FP64 residuals
+// of J2 and Neo-Hookean problems room for four: see elem_waves)
 // ACC32 (FP32 problems only): the nodal sums accumulate in FP32 LDS as well; by default they
 // are formed in FP64 in both precisions.
+template <typename T, int OP, int MS> constexpr int elem_waves() {
+  return MS == MS_SUR ? 2 : 4;
+}
+
 template <typename T, int OP, int MS, bool ACC32 = false>
-__global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) void elem_kernel(ElemArgs a,
-                                                                                              const int* stop) {
+__global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_waves<T, OP, MS>()))) void elem_kernel(
+    ElemArgs a, const int* stop) {
   static_assert(!ACC32 || sizeof(T) == 4, "FP32 accumulation is an FP32-problem variant");
   using Acc = typename std::conditional<ACC32, float, double>::type;
   constexpr bool APPLY_LIKE = (OP == OP_APPLY) || (OP == OP_CG_APPLY);
   constexpr bool NEED_L = OP == OP_VJP;
+  constexpr bool SUR = MS == MS_SUR, J2M = MS == MS_J2 || SUR;
+  constexpr int NHB = sizeof(T) == 8 ? 1 : 2;  // register sets of Neo-Hookean words in flight
   __shared__ T s_x[NN * 3];
   __shared__ Acc s_y[OP == OP_VJP ? 1 : NN * 3];  // nodal sums
   __shared__ T s_l[NEED_L ? NN * 3 : 1];
   __shared__ T s_b[OP == OP_CG_APPLY ? NN * 3 : 1];  // CG: u on constrained dofs (A u = u there)
-  __shared__ double s_red[6][EBLOCK / 64];
-  __shared__ unsigned char s_fx[NN * 3];  // constrained dof flags of the brick (apply_bc)
+  __shared__ double s_red[6][EWAVES];
+  // FP64 laws with stored words: the gradients of the points q = 1 wait here while those of q = 0
+  // are worked on, then the stress sums of q = 0 do (18 registers less at the peak: no spills at
+  // four waves per SIMD; one slot per lane, so no barrier)
+  constexpr bool PARK = sizeof(T) == 8 && MS != MS_LINEAR;
+  __shared__ T s_park[PARK ? 9 : 1][PARK ? EBLOCK : 1];
 
   if (stop && *stop) return;
   const int n = a.n;
@@ -422,249 +444,259 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
       if (a.stress_part && a.stress_sum && threadIdx.x < 6) a.stress_part[(int64_t)blockIdx.x * 6 + threadIdx.x] = 0.0;
     return;
   }
-  const int a0 = (tile % ntx) * TX, b0 = ((tile / ntx) % nty) * TY, c0 = (tile / (ntx * nty)) * TZ;
+  const Brick br(n, tile, ntx, nty);
   const int tid = threadIdx.x;
   const T* X = static_cast<const T*>(a.x);
-  const T* XL = static_cast<const T*>(a.xlin);
-  const int ex = tid % TX, ey = (tid / TX) % TY, ez = tid / (TX * TY);
-  const int ga = a0 + ex, gb = b0 + ey, gc = c0 + ez;
+  // element of this lane: 32 of a wave's 64 lanes are two x-runs of the brick; upper half: r = 1
+  const int r = br.lane >> 5;
+  const int ex = br.lane & 15, ey = 2 * (br.wave & 1) + ((br.lane >> 4) & 1), ez = br.wave >> 1;
+  const int ga = br.a0 + ex, gb = br.b0 + ey, gc = br.c0 + ez;
   const bool valid = ga < n && gb < n && gc < n;
   const int64_t e = valid ? (ga + (int64_t)n * (gb + (int64_t)n * gc)) : 0;
   const int64_t ne = a.n_el;
-  const T h = T(a.h), inv_h = T(1.0 / a.h);
+  const int64_t e4 = e + 4 * r * ne;  // first point of this half in [..][8][n_el] arrays
+  const T h = T(a.h);
+  const T w0 = r ? T(GB) : T(GA), w1 = r ? T(GA) : T(GB);
   // the element's phase is requested before the staging loads; the operator's first stored-
   // tangent word of every Gauss point right after them (both arrive before they are used)
   const int ph = valid ? (int)a.phase[e] : 0;
   const T* tang_c = static_cast<const T*>(a.tangent);
-  T tq0[8];
-  T nw[2][10];  // Neo-Hookean operator: F^-T and ln J of two Gauss points (see below)
-  // (FP32 requests the first point's words with the staging, measured faster there; FP64 after
-  // the gradients, measured faster there)
-  constexpr bool NH_EARLY = sizeof(T) == 4;
+  T tq0[4];
   auto early = [&]() {
-    if (APPLY_LIKE && MS == MS_J2) {
+    if (APPLY_LIKE && J2M) {
       const bool j2 = valid && a.mat.ph[ph].model == FE_J2;
 #pragma unroll
-      for (int qq = 0; qq < 8; ++qq) tq0[qq] = j2 ? tang_c[(int64_t)qq * ne + e] : T(-1);
-    }
-    if (APPLY_LIKE && MS == MS_NH && NH_EARLY) {
-      const bool nh = valid && a.mat.ph[ph].model == FE_NEOHOOKE;
-#pragma unroll
-      for (int k = 0; k < 10; ++k) nw[0][k] = nh ? tang_c[(int64_t)(k * 8) * ne + e] : T(0);
+      for (int qq = 0; qq < 4; ++qq) tq0[qq] = j2 ? tang_c[e4 + qq * ne] : T(-1);
     }
   };
 
   double cg_g = 0, cg_rr = 0;  // owners' shares of (r_j, u_j) and ||r_j||^2
-  const int64_t np1 = n + 1;
+  unsigned fixed = 0;          // bit t: this lane's word of node row t is constrained
 
-  if (OP == OP_CG_APPLY) {
+  if constexpr (OP == OP_CG_APPLY) {
     if (blockIdx.x == 0)
       for (int i = tid; i < 3 * CGS_SLOTS; i += EBLOCK) a.cg_acc_zero[i] = 0.0;  // slots of launch j+1
     // (one instance per preconditioner form, so each staging path is branch-free)
-    const bool go =
-        a.cg_block
-            ? cg_stage_brick<T, NEED_L, true>(a, n, a0, b0, c0, s_red, s_x, s_y, s_b, s_l, s_fx, cg_g, cg_rr, early)
-            : cg_stage_brick<T, NEED_L, false>(a, n, a0, b0, c0, s_red, s_x, s_y, s_b, s_l, s_fx, cg_g, cg_rr, early);
+    const bool go = a.cg_block ? cg_stage_brick<T, true>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
+                               : cg_stage_brick<T, false>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
     if (!go) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      cg_g += __shfl_down(cg_g, off, 64);
+      cg_rr += __shfl_down(cg_rr, off, 64);
+    }
+    if (br.lane == 0) {
+      s_red[4][br.wave] = cg_g;
+      s_red[5][br.wave] = cg_rr;
+    }
   } else {  // all loads of the lane first, then the LDS stores
-    T v[STAGE_IT], vl[STAGE_IT];
-    unsigned char mk[STAGE_IT];
-    bool in[STAGE_IT];
+    const T* XL = static_cast<const T*>(a.xlin);
+    T v[ROW_IT], vl[ROW_IT];
+    unsigned char mk[ROW_IT];
     const bool bc = a.apply_bc && a.mask;
 #pragma unroll
-    for (int t = 0; t < STAGE_IT; ++t) {
-      const int i = tid + t * EBLOCK;
-      const int c = i % 3, nd = i / 3;
-      const int li = nd % NX, lj = (nd / NX) % NY, lk = nd / (NX * NY);
-      const int gi = a0 + li, gj = b0 + lj, gk = c0 + lk;
-      in[t] = i < NN * 3 && gi <= n && gj <= n && gk <= n;
-      const int64_t dof = in[t] ? 3 * (gi + np1 * (gj + np1 * gk)) + c : 0;
-      v[t] = in[t] ? X[dof] : T(0);
-      vl[t] = NEED_L && in[t] ? XL[dof] : T(0);
-      mk[t] = bc ? a.mask[dof] : (unsigned char)0;
+    for (int t = 0; t < ROW_IT; ++t) {
+      v[t] = vl[t] = T(0);
+      mk[t] = 0;
+      const Brick::Row rw = br.row(t);
+      if (!rw.live) continue;
+      const int64_t dof = rw.word + br.off;
+      v[t] = X[dof];
+      if (NEED_L) vl[t] = XL[dof];
+      if (bc) mk[t] = a.mask[dof];
     }
     early();
 #pragma unroll
-    for (int t = 0; t < STAGE_IT; ++t) {
-      const int i = tid + t * EBLOCK;
-      if (i >= NN * 3) break;
+    for (int t = 0; t < ROW_IT; ++t) {
+      const Brick::Row rw = br.row(t);
+      if (!rw.live) continue;
       int mkv = mk[t];
       asm volatile("" : "+v"(mkv));  // (the flag test stays here, see cg_stage_brick)
-      const bool fx = in[t] && mkv != 0;
-      s_fx[i] = fx ? 1 : 0;
-      s_x[i] = (APPLY_LIKE && fx) ? T(0) : v[t];
-      if (OP != OP_VJP) s_y[i] = 0;
-      if (NEED_L) s_l[i] = vl[t];
+      if (br.inx) {
+        const int i = rw.row * ROWW + br.lane;
+        if (mkv != 0) fixed |= 1u << t;
+        s_x[i] = (APPLY_LIKE && mkv != 0) ? T(0) : v[t];
+        if (OP != OP_VJP) s_y[i] = 0;
+        if (NEED_L) s_l[i] = vl[t];
+      }
     }
   }
   __syncthreads();
 
-  T Fo[2][2][2][3];
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) Fo[k][j][i][c] = 0;
+  T F[2][2][3];  // nodal forces of the nodes (i, j, k = r), [j][i][c]
   double ssum[6] = {0, 0, 0, 0, 0, 0};
+  const int s0 = 3 * (ex + NX * (ey + NY * ez));  // LDS word of the element's node (0,0,0)
+  double pq = 0;
 
   if (valid) {
     const PhaseConst pc = a.mat.ph[ph];
     const T sc = (a.scale && OP != OP_VJP) ? static_cast<const T*>(a.scale)[e] : T(1);
-    const T lam = T(pc.lam) * sc, mu = T(pc.mu) * sc;
-    const T Kb = T(pc.K) * sc, Gs = T(pc.G) * sc, sy = T(pc.sy), Hh = T(pc.H);
-
-    T U[2][2][2][3];
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int c = 0; c < 3; ++c) U[k][j][i][c] = s_x[3 * ((ex + i) + NX * ((ey + j) + NY * (ez + k))) + c];
-    T Gx[2][2][3], Gy[2][2][3], Gz[2][2][3];
-    gradients(U, inv_h, Gx, Gy, Gz);
-
-    // Neo-Hookean operator: F^-T and ln J of the linearisation, stored by the residual per
-    // Gauss point ([10][8][n_el]), requested one point ahead of their use
-    const bool nh_el = MS == MS_NH && pc.model == FE_NEOHOOKE;
-    auto load_nh = [&](int qp, T* w) {
-#pragma unroll
-      for (int k = 0; k < 10; ++k) w[k] = nh_el ? tang_c[(int64_t)(k * 8 + qp) * ne + e] : T(0);
-    };
-    if (APPLY_LIKE && MS == MS_NH && !NH_EARLY) load_nh(0, nw[0]);
-
-    T Px[2][2][3], Py[2][2][3], Pz[2][2][3];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) Px[x][y][c] = Py[x][y][c] = Pz[x][y][c] = 0;
 
     // J2 operator: the first stored-tangent word of every Gauss point arrived with the staging
-    // (tq0); the five plastic-point words are requested PF Gauss points ahead of their use (a
-    // ring of PF + 1 register sets: 2 measured best, 3 costs more registers than it hides)
-    constexpr int PF = 2;
+    // (tq0); the five plastic-point words are requested PF Gauss points ahead of their use.  An
+    // elastic point reads the zero word behind the array instead: a branch around the loads costs
+    // the FP64 instance 30 spilled registers, and its own words would be traffic
+    const int64_t zero_at = J2_TANGENT_WORDS * 8 * ne;
+    constexpr int PF = 1;
     T pw[PF + 1][5];
-    auto load_pw = [&](int qp, T* w) {
+    auto load_pw = [&](int q4, T* w) {
+      const bool pl = tq0[q4] >= 0;
+      const T* at = tang_c + (pl ? e4 + q4 * ne : zero_at);
+      const int64_t st = pl ? 8 * ne : 0;
 #pragma unroll
-      for (int k = 1; k < 6; ++k) w[k - 1] = tq0[qp] >= 0 ? tang_c[(int64_t)(k * 8 + qp) * ne + e] : T(0);
+      for (int k = 0; k < 5; ++k) w[k] = *(at += st);
     };
-    if (APPLY_LIKE && MS == MS_J2)
+    if (APPLY_LIKE && J2M)
 #pragma unroll
       for (int q0 = 0; q0 < PF; ++q0) load_pw(q0, pw[q0]);
+    // Neo-Hookean operator: F^-T and ln J of the linearisation, stored by the residual per
+    // Gauss point ([10][8][n_el]), requested one point ahead of their use
+    T nw[NHB][10];
+    const bool nh_el = MS == MS_NH && pc.model == FE_NEOHOOKE;
+    auto load_nh = [&](int q4, T* w) {
+#pragma unroll
+      for (int k = 0; k < 10; ++k) w[k] = nh_el ? tang_c[e4 + (k * 8 + q4) * ne] : T(0);
+    };
+    if (APPLY_LIKE && MS == MS_NH) load_nh(0, nw[0]);
+
+    HalfGrad<T> g, s;  // gradients (times h), stress sums
+    half_gradients<T>([&](int k, int j, int i, int c) { return s_x[s0 + 3 * (i + NX * (j + NY * k)) + c]; }, w0, w1, g);
+    if constexpr (PARK) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        s_park[c][tid] = g.x[1][c];
+        s_park[3 + c][tid] = g.z[1][0][c];
+        s_park[6 + c][tid] = g.z[1][1][c];
+      }
+      asm volatile("" ::: "memory");  // (the values are to be read back, not kept)
+    }
+    // the operators are linear in the gradient, so 1/h goes into the final factor there
+    const T inv_h = APPLY_LIKE ? T(1) : T(1.0 / a.h);
+
     const T* st_in = static_cast<const T*>(a.state_in);
     T* st_out = static_cast<T*>(a.state_out);
     T* tang = static_cast<T*>(a.tangent);
 
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const int qp = p + 2 * q + 4 * r;
-          if (APPLY_LIKE && MS == MS_J2 && qp + PF < 8) load_pw(qp + PF, pw[(qp + PF) % (PF + 1)]);
-          if (APPLY_LIKE && MS == MS_NH && qp < 7) load_nh(qp + 1, nw[(qp + 1) & 1]);
-          T H[3][3], S[3][3];
+    for (int q = 0; q < 2; ++q) {
+      if constexpr (PARK) {
+        if (q == 1) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            H[c][0] = Gx[r][q][c];
-            H[c][1] = Gy[r][p][c];
-            H[c][2] = Gz[q][p][c];
+            g.x[1][c] = s_park[c][tid];
+            g.z[1][0][c] = s_park[3 + c][tid];
+            g.z[1][1][c] = s_park[6 + c][tid];
+            s_park[c][tid] = s.x[0][c];
+            s_park[3 + c][tid] = s.z[0][0][c];
+            s_park[6 + c][tid] = s.z[0][1][c];
           }
-          bool done = false;
-          if (MS == MS_J2 && pc.model == FE_J2) {
-            if (OP == OP_RESID) {
-              T epn[6], an = 0, ep[6], al, tn[6];
+          asm volatile("" ::: "memory");
+        }
+      }
 #pragma unroll
-              for (int k = 0; k < 6; ++k) epn[k] = st_in ? st_in[(int64_t)(k * 8 + qp) * ne + e] : T(0);
-              if (st_in) an = st_in[(int64_t)(6 * 8 + qp) * ne + e];
-              j2_update(H, epn, an, Kb, Gs, sy, Hh, S, ep, al, tn);
-              if (a.sur_mode != SUR_OFF) {
-                const int64_t pidx = (int64_t)qp * ne + e;
-                const bool ptrial = tn[0] >= 0;  // elastic trial is plastic: the surrogate's domain
-                if (a.sur_mode == SUR_CAPTURE) {
-                  const bool keep = ptrial && (((unsigned)pidx * 2654435761u + a.sur_salt) % a.sur_stride == 0);
-                  const unsigned slot = wave_append(a.sur_count, keep);
-                  if (keep && slot < a.sur_cap) {
-                    sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
-                    const T rt2 = T(1.41421356237309504880), is = T(1) / T(a.sur_sout);
-                    float* yo = a.sur_y + (int64_t)slot * 6;
-                    yo[0] = float(S[0][0] * is);
-                    yo[1] = float(S[1][1] * is);
-                    yo[2] = float(S[2][2] * is);
-                    yo[3] = float(S[1][2] * rt2 * is);
-                    yo[4] = float(S[0][2] * rt2 * is);
-                    yo[5] = float(S[0][1] * rt2 * is);
-                  }
-                } else if (a.sur_mode == SUR_CLASSIFY) {
-                  const unsigned slot = wave_append(a.sur_count, ptrial);
-                  const bool listed = ptrial && slot < a.sur_cap;
-                  a.sur_map[pidx] = listed ? (int)slot : -1;
-                  if (listed) sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
-                } else {  // SUR_CONSUME
-                  const int slot = a.sur_map[pidx];
-                  bool accepted = false, fallback = false;
-                  if (ptrial && slot >= 0) {
-                    T Ss[3][3], eps2[6], al2;
-                    float* Dsym = static_cast<float*>(a.sur_D) + (int64_t)slot * 36;
-                    accepted = sur_consume(H, epn, an, Kb, Gs, sy, Hh, a.sur_y + (int64_t)slot * 6,
-                                           a.sur_jac + (int64_t)slot * 36, a.sur_sin, a.sur_sout, a.sur_tol, tn,
-                                           Ss, eps2, al2, Dsym, a.sur_full);
-                    fallback = !accepted;
-                    if (accepted) {
+      for (int p = 0; p < 2; ++p) {
+        const int q4 = p + 2 * q;
+        if (APPLY_LIKE && J2M && q4 + PF < 4) load_pw(q4 + PF, pw[(q4 + PF) % (PF + 1)]);
+        if (APPLY_LIKE && MS == MS_NH && NHB == 2 && q4 < 3) load_nh(q4 + 1, nw[(q4 + 1) % NHB]);
+        T H[3][3], S[3][3];
 #pragma unroll
-                      for (int i = 0; i < 3; ++i)
+        for (int c = 0; c < 3; ++c) {
+          H[c][0] = APPLY_LIKE ? g.x[q][c] : g.x[q][c] * inv_h;
+          H[c][1] = APPLY_LIKE ? g.y[p][c] : g.y[p][c] * inv_h;
+          H[c][2] = APPLY_LIKE ? g.z[q][p][c] : g.z[q][p][c] * inv_h;
+        }
+        if constexpr (APPLY_LIKE && J2M) {
+          // one path for all points: a linear phase is an elastic point (tq0 = -1, N = 0)
+          const T K = T(pc.K) * sc, G = T(pc.G) * sc;
+          if (SUR && tq0[q4] < T(-1.5)) {  // surrogate tangent of this point
+            const int slot = a.sur_map[e4 + q4 * ne];
+            general_apply(H, static_cast<const float*>(a.sur_D) + (int64_t)slot * 36, S);
+          } else {
+            T lp, mp, beta;
+            const T(&w)[5] = pw[q4 % (PF + 1)];
+            const T N[6] = {w[0], w[1], -(w[0] + w[1]), w[2], w[3], w[4]};
+            j2_tangent_coeffs(tq0[q4], K, G, T(pc.H), lp, mp, beta);
+            j2_apply(H, lp, mp, beta, N, S);
+          }
+        } else if constexpr (OP == OP_RESID && J2M) {
+          if (pc.model == FE_J2) {
+            const T Kb = T(pc.K) * sc, Gs = T(pc.G) * sc, sy = T(pc.sy), Hh = T(pc.H);
+            T epn[6], an = 0, ep[6], al, tn[6];
 #pragma unroll
-                        for (int j = 0; j < 3; ++j) S[i][j] = Ss[i][j];
-#pragma unroll
-                      for (int k = 0; k < 6; ++k) ep[k] = eps2[k];
-                      al = al2;
-                      tn[0] = T(SUR_FLAG);
-                    }
-                  }
-                  wave_count(a.sur_stats, accepted);
-                  wave_count(a.sur_stats + 1, fallback);
+            for (int k = 0; k < 6; ++k) epn[k] = st_in ? st_in[e4 + (k * 8 + q4) * ne] : T(0);
+            if (st_in) an = st_in[e4 + (6 * 8 + q4) * ne];
+            j2_update(H, epn, an, Kb, Gs, sy, Hh, S, ep, al, tn);
+            if (SUR) {
+              const int64_t pidx = e4 + q4 * ne;
+              const bool ptrial = tn[0] >= 0;  // elastic trial is plastic: the surrogate's domain
+              if (a.sur_mode == SUR_CAPTURE) {
+                const bool keep = ptrial && (((unsigned)pidx * 2654435761u + a.sur_salt) % a.sur_stride == 0);
+                const unsigned slot = wave_append(a.sur_count, keep);
+                if (keep && slot < a.sur_cap) {
+                  sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
+                  const T rt2 = T(1.41421356237309504880), is = T(1) / T(a.sur_sout);
+                  float* yo = a.sur_y + (int64_t)slot * 6;
+                  yo[0] = float(S[0][0] * is);
+                  yo[1] = float(S[1][1] * is);
+                  yo[2] = float(S[2][2] * is);
+                  yo[3] = float(S[1][2] * rt2 * is);
+                  yo[4] = float(S[0][2] * rt2 * is);
+                  yo[5] = float(S[0][1] * rt2 * is);
                 }
-              }
-              if (st_out) {
+              } else if (a.sur_mode == SUR_CLASSIFY) {
+                const unsigned slot = wave_append(a.sur_count, ptrial);
+                const bool listed = ptrial && slot < a.sur_cap;
+                a.sur_map[pidx] = listed ? (int)slot : -1;
+                if (listed) sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
+              } else if (a.sur_mode == SUR_CONSUME) {
+                const int slot = a.sur_map[pidx];
+                bool accepted = false, fallback = false;
+                if (ptrial && slot >= 0) {
+                  T Ss[3][3], eps2[6], al2;
+                  float* Dsym = static_cast<float*>(a.sur_D) + (int64_t)slot * 36;
+                  accepted = sur_consume(H, epn, an, Kb, Gs, sy, Hh, a.sur_y + (int64_t)slot * 6,
+                                         a.sur_jac + (int64_t)slot * 36, a.sur_sin, a.sur_sout, a.sur_tol, tn,
+                                         Ss, eps2, al2, Dsym, a.sur_full);
+                  fallback = !accepted;
+                  if (accepted) {
 #pragma unroll
-                for (int k = 0; k < 6; ++k) st_out[(int64_t)(k * 8 + qp) * ne + e] = ep[k];
-                st_out[(int64_t)(6 * 8 + qp) * ne + e] = al;
-              }
-              if (a.store_tangent) {
+                    for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int k = 0; k < 6; ++k) tang[(int64_t)(k * 8 + qp) * ne + e] = tn[k];
-              }
-              done = true;
-            } else if (APPLY_LIKE) {
-              T tn[6], lp, mp, beta, N[6];
-              tn[0] = tq0[qp];
-              if (tn[0] < T(-1.5)) {  // surrogate tangent of this point
-                const int slot = a.sur_map[(int64_t)qp * ne + e];
-                general_apply(H, static_cast<const float*>(a.sur_D) + (int64_t)slot * 36, S);
-              } else {
+                      for (int j = 0; j < 3; ++j) S[i][j] = Ss[i][j];
 #pragma unroll
-                for (int k = 1; k < 6; ++k) tn[k] = pw[qp % (PF + 1)][k - 1];
-                j2_tangent_coeffs(tn, Kb, Gs, Hh, lp, mp, beta, N);
-                j2_apply(H, lp, mp, beta, N, S);
+                    for (int k = 0; k < 6; ++k) ep[k] = eps2[k];
+                    al = al2;
+                    tn[0] = T(SUR_FLAG);
+                  }
+                }
+                wave_count(a.sur_stats, accepted);
+                wave_count(a.sur_stats + 1, fallback);
               }
-              done = true;
+            }
+            if (st_out) {
+#pragma unroll
+              for (int k = 0; k < 6; ++k) st_out[e4 + (k * 8 + q4) * ne] = ep[k];
+              st_out[e4 + (6 * 8 + q4) * ne] = al;
+            }
+            if (a.store_tangent) {
+#pragma unroll
+              for (int k = 0; k < 6; ++k) tang[e4 + (k * 8 + q4) * ne] = tn[k];
+            }
+          } else {
+            hooke(H, T(pc.lam) * sc, T(pc.mu) * sc, S);
+            if (st_out) {  // non-J2 phase: state passes through
+#pragma unroll
+              for (int k = 0; k < 7; ++k)
+                st_out[e4 + (k * 8 + q4) * ne] = st_in ? st_in[e4 + (k * 8 + q4) * ne] : T(0);
             }
           }
+        } else {
+          const T lam = T(pc.lam) * sc, mu = T(pc.mu) * sc;
           if (MS == MS_NH && pc.model == FE_NEOHOOKE) {
-            if (APPLY_LIKE) {
-              T FiT[3][3];
-#pragma unroll
-              for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) FiT[i][j] = nw[qp & 1][3 * i + j];
-              nh_apply(H, FiT, nw[qp & 1][9], lam, mu, S);
+            if constexpr (APPLY_LIKE) {
+              const T(&w)[10] = nw[q4 % NHB];
+              const T FiT[3][3] = {{w[0], w[1], w[2]}, {w[3], w[4], w[5]}, {w[6], w[7], w[8]}};
+              nh_apply(H, FiT, w[9], lam, mu, S);
             } else {
               T FiT[3][3], lnJ;
               if (!nh_kin(H, FiT, lnJ) && a.flags) atomicOr(a.flags, 1);
@@ -673,37 +705,49 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
                 for (int i = 0; i < 3; ++i)
 #pragma unroll
-                  for (int j = 0; j < 3; ++j) tang[(int64_t)((3 * i + j) * 8 + qp) * ne + e] = FiT[i][j];
-                tang[(int64_t)(9 * 8 + qp) * ne + e] = lnJ;
+                  for (int j = 0; j < 3; ++j) tang[e4 + ((3 * i + j) * 8 + q4) * ne] = FiT[i][j];
+                tang[e4 + (9 * 8 + q4) * ne] = lnJ;
               }
             }
-            done = true;
-          }
-          if (!done) {
+          } else {
             hooke(H, lam, mu, S);
-            if (MS == MS_J2 && OP == OP_RESID && st_out) {  // non-J2 phase: state passes through
-#pragma unroll
-              for (int k = 0; k < 7; ++k)
-                st_out[(int64_t)(k * 8 + qp) * ne + e] = st_in ? st_in[(int64_t)(k * 8 + qp) * ne + e] : T(0);
-            }
           }
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            Px[r][q][c] += S[c][0];
-            Py[r][p][c] += S[c][1];
-            Pz[q][p][c] += S[c][2];
-          }
-          if (OP == OP_RESID && a.stress_sum) {
-            ssum[0] += S[0][0];
-            ssum[1] += S[1][1];
-            ssum[2] += S[2][2];
-            ssum[3] += S[1][2];
-            ssum[4] += S[0][2];
-            ssum[5] += S[0][1];
-          }
+          if (APPLY_LIKE && MS == MS_NH && NHB == 1 && q4 < 3) load_nh(q4 + 1, nw[0]);
         }
-    // w_q detJ = h^3/8, physical derivative factor 1/h
-    push_back(Px, Py, Pz, T(0.125) * h * h, Fo);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          s.x[q][c] = p == 0 ? S[c][0] : s.x[q][c] + S[c][0];
+          s.y[p][c] = q == 0 ? S[c][1] : s.y[p][c] + S[c][1];
+          s.z[q][p][c] = S[c][2];
+        }
+        if (OP == OP_RESID && sizeof(T) == 4 && a.stress_sum) {
+          ssum[0] += S[0][0];
+          ssum[1] += S[1][1];
+          ssum[2] += S[2][2];
+          ssum[3] += S[1][2];
+          ssum[4] += S[0][2];
+          ssum[5] += S[0][1];
+        }
+      }
+    }
+    if constexpr (PARK) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        s.x[0][c] = s_park[c][tid];
+        s.z[0][0][c] = s_park[3 + c][tid];
+        s.z[0][1][c] = s_park[6 + c][tid];
+      }
+    }
+    if (OP == OP_RESID && sizeof(T) == 8 && a.stress_sum) {  // the point sums hold every stress entry
+      ssum[0] = s.x[0][0] + s.x[1][0];
+      ssum[1] = s.y[0][1] + s.y[1][1];
+      ssum[2] = (s.z[0][0][2] + s.z[0][1][2]) + (s.z[1][0][2] + s.z[1][1][2]);
+      ssum[3] = (s.z[0][0][1] + s.z[0][1][1]) + (s.z[1][0][1] + s.z[1][1][1]);
+      ssum[4] = (s.z[0][0][0] + s.z[0][1][0]) + (s.z[1][0][0] + s.z[1][1][0]);
+      ssum[5] = s.y[0][0] + s.y[1][0];
+    }
+    // w_q detJ = h^3/8, physical derivative factor 1/h (and the operators' gradient factor 1/h)
+    half_push_back(s, w0, w1, APPLY_LIKE ? T(0.125) * h : T(0.125) * h * h, F);
   }
 
   if (OP == OP_RESID && a.stress_sum) {
@@ -713,7 +757,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
       double v = ssum[k] * w;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-      if ((tid & 63) == 0) s_red[k][tid >> 6] = v;
+      if (br.lane == 0) s_red[k][br.wave] = v;
     }
   }
 
@@ -722,21 +766,19 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
   if constexpr (OP == OP_RESID || OP == OP_APPLY) {
     if (a.elf) {
       if (valid) {
-        T* F = static_cast<T*>(a.elf);
+        T* E = static_cast<T*>(a.elf);
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int c = 0; c < 3; ++c) F[(int64_t)(3 * (i + 2 * j + 4 * k) + c) * ne + e] = Fo[k][j][i][c];
+            for (int c = 0; c < 3; ++c) E[(int64_t)(3 * (i + 2 * j + 4 * r) + c) * ne + e] = F[j][i][c];
       }
       if (OP == OP_RESID && a.stress_sum) {
         __syncthreads();
         if (tid < 6) {
           double v = 0;
-          for (int w = 0; w < EBLOCK / 64; ++w) v += s_red[tid][w];
+          for (int w = 0; w < EWAVES; ++w) v += s_red[tid][w];
           a.stress_part[(int64_t)blockIdx.x * 6 + tid] = v;
         }
       }
@@ -744,10 +786,11 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
     }
   }
 
-  if (OP == OP_VJP) {
+  if constexpr (OP == OP_VJP) {
+    // the element's nodal forces sum to zero, so lambda may be taken relative to its
+    // element mean: exact, and it removes the cancellation of a large rigid part
+    double d = 0;
     if (valid) {
-      // the element's nodal forces sum to zero, so lambda may be taken relative to its
-      // element mean: exact, and it removes the cancellation of a large rigid part
       double lm[3] = {0, 0, 0};
 #pragma unroll
       for (int k = 0; k < 2; ++k)
@@ -756,77 +799,56 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) lm[c] += (double)s_l[3 * ((ex + i) + NX * ((ey + j) + NY * (ez + k))) + c];
-      double d = 0;
+            for (int c = 0; c < 3; ++c) lm[c] += (double)s_l[s0 + 3 * (i + NX * (j + NY * k)) + c];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-              d += (double)Fo[k][j][i][c] *
-                   ((double)s_l[3 * ((ex + i) + NX * ((ey + j) + NY * (ez + k))) + c] - 0.125 * lm[c]);
-      static_cast<T*>(a.out_el)[e] = T(d);
+          for (int c = 0; c < 3; ++c)
+            d += (double)F[j][i][c] * ((double)s_l[s0 + 3 * (i + NX * (j + NY * r)) + c] - 0.125 * lm[c]);
     }
+    d += __shfl_xor(d, 32, 64);
+    if (valid && r == 0) static_cast<T*>(a.out_el)[e] = T(d);
     return;
   }
 
-  // CG: element part of p.Ap = sum_e p_e . K_e p_e (p masked on constrained dofs)
-  double pq = 0;
-  if (OP == OP_CG_APPLY && valid) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            pq += (double)Fo[k][j][i][c] * (double)s_x[3 * ((ex + i) + NX * ((ey + j) + NY * (ez + k))) + c];
-  }
-
-  // nodal sums in LDS: workgroup-scope FP64 atomic adds by all lanes at once (one corner per
-  // instruction, so the lanes of a wave address distinct nodes); measured 12 % faster per
-  // FP64 CG iteration than 8 colour passes with a barrier each (FP32 float LDS atomics were
-  // twice as slow as the passes, hence FP64 sums for FP32 problems as well)
   if (valid) {
+    // nodal sums in LDS: workgroup-scope FP64 atomic adds by all lanes at once (one corner per
+    // instruction, so the lanes of a wave address distinct nodes); measured 12 % faster per
+    // FP64 CG iteration than 8 colour passes with a barrier each (FP32 float LDS atomics were
+    // twice as slow as the passes, hence FP64 sums for FP32 problems as well).
+    // CG: element part of p.Ap = sum_e p_e . K_e p_e (p masked on constrained dofs)
+    const int sr = s0 + 3 * NX * NY * r;
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            __hip_atomic_fetch_add(&s_y[3 * ((ex + i) + NX * ((ey + j) + NY * (ez + k))) + c],
-                                   (Acc)Fo[k][j][i][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int c = 0; c < 3; ++c) {
+          const int w = sr + 3 * (i + NX * j) + c;
+          if (OP == OP_CG_APPLY) pq += (double)F[j][i][c] * (double)s_x[w];
+          __hip_atomic_fetch_add(&s_y[w], (Acc)F[j][i][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
   }
   __syncthreads();
 
   if (OP == OP_RESID && a.stress_sum && tid < 6) {
     double v = 0;
-    for (int w = 0; w < EBLOCK / 64; ++w) v += s_red[tid][w];
+    for (int w = 0; w < EWAVES; ++w) v += s_red[tid][w];
     atomic_add(a.stress_sum + tid, v);
   }
 
   T* Y = static_cast<T*>(a.y);
   if (!Y) return;
-#pragma unroll 1  // (unrolled, the instance spills)
-  for (int t = 0; t < STAGE_IT; ++t) {
-    const int i = tid + t * EBLOCK;
-    if (i >= NN * 3) break;
-    const int c = i % 3, nd = i / 3;
-    const int li = nd % NX, lj = (nd / NX) % NY, lk = nd / (NX * NY);
-    const int gi = a0 + li, gj = b0 + lj, gk = c0 + lk;
-    if (gi > n || gj > n || gk > n) continue;
-    const int64_t dof = 3 * (gi + np1 * (gj + np1 * gk)) + c;
-    const bool own = (min(gi, n - 1) - a0 < TX) && (min(gj, n - 1) - b0 < TY) && (min(gk, n - 1) - c0 < TZ);
-    const bool priv = (gi == 0 || li >= 1) && (gi == n || li < TX) && (gj == 0 || lj >= 1) && (gj == n || lj < TY) &&
-                      (gk == 0 || lk >= 1) && (gk == n || lk < TZ);
-    if (s_fx[i]) {
-      if (own) {
+#pragma unroll
+  for (int t = 0; t < ROW_IT; ++t) {
+    const Brick::Row rw = br.row(t);
+    if (!rw.live || !br.inx) continue;
+    const int i = rw.row * ROWW + br.lane;
+    const int64_t dof = rw.word + br.off;
+    if (fixed & (1u << t)) {
+      if (rw.own && br.ownx) {
         if (OP == OP_CG_APPLY) {  // A u = u on constrained dofs; their (u, A u) share is u^2
           const T v = s_b[i];
           Y[dof] = v;
@@ -835,35 +857,21 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
           Y[dof] = (OP == OP_APPLY) ? X[dof] : T(0);
         }
       }
-      continue;
-    }
-    if (priv)
+    } else if (rw.priv && br.privx) {
       Y[dof] = T(s_y[i]);
-    else
+    } else {
       atomic_add(Y + dof, T(s_y[i]));
-  }
-  if (OP == OP_CG_APPLY) {  // partials of (u_j, A u_j), (r_j, u_j), ||r_j||^2
-    double q3[3] = {pq, cg_g, cg_rr};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) q3[k] += __shfl_down(q3[k], off, 64);
     }
-    if ((tid & 63) == 0)
+  }
+  if constexpr (OP == OP_CG_APPLY) {  // partials of (u_j, A u_j), (r_j, u_j), ||r_j||^2
 #pragma unroll
-      for (int k = 0; k < 3; ++k) s_red[3 + k][tid >> 6] = q3[k];
+    for (int off = 32; off > 0; off >>= 1) pq += __shfl_down(pq, off, 64);
+    if (br.lane == 0) s_red[3][br.wave] = pq;
     __syncthreads();
-    if (threadIdx.x == 0) {  // workgroups share CGS_SLOTS slots per quantity
-      double t0 = 0, t1 = 0, t2 = 0;
-      for (int w = 0; w < EBLOCK / 64; ++w) {
-        t0 += s_red[3][w];
-        t1 += s_red[4][w];
-        t2 += s_red[5][w];
-      }
-      const int sl = (int)(blockIdx.x % CGS_SLOTS);
-      atomic_add(a.cg_acc_out + sl, t0);
-      atomic_add(a.cg_acc_out + CGS_SLOTS + sl, t1);
-      atomic_add(a.cg_acc_out + 2 * CGS_SLOTS + sl, t2);
+    if (threadIdx.x < 3) {  // workgroups share CGS_SLOTS slots per quantity
+      double t = 0;
+      for (int w = 0; w < EWAVES; ++w) t += s_red[3 + threadIdx.x][w];
+      atomic_add(a.cg_acc_out + threadIdx.x * CGS_SLOTS + (int)(blockIdx.x % CGS_SLOTS), t);
     }
   }
 }
@@ -876,25 +884,28 @@ static int elem_grid(int n) {
 template <typename T, int OP>
 static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
   const dim3 grid(elem_grid(p->n)), block(EBLOCK);
+  // J2 problems that may meet surrogate points (their stored tangents, or a surrogate / capture
+  // mode of this residual) take the instance with those branches
+  const bool sur = p->model_set == MS_J2 && (OP == OP_RESID ? a.sur_mode != SUR_OFF : p->sur_map != nullptr);
+  const int ms = OP != OP_VJP && sur ? (int)MS_SUR : p->model_set;
   if constexpr (sizeof(T) == 4 && OP != OP_VJP) {
     if (p->acc32) {
-      switch (p->model_set) {
+      switch (ms) {
         case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2, true>), grid, block, 0, s, a, stop); break;
         case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH, true>), grid, block, 0, s, a, stop); break;
+        case MS_SUR: timed_launch((elem_kernel<T, OP, MS_SUR, true>), grid, block, 0, s, a, stop); break;
         default: timed_launch((elem_kernel<T, OP, MS_LINEAR, true>), grid, block, 0, s, a, stop);
       }
       return hipGetLastError();
     }
   }
-  switch (p->model_set) {
-    case MS_J2:
-      timed_launch((elem_kernel<T, OP, MS_J2>), grid, block, 0, s, a, stop);
+  switch (ms) {
+    case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2>), grid, block, 0, s, a, stop); break;
+    case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH>), grid, block, 0, s, a, stop); break;
+    case MS_SUR:
+      if constexpr (OP != OP_VJP) timed_launch((elem_kernel<T, OP, MS_SUR>), grid, block, 0, s, a, stop);
       break;
-    case MS_NH:
-      timed_launch((elem_kernel<T, OP, MS_NH>), grid, block, 0, s, a, stop);
-      break;
-    default:
-      timed_launch((elem_kernel<T, OP, MS_LINEAR>), grid, block, 0, s, a, stop);
+    default: timed_launch((elem_kernel<T, OP, MS_LINEAR>), grid, block, 0, s, a, stop);
   }
   return hipGetLastError();
 }
