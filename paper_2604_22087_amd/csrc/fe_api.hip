@@ -806,6 +806,7 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
     if (chunk < 32) chunk *= 2;
   }
   const CgCtrl& c = *p->host_ctrl;
+  if (fused) HIPCHK(cgs_flush(p, x, c.iters, s));
   const int status = c.status == CG_RUNNING ? FE_ERR_NOT_CONVERGED : (c.status == CG_CONVERGED ? FE_OK : c.status);
   // operator launches after the stopping iteration returned at once: drop their timings
   // (the fused form runs one launch more than iterations: launch j forms u_j = M^-1 r_j)
@@ -818,9 +819,10 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
     const size_t timed = p->prof_recs.size() - rec0;
     double b = 0;
     if (int e = operator_bytes(p, op, s, &b)) return e;
-    // the fused matrix-free CG launch reads r, w, s, p, x and M^-1 (1 or 2 reals per dof)
-    // and writes r, s, p, x and the zeroed w instead of reading x
-    if (fused) b += (p->precond == FE_PC_BLOCK_JACOBI ? 11.0 : 10.0) * (double)real_size(p) * (double)p->n_dof;
+    // the fused matrix-free CG launch reads r, w, s and M^-1 (1 or 2 reals per dof) and writes
+    // r, s and the zeroed w instead of reading x; every second launch also reads r_{j-2}, p and x
+    // and writes p and x
+    if (fused) b += (p->precond == FE_PC_BLOCK_JACOBI ? 9.5 : 8.5) * (double)real_size(p) * (double)p->n_dof;
     p->prof_bytes[cls] += b * (double)timed;
   }
   if (info) {

@@ -20,13 +20,32 @@ constexpr int VGRID_MAX = 1024; // vector kernels: blocks (== partial-sum slots)
 
 template <typename T> __device__ __forceinline__ void atomic_add(T* p, T v) { unsafeAtomicAdd(p, v); }
 
+// v + the value of another lane chosen by a DPP control (0 where there is none): one step of a
+// wavefront sum without a trip through the LDS crossbar.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+  return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Sum over the 64 lanes of a wavefront, valid in lane 63 (WAVE_LAST); all lanes take part.
+constexpr int WAVE_LAST = 63;
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: sums of 16 lanes in lane 15 of each row
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+}
+
 // Block sum of a double over 256 lanes; the result is valid in lane 0.
 __device__ __forceinline__ double block_sum(double v, double* sh) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v = wave_sum_last(v);
   const int w = threadIdx.x >> 6;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[w] = v;
   __syncthreads();
   double r = 0;
   if (threadIdx.x == 0)

@@ -105,7 +105,7 @@ struct CgCtrl {
   int status;       // CG_RUNNING, CG_CONVERGED or an fe_status error code
   int max_it;
   int pad;
-  double ghist[2], ahist[2];  // single-reduction CG: (r, M^-1 r) and alpha of iterate i in slot i & 1
+  double ghist[2], ahist[2], bhist[2];  // single-reduction CG: (r, M^-1 r), alpha, beta of iterate i in slot i & 1
 };
 
 // Device scalar block of BiCGStab (one per problem).
@@ -142,6 +142,7 @@ struct ElemArgs {
   int apply_bc;
   int store_tangent;
   Phases mat;
+  unsigned j2_mask;       // bit i: phase i is a J2 phase (set by the launch)
   // learned surrogate at J2 points whose elastic trial is plastic
   int sur_mode;           // SUR_OFF / SUR_CAPTURE / SUR_CLASSIFY / SUR_CONSUME
   int* sur_map;           // [8][n_el] list slot of each point, -1 if none
@@ -159,13 +160,13 @@ struct ElemArgs {
   // OP_CG_APPLY only (single-reduction CG, one operator launch per iteration; see the kernel)
   long cg_j;              // launch index j; launch 0 makes no update, only u_0 = M^-1 b and w_0 = A u_0
   const void* cg_rold;    // r_{j-1}
-  void* cg_rnew;          // r_j (written by owners)
+  void* cg_rnew;          // r_j (written by owners; holds r_{j-2} before)
   const void* cg_wold;    // w_{j-1} = A u_{j-1}
   void* cg_wzero;         // the w buffer of launch j+1 (zeroed by owners)
   const void* cg_sold;    // s_{j-2}
   void* cg_snew;          // s_{j-1} (written by owners)
-  void* cg_pvec;          // p (updated in place by owners)
-  void* cg_x;             // x (updated in place by owners)
+  void* cg_pvec;          // p (updated in place by owners, two steps in every even launch)
+  void* cg_x;             // x (likewise)
   const void* cg_dinv;    // preconditioner: inverse diagonal [n_dof] or inverse node blocks [n_nodes][6]
   int cg_block;           // 1: node-block Jacobi
   CgCtrl* ctrl;           // scalars and status (workgroup 0 writes those of launch j)
@@ -378,6 +379,7 @@ hipError_t ilu_apply(const fe_problem* p, const void* r, void* z, const int* sto
 // iteration (its last workgroup computes the scalars of the next launch)
 hipError_t cgs_init(const fe_problem* p, const void* b, void* x, double rtol, int max_it, hipStream_t s);
 hipError_t cgs_operator(const fe_problem* p, void* x, long j, hipStream_t s);
+hipError_t cgs_flush(const fe_problem* p, void* x, int iters, hipStream_t s);  // after the stop: completes x
 int elem_grid_size(int n);  // workgroups of an element-kernel launch (also the partial-sum slots it needs)
 
 // general hex8 meshes (fe_general.hip); TanArgs is defined in fe_device.hpp

@@ -1,7 +1,7 @@
 // HIP kernels of libfe for gfx950 (MI355X).
 //
-// Element kernels work on bricks of TX x TY x TZ = 16 x 4 x 4 elements, two lanes per element
-// (lane half r takes the four Gauss points of reference layer z = r), 512 lanes per workgroup:
+// Element kernels work on bricks of TX x TY x TZ = 16 x 4 x 2 elements, two lanes per element
+// (lane half r takes the four Gauss points of reference layer z = r), 256 lanes per workgroup:
 //   1. the brick's (TX+1)(TY+1)(TZ+1) nodal values are staged in LDS, one wave per node row
 //      (the row's address and its place in the brick are scalars, the lane is the offset);
 //   2. each lane forms the displacement gradient at its 4 Gauss points by sum factorisation of
@@ -15,7 +15,9 @@
 //      added with hardware FP atomics.
 // What bounds them is latency more than bytes (staging loads, then a serial chain of points), so
 // the split aims at waves in flight: one lane per element needs 231 registers for its 72 table
-// entries (two waves per SIMD, the FP64 J2 residual spilled), half an element fits in 128.
+// entries (two waves per SIMD, the FP64 J2 residual spilled), half an element fits in 128.  Small
+// workgroups keep the phases of a CU's residents apart: CG launch at 64^3 FP64 with bricks of 4, 2
+// and 1 element layers 37.5, 34.0 and 50.1 us (halo 1.66, 1.99, 2.66 nodes staged per element).
 // Bricks are numbered so that consecutive bricks land on one XCD (workgroups
 // are dealt round-robin over the 8 XCDs), keeping shared face nodes in one L2.
 #include "fe_internal.hpp"
@@ -28,13 +30,16 @@ LaunchEvents& launch_events() {
   return ev;
 }
 
-constexpr int TX = 16, TY = 4, TZ = 4;
+constexpr int TX = 16, TY = 4, TZ = 2;
 constexpr int NX = TX + 1, NY = TY + 1, NZ = TZ + 1, NN = NX * NY * NZ;
 constexpr int EBLOCK = 2 * TX * TY * TZ;     // two lanes per element
 constexpr int EWAVES = EBLOCK / 64;
 constexpr int ROWW = 3 * NX, NROWS = NY * NZ;  // a brick's node rows (along x): words per row, rows
 constexpr int ROW_IT = (NROWS + EWAVES - 1) / EWAVES;
-static_assert(TX == 16 && TY == 4 && EBLOCK == 512 && ROWW <= 64, "lane layout of the element kernel");
+constexpr int NACC = (3 * CGS_SLOTS + EBLOCK - 1) / EBLOCK;  // reduction slots per lane
+static_assert(TX == 16 && TY == 4 && ROWW <= 64, "lane layout of the element kernel");
+static_assert(CGS_SLOTS == 256, "four waves per reduced quantity");
+
 
 // CG direction step of iteration k (see the CG section below); false when the
 // iteration stops (block 0 records the status).
@@ -224,12 +229,22 @@ struct Brick {
 // in order, so the scalar step below waits for the slot sums alone), forms alpha, beta, and then
 //   s_{j-1} = w_{j-1} + beta s_{j-2},  r_j = r_{j-1} - alpha s_{j-1},  u_j = M^-1 r_j
 // (launch 0: r_0 = b, u_0 = M^-1 b).  Every brick that touches a node forms the same u_j; the
-// owner also stores s_{j-1}, r_j, p_{j-1} = u_{j-1} + beta p_{j-2}, x_j = x_{j-1} + alpha p_{j-1},
-// zeroes the w buffer of launch j+1 and adds its shares of (r_j, u_j) and ||r_j||^2.
+// owner also stores s_{j-1}, r_j, zeroes the w buffer of launch j+1 and adds its shares of
+// (r_j, u_j) and ||r_j||^2.  p and x, which no later staging needs, advance two steps in every
+// even launch (five vector accesses per two iterations instead of eight: the launch is bound by
+// this traffic, its element work adds a quarter to the time of staging and write-out alone):
+//   p_i = M^-1 r_i + beta_i p_{i-1},  x_{i+1} = x_i + alpha_i p_i  for i = j-2 and j-1,
+// with r_{j-2} read from the buffer that r_j replaces.  cgs_flush makes up the last odd step.
 // u_j goes to s_x (0 on constrained dofs, whose value goes to s_b), s_y is cleared.
+// The scalars of earlier launches that launch j uses (workgroup 0 of launch j writes none of them).
+struct CgHist {
+  double rtol2, tol2, g, alpha, beta;  // g, alpha, beta of iterate j-2
+  int status, max_it;
+};
+
 template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[2], double (*sh)[EWAVES],
-                                           T& alpha_out, T& beta_out);
+__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const CgHist& c, const double v_in[NACC],
+                                           double (*sh)[EWAVES], T& alpha_out, T& beta_out);
 
 // (the node's three components sit in adjacent lanes of the row: node-block Jacobi fetches the
 // other two by lane exchange)
@@ -237,21 +252,26 @@ template <typename T, bool BLK, typename Acc, typename Early>
 __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& br, double (*sh)[EWAVES], T* s_x,
                                                Acc* s_y, T* s_b, unsigned& fixed, double& g, double& rr,
                                                Early&& early) {
-  static_assert(2 * CGS_SLOTS == EBLOCK, "lanes per reduction slot");
   // the previous launch's slot sums are requested before the staging loads (loads return in
   // order), so the scalar reduction overlaps the staging traffic
-  double acc_v[2] = {0, 0};
+  double acc_v[NACC] = {};
   const bool prev = a.cg_j > 0;
   if (prev) {
-    acc_v[0] = a.cg_acc_in[threadIdx.x];
-    if (br.wave < EWAVES / 2) acc_v[1] = a.cg_acc_in[EBLOCK + threadIdx.x];
+#pragma unroll
+    for (int k = 0; k < NACC; ++k)
+      if (br.wave + k * EWAVES < 12) acc_v[k] = a.cg_acc_in[k * EBLOCK + threadIdx.x];
   }
+  // requested with everything else: one wait instead of a test of the status word before any load
+  const CgCtrl* cc = a.ctrl;
+  const int slot = (int)(a.cg_j & 1);
+  const CgHist ctl = {cc->rtol2, cc->tol2, cc->ghist[slot], cc->ahist[slot], cc->bhist[slot], cc->status, cc->max_it};
   T alpha = 0, beta = 0;
+  const bool two = a.cg_j >= 2 && (a.cg_j & 1) == 0;  // p and x advance
   const T* __restrict__ RO = static_cast<const T*>(a.cg_rold);
   const T* __restrict__ WO = static_cast<const T*>(a.cg_wold);
   const T* __restrict__ SO = static_cast<const T*>(a.cg_sold);
   const T* __restrict__ M = static_cast<const T*>(a.cg_dinv);
-  T* __restrict__ RN = static_cast<T*>(a.cg_rnew);
+  T* RN = static_cast<T*>(a.cg_rnew);
   T* __restrict__ SN = static_cast<T*>(a.cg_snew);
   T* __restrict__ P = static_cast<T*>(a.cg_pvec);
   T* __restrict__ X = static_cast<T*>(a.cg_x);
@@ -261,10 +281,10 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
   const int c = br.off % 3;
   const int i0 = c == 0 ? 0 : (c == 1 ? 5 : 4), i1 = c == 0 ? 5 : (c == 1 ? 1 : 3), i2 = c == 0 ? 4 : (c == 1 ? 3 : 2);
   unsigned char mk[ROW_IT];
-  T ro[ROW_IT], wo[ROW_IT], so[ROW_IT], m[ROW_IT][BLK ? 3 : 1], po[ROW_IT], xo[ROW_IT];
+  T ro[ROW_IT], wo[ROW_IT], so[ROW_IT], m[ROW_IT][BLK ? 3 : 1], r2[ROW_IT], po[ROW_IT], xo[ROW_IT];
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
-    ro[t] = wo[t] = so[t] = po[t] = xo[t] = T(0);
+    ro[t] = wo[t] = so[t] = r2[t] = po[t] = xo[t] = T(0);
     mk[t] = 0;
     const Brick::Row r = br.row(t);
     if (!r.live) continue;
@@ -283,13 +303,16 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
       m[t][0] = M[dof];
     }
     if (mask) mk[t] = mask[dof];
-    if (!first && r.own) {
+    if (two && r.own) {
+      r2[t] = RN[dof];
       po[t] = P[dof];
       xo[t] = X[dof];
     }
   }
   early();
-  if (prev && !cg_scalars<T>(a, acc_v, sh, alpha, beta)) return false;
+  if (ctl.status) return false;  // the solve has stopped
+  if (prev && !cg_scalars<T>(a, ctl, acc_v, sh, alpha, beta)) return false;
+  const T alpha2 = T(ctl.alpha), beta2 = T(ctl.beta);
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
     const Brick::Row r = br.row(t);
@@ -299,22 +322,26 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
     const bool fx = mkv != 0;
     const T sn = wo[t] + beta * so[t];
     const T rn = first ? ro[t] : ro[t] - alpha * sn;
-    T u, uo;
+    T u, uo, u2;  // M^-1 of r_j, r_{j-1}, r_{j-2}
     if constexpr (BLK) {
       const int l0 = br.off - c;
       u = m[t][0] * __shfl(rn, l0, 64) + m[t][1] * __shfl(rn, l0 + 1, 64) + m[t][2] * __shfl(rn, l0 + 2, 64);
       uo = m[t][0] * __shfl(ro[t], l0, 64) + m[t][1] * __shfl(ro[t], l0 + 1, 64) + m[t][2] * __shfl(ro[t], l0 + 2, 64);
+      u2 = m[t][0] * __shfl(r2[t], l0, 64) + m[t][1] * __shfl(r2[t], l0 + 1, 64) + m[t][2] * __shfl(r2[t], l0 + 2, 64);
     } else {
       u = m[t][0] * rn;
       uo = m[t][0] * ro[t];
+      u2 = m[t][0] * r2[t];
     }
     if (r.own && br.ownx) {
       const int64_t dof = r.word + br.off;
       WZ[dof] = 0;
+      if (two) {
+        const T p2 = u2 + beta2 * po[t], p1 = uo + beta * p2;
+        P[dof] = p1;
+        X[dof] = xo[t] + alpha2 * p2 + alpha * p1;
+      }
       if (!first) {
-        const T pn = uo + beta * po[t];
-        P[dof] = pn;
-        X[dof] = xo[t] + alpha * pn;
         SN[dof] = sn;
         RN[dof] = rn;
       }
@@ -345,39 +372,37 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
 // (g, alpha) of iterate j-1 go to history slot (j-1) & 1 while slot j & 1 is read.
 // Returns false when the iteration stops (every workgroup reaches the same decision).
 template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[2], double (*sh)[EWAVES],
-                                           T& alpha_out, T& beta_out) {
+__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const CgHist& c, const double v_in[NACC],
+                                           double (*sh)[EWAVES], T& alpha_out, T& beta_out) {
   const long j = a.cg_j;
-  double v[2] = {v_in[0], v_in[1]};  // waves 0-3: d and rr slots, waves 4-7: g slots
+  double v[NACC];  // 64 slots per wave; the 12 wave sums are four each of d, g and rr
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
+  for (int k = 0; k < NACC; ++k) v[k] = wave_sum_last(v_in[k]);
+  if ((threadIdx.x & 63) == WAVE_LAST)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) sh[k][threadIdx.x >> 6] = v[k];
+    for (int k = 0; k < NACC; ++k) sh[k][threadIdx.x >> 6] = v[k];
   __syncthreads();
   double d = 0, g = 0, rr = 0;
-  for (int w = 0; w < EWAVES / 2; ++w) {
-    d += sh[0][w];
-    g += sh[0][EWAVES / 2 + w];
-    rr += sh[1][w];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    d += (&sh[0][0])[w];
+    g += (&sh[0][0])[4 + w];
+    rr += (&sh[0][0])[8 + w];
   }
   __syncthreads();  // sh is reused by the caller
-  const CgCtrl* c = a.ctrl;
   const int slot = (int)(j & 1);  // history of iterate j-2
-  const double tol2 = j == 1 ? c->rtol2 * rr : c->tol2;
+  const double tol2 = j == 1 ? c.rtol2 * rr : c.tol2;
   int st = CG_RUNNING;
   double alpha = 0, beta = 0;
   if (!finite(d) || !finite(g) || !finite(rr)) {
     st = FE_ERR_NONFINITE;
   } else if (j == 1 ? rr == 0.0 : rr <= tol2) {
     st = CG_CONVERGED;
-  } else if (j - 1 >= c->max_it) {
+  } else if (j - 1 >= c.max_it) {
     st = FE_ERR_NOT_CONVERGED;
   } else {
-    beta = j == 1 ? 0.0 : g / c->ghist[slot];
-    const double den = j == 1 ? d : d - beta * g / c->ahist[slot];
+    beta = j == 1 ? 0.0 : g / c.g;
+    const double den = j == 1 ? d : d - beta * g / c.alpha;
     if (!finite(den)) st = FE_ERR_NONFINITE;
     else if (den <= 0.0) st = FE_ERR_BREAKDOWN;
     else alpha = g / den;
@@ -395,6 +420,7 @@ __device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const double v_in[
     w->beta = beta;
     w->ghist[slot ^ 1] = g;
     w->ahist[slot ^ 1] = alpha;
+    w->bhist[slot ^ 1] = beta;
     if (st != CG_RUNNING) w->status = st;
   }
   alpha_out = T(alpha);
@@ -427,13 +453,14 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   __shared__ T s_l[NEED_L ? NN * 3 : 1];
   __shared__ T s_b[OP == OP_CG_APPLY ? NN * 3 : 1];  // CG: u on constrained dofs (A u = u there)
   __shared__ double s_red[6][EWAVES];
+  __shared__ double s_mat[8 * FE_MAX_PHASES];  // phase constants
   // FP64 laws with stored words: the gradients of the points q = 1 wait here while those of q = 0
   // are worked on, then the stress sums of q = 0 do (18 registers less at the peak: no spills at
   // four waves per SIMD; one slot per lane, so no barrier)
   constexpr bool PARK = sizeof(T) == 8 && MS != MS_LINEAR;
   __shared__ T s_park[PARK ? 9 : 1][PARK ? EBLOCK : 1];
 
-  if (stop && *stop) return;
+  if (OP != OP_CG_APPLY && stop && *stop) return;  // (the CG launch tests its status after requesting its data)
   const int n = a.n;
   const int ntx = (n + TX - 1) / TX, nty = (n + TY - 1) / TY, ntz = (n + TZ - 1) / TZ;
   const int nb = ntx * nty * ntz;
@@ -457,6 +484,13 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   const int64_t e4 = e + 4 * r * ne;  // first point of this half in [..][8][n_el] arrays
   const T h = T(a.h);
   const T w0 = r ? T(GB) : T(GA), w1 = r ? T(GA) : T(GB);
+  // the phase table goes to LDS: a lane's constants are then one short read after the barrier
+  // instead of a dependent trip to memory
+  if (tid < 8 * FE_MAX_PHASES && (tid >> 3) < a.mat.n) {
+    const PhaseConst& c = a.mat.ph[tid >> 3];
+    const int k = tid & 7;
+    s_mat[tid] = k == 0 ? c.lam : k == 1 ? c.mu : k == 2 ? c.K : k == 3 ? c.G : k == 4 ? c.sy : k == 5 ? c.H : (double)c.model;
+  }
   // the element's phase is requested before the staging loads; the operator's first stored-
   // tangent word of every Gauss point right after them (both arrive before they are used)
   const int ph = valid ? (int)a.phase[e] : 0;
@@ -464,7 +498,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   T tq0[4];
   auto early = [&]() {
     if (APPLY_LIKE && J2M) {
-      const bool j2 = valid && a.mat.ph[ph].model == FE_J2;
+      const bool j2 = valid && ((a.j2_mask >> ph) & 1u);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) tq0[qq] = j2 ? tang_c[e4 + qq * ne] : T(-1);
     }
@@ -480,12 +514,9 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     const bool go = a.cg_block ? cg_stage_brick<T, true>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
                                : cg_stage_brick<T, false>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
     if (!go) return;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      cg_g += __shfl_down(cg_g, off, 64);
-      cg_rr += __shfl_down(cg_rr, off, 64);
-    }
-    if (br.lane == 0) {
+    cg_g = wave_sum_last(cg_g);
+    cg_rr = wave_sum_last(cg_rr);
+    if (br.lane == WAVE_LAST) {
       s_red[4][br.wave] = cg_g;
       s_red[5][br.wave] = cg_rr;
     }
@@ -529,7 +560,12 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   double pq = 0;
 
   if (valid) {
-    const PhaseConst pc = a.mat.ph[ph];
+    PhaseConst pc;
+    {
+      const double* m = s_mat + 8 * ph;
+      pc.lam = m[0], pc.mu = m[1], pc.K = m[2], pc.G = m[3], pc.sy = m[4], pc.H = m[5];
+      pc.model = (int)m[6];
+    }
     const T sc = (a.scale && OP != OP_VJP) ? static_cast<const T*>(a.scale)[e] : T(1);
 
     // J2 operator: the first stored-tangent word of every Gauss point arrived with the staging
@@ -754,10 +790,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     const double w = a.h * a.h * a.h * 0.125;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-      double v = ssum[k] * w;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-      if (br.lane == 0) s_red[k][br.wave] = v;
+      const double v = wave_sum_last(ssum[k] * w);
+      if (br.lane == WAVE_LAST) s_red[k][br.wave] = v;
     }
   }
 
@@ -864,9 +898,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     }
   }
   if constexpr (OP == OP_CG_APPLY) {  // partials of (u_j, A u_j), (r_j, u_j), ||r_j||^2
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) pq += __shfl_down(pq, off, 64);
-    if (br.lane == 0) s_red[3][br.wave] = pq;
+    pq = wave_sum_last(pq);
+    if (br.lane == WAVE_LAST) s_red[3][br.wave] = pq;
     __syncthreads();
     if (threadIdx.x < 3) {  // workgroups share CGS_SLOTS slots per quantity
       double t = 0;
@@ -884,6 +917,9 @@ static int elem_grid(int n) {
 template <typename T, int OP>
 static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
   const dim3 grid(elem_grid(p->n)), block(EBLOCK);
+  ElemArgs b = a;
+  b.j2_mask = 0;
+  for (int i = 0; i < p->mat.n; ++i) b.j2_mask |= p->mat.ph[i].model == FE_J2 ? 1u << i : 0u;
   // J2 problems that may meet surrogate points (their stored tangents, or a surrogate / capture
   // mode of this residual) take the instance with those branches
   const bool sur = p->model_set == MS_J2 && (OP == OP_RESID ? a.sur_mode != SUR_OFF : p->sur_map != nullptr);
@@ -891,21 +927,21 @@ static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const in
   if constexpr (sizeof(T) == 4 && OP != OP_VJP) {
     if (p->acc32) {
       switch (ms) {
-        case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2, true>), grid, block, 0, s, a, stop); break;
-        case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH, true>), grid, block, 0, s, a, stop); break;
-        case MS_SUR: timed_launch((elem_kernel<T, OP, MS_SUR, true>), grid, block, 0, s, a, stop); break;
-        default: timed_launch((elem_kernel<T, OP, MS_LINEAR, true>), grid, block, 0, s, a, stop);
+        case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2, true>), grid, block, 0, s, b, stop); break;
+        case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH, true>), grid, block, 0, s, b, stop); break;
+        case MS_SUR: timed_launch((elem_kernel<T, OP, MS_SUR, true>), grid, block, 0, s, b, stop); break;
+        default: timed_launch((elem_kernel<T, OP, MS_LINEAR, true>), grid, block, 0, s, b, stop);
       }
       return hipGetLastError();
     }
   }
   switch (ms) {
-    case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2>), grid, block, 0, s, a, stop); break;
-    case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH>), grid, block, 0, s, a, stop); break;
+    case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2>), grid, block, 0, s, b, stop); break;
+    case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH>), grid, block, 0, s, b, stop); break;
     case MS_SUR:
-      if constexpr (OP != OP_VJP) timed_launch((elem_kernel<T, OP, MS_SUR>), grid, block, 0, s, a, stop);
+      if constexpr (OP != OP_VJP) timed_launch((elem_kernel<T, OP, MS_SUR>), grid, block, 0, s, b, stop);
       break;
-    default: timed_launch((elem_kernel<T, OP, MS_LINEAR>), grid, block, 0, s, a, stop);
+    default: timed_launch((elem_kernel<T, OP, MS_LINEAR>), grid, block, 0, s, b, stop);
   }
   return hipGetLastError();
 }
@@ -2078,8 +2114,8 @@ static hipError_t cg_operator_t(const fe_problem* p, int op, const int32_t* rp, 
 // Matrix-free CG with one operator launch per iteration (single-reduction form of
 // Chronopoulos & Gear 1989; exact-arithmetic equivalent of the CG recursion):
 //   launch j forms u_j = M^-1 r_j, w_j = A u_j and the partials of (u_j, w_j),
-//   (r_j, u_j), ||r_j||^2; its staging applies update j-1 (see cg_stage) and its last
-//   workgroup reduces the partials into alpha_j, beta_j or a stop (see cg_finish).
+//   (r_j, u_j), ||r_j||^2; its staging forms alpha and beta of iterate j-1 or a stop from the
+//   partials of launch j-1 and applies that update (see cg_scalars, cg_stage_brick).
 // Vectors: x (caller), p (in place, owners only), r in two buffers, s in two, w in three
 // (launch j writes w into the buffer that launch j-1 zeroed).
 
@@ -2101,7 +2137,7 @@ template <typename T> __global__ __launch_bounds__(VBLOCK) void cgs_init_kernel(
     ctrl->iters = 0;
     ctrl->max_it = max_it;
     ctrl->alpha = ctrl->beta = ctrl->pq = 0;
-    ctrl->ghist[0] = ctrl->ghist[1] = ctrl->ahist[0] = ctrl->ahist[1] = 0;
+    ctrl->ghist[0] = ctrl->ghist[1] = ctrl->ahist[0] = ctrl->ahist[1] = ctrl->bhist[0] = ctrl->bhist[1] = 0;
     ctrl->status = CG_RUNNING;
   }
 }
@@ -2159,6 +2195,30 @@ template <typename T> static hipError_t cgs_operator_t(const fe_problem* p, T* x
   a.cg_acc_out = acc + (j % 3) * 3 * CGS_SLOTS;
   a.cg_acc_zero = acc + ((j + 1) % 3) * 3 * CGS_SLOTS;
   return launch_elem_t<T, OP_CG_APPLY>(p, a, &p->ctrl->status, s);
+}
+
+// After a stop at an odd number of updates: the last of them has not reached p and x yet.
+template <typename T> __global__ __launch_bounds__(VBLOCK) void cgs_flush_kernel(
+    int64_t n, T* __restrict__ x, T* __restrict__ p, const T* __restrict__ r, const T* __restrict__ dinv, int block,
+    const CgCtrl* ctrl, int slot) {
+  const T alpha = T(ctrl->ahist[slot]), beta = T(ctrl->bhist[slot]);
+  for (int64_t i = (int64_t)blockIdx.x * VBLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * VBLOCK) {
+    const T pn = pc_apply(dinv, r, i, block) + beta * p[i];
+    p[i] = pn;
+    x[i] += alpha * pn;
+  }
+}
+
+template <typename T> static hipError_t cgs_flush_t(const fe_problem* p, T* x, int iters, hipStream_t s) {
+  if ((iters & 1) == 0) return hipSuccess;
+  const int i = iters - 1;  // the missing update
+  hipLaunchKernelGGL(cgs_flush_kernel<T>, dim3(vgrid(p->n_dof)), dim3(VBLOCK), 0, s, p->n_dof, x, (T*)p->w_p,
+                     (const T*)cgs_r<T>(p, i), (const T*)pc_buffer(p), p->precond, (const CgCtrl*)p->ctrl, i & 1);
+  return hipGetLastError();
+}
+
+hipError_t cgs_flush(const fe_problem* p, void* x, int iters, hipStream_t s) {
+  return p->prec == FE_F64 ? cgs_flush_t(p, (double*)x, iters, s) : cgs_flush_t(p, (float*)x, iters, s);
 }
 
 hipError_t cgs_operator(const fe_problem* p, void* x, long j, hipStream_t s) {
