@@ -137,10 +137,12 @@ int fe_problem_create(fe_problem** out, int n, int precision);
  * the structured problem (dofs 3 node + c, Gauss point q of element e at index
  * q n_el + e of state arrays, fe_lift from the stored coordinates, fe_mean_stress
  * divided by the mesh volume), except: FE_PC_ILU0, the learned surrogate and its
- * sample capture, and fe_vjp_path are structured-only (FE_ERR_ARG); CG runs one
- * operator, one update and one direction launch per iteration.  Synchronises the
- * stream.  Needs device memory of 64 n_el + 12 (node pairs) + 3 n_nodes int32 and,
- * once fe_tangent_csr runs, 576 n_el reals for the element Jacobians. */
+ * sample capture, and fe_vjp_path are structured-only (FE_ERR_ARG); matrix-free CG
+ * runs one element launch and one node launch per iteration.  Synchronises the
+ * stream.  Needs device memory of 72 n_el + 12 (node pairs) + 4 n_nodes int32 and,
+ * once fe_tangent_csr runs, 576 n_el reals for the element Jacobians; the first
+ * matrix-free solve adds 24 n_el + 3 n_nodes reals (element forces), without which
+ * (no memory) the solvers add element forces atomically. */
 int fe_problem_create_hex8(fe_problem** out, int64_t n_nodes, int64_t n_el, const double* coords,
                            const int32_t* conn, int precision, void* stream);
 void fe_problem_destroy(fe_problem* p);

@@ -171,6 +171,9 @@ void fe_problem_destroy(fe_problem* p) {
   free_dev(p->pair_src_ptr);
   free_dev(p->pair_src);
   free_dev(p->gen_col);
+  free_dev(p->inc_ptr);
+  free_dev(p->inc);
+  free_dev(p->gen_elf);
   free_dev(p->ke);
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
   if (p->host_ctrl) (void)hipHostFree(p->host_ctrl);
@@ -267,6 +270,8 @@ int fe_problem_create_hex8(fe_problem** out, int64_t n_nodes, int64_t n_el, cons
   if ((st = alloc(&p->coords, rs * 3 * n_nodes)) || (st = alloc((void**)&p->conn, sizeof(int32_t) * 8 * n_el)) ||
       (st = alloc((void**)&p->adj_ptr, sizeof(int32_t) * (n_nodes + 1))) ||
       (st = alloc((void**)&p->pair_src, sizeof(int32_t) * 64 * n_el)) ||
+      (st = alloc((void**)&p->inc_ptr, sizeof(int32_t) * (n_nodes + 1))) ||
+      (st = alloc((void**)&p->inc, sizeof(int32_t) * 8 * n_el)) ||
       (st = alloc((void**)&p->gen_col, sizeof(int32_t) * 64 * n_el)) ||
       (st = alloc((void**)&cnt, sizeof(int32_t) * n_nodes)) ||
       (st = alloc((void**)&coo_ptr, sizeof(int32_t) * (n_nodes + 1))) ||
@@ -757,6 +762,17 @@ static int ipcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci,
   return status;
 }
 
+// Element-force workspace of the solvers on a general mesh; without it (no memory) they run on the
+// atomic operator.
+static void ensure_gen_elf(fe_problem* p) {
+  if (!p->general || p->gen_elf) return;
+  const size_t words = 24 * (size_t)p->n_el + (size_t)p->n_dof;
+  if (hipMalloc(&p->gen_elf, words * real_size(p)) != hipSuccess) {
+    p->gen_elf = nullptr;
+    (void)hipGetLastError();
+  }
+}
+
 static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, const void* vals, const void* b,
                    void* x, double rtol, int max_it, fe_pcg_info* info, hipStream_t s, int* applies) {
   if (p->precond == FE_PC_ILU0) return ipcg_run(p, op, rp, ci, vals, b, x, rtol, max_it, info, s, applies);
@@ -768,8 +784,12 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
   } else {
     HIPCHK(launch_diag(p, p->w_d, 1, s));
   }
-  const bool fused = op == FE_OP_MATFREE && !p->general && !p->deterministic;
-  if (fused) {
+  if (op == FE_OP_MATFREE) ensure_gen_elf(p);
+  const bool gfused = op == FE_OP_MATFREE && p->general && p->gen_elf;
+  const bool sfused = op == FE_OP_MATFREE && !p->general && !p->deterministic;
+  if (gfused) {
+    HIPCHK(gen_cgs_init(p, b, x, rtol, max_it, s));
+  } else if (sfused) {
     if (!p->w_cg && alloc(&p->w_cg, 6 * real_size(p) * (size_t)p->n_dof)) return FE_ERR_OOM;
     HIPCHK(cgs_init(p, b, x, rtol, max_it, s));
   } else {
@@ -788,11 +808,16 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
   } while (0)
   int launched = 0, chunk = 8;
   long k = 0;
-  if (fused) CG_OPERATOR(cgs_operator(p, x, 0, s));
+  if (sfused) CG_OPERATOR(cgs_operator(p, x, 0, s));
   for (;;) {
     for (int c = 0; c < chunk; ++c, ++k) {
-      if (fused) {
+      if (sfused) {
         CG_OPERATOR(cgs_operator(p, x, k + 1, s));
+        continue;
+      }
+      if (gfused) {
+        CG_OPERATOR(gen_cgs_operator(p, k, s));
+        HIPCHK(gen_cgs_update(p, x, k, s));
         continue;
       }
       HIPCHK(cg_pre(p, op, k, s));
@@ -806,12 +831,12 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
     if (chunk < 32) chunk *= 2;
   }
   const CgCtrl& c = *p->host_ctrl;
-  if (fused) HIPCHK(cgs_flush(p, x, c.iters, s));
+  if (sfused) HIPCHK(cgs_flush(p, x, c.iters, s));
   const int status = c.status == CG_RUNNING ? FE_ERR_NOT_CONVERGED : (c.status == CG_CONVERGED ? FE_OK : c.status);
   // operator launches after the stopping iteration returned at once: drop their timings
-  // (the fused form runs one launch more than iterations: launch j forms u_j = M^-1 r_j)
-  const size_t executed = (size_t)c.iters + (fused ? 1 : 0) +
-                          (!fused && (status == FE_ERR_BREAKDOWN || status == FE_ERR_NONFINITE) ? 1 : 0);
+  // (the fused structured form runs one launch more than iterations: launch j forms u_j = M^-1 r_j)
+  const size_t executed = (size_t)c.iters + (sfused ? 1 : 0) +
+                          (!sfused && (status == FE_ERR_BREAKDOWN || status == FE_ERR_NONFINITE) ? 1 : 0);
 #undef CG_OPERATOR
   if (p->prof) {  // timed launches among the executed ones: 0, stride, 2 stride, ...
     const size_t kept = (executed + (size_t)stride - 1) / (size_t)stride;
@@ -822,7 +847,7 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
     // the fused matrix-free CG launch reads r, w, s and M^-1 (1 or 2 reals per dof) and writes
     // r, s and the zeroed w instead of reading x; every second launch also reads r_{j-2}, p and x
     // and writes p and x
-    if (fused) b += (p->precond == FE_PC_BLOCK_JACOBI ? 9.5 : 8.5) * (double)real_size(p) * (double)p->n_dof;
+    if (sfused) b += (p->precond == FE_PC_BLOCK_JACOBI ? 9.5 : 8.5) * (double)real_size(p) * (double)p->n_dof;
     p->prof_bytes[cls] += b * (double)timed;
   }
   if (info) {
@@ -855,6 +880,7 @@ static int bicg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci,
   } else {
     HIPCHK(launch_diag(p, p->w_d, 1, s));
   }
+  if (op == FE_OP_MATFREE) ensure_gen_elf(p);
   HIPCHK(bicg_init(p, b, x, rtol, max_it, s));
   const int* stop = &p->bicg_ctrl->status;
   char* base = static_cast<char*>(p->w_bicg);
@@ -950,6 +976,7 @@ static int gmres_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci
     HIPCHK(hipStreamSynchronize(s));
     return FE_OK;
   };
+  if (op == FE_OP_MATFREE) ensure_gen_elf(p);
   HIPCHK(gm_setup(p, b, x, rtol, max_it, m, s));
   HIPCHK(gm_step(p, GM_START, 0, b, x, s));
   int restarts = 0;

@@ -78,6 +78,89 @@ __device__ __forceinline__ double reduce_partials(const double* partials, int nb
 
 __device__ __forceinline__ bool finite(double v) { return v == v && v - v == 0.0; }
 
+// ---- single-reduction CG (Chronopoulos & Gear 1989), scalars of launch j >= 1 -------------------
+// The scalars of earlier launches that launch j uses (workgroup 0 of launch j writes none of them).
+struct CgHist {
+  double rtol2, tol2, g, alpha, beta;  // g, alpha, beta of iterate j-2
+  int status, max_it;
+};
+
+__device__ __forceinline__ CgHist cg_history(const CgCtrl* c, long j) {
+  const int slot = (int)(j & 1);
+  return {c->rtol2, c->tol2, c->ghist[slot], c->ahist[slot], c->bhist[slot], c->status, c->max_it};
+}
+
+// From d = (u, A u), g = (r, u), rr = ||r||^2 of iterate j-1:
+//   beta_{j-1} = g_{j-1} / g_{j-2},  alpha_{j-1} = g_{j-1} / (d_{j-1} - beta g_{j-1} / alpha_{j-2})
+// (j = 1: beta_0 = 0, alpha_0 = g_0 / d_0), or a stop: ||r_{j-1}|| <= rtol ||b||, j - 1 = max_it,
+// breakdown, non-finite.  Every workgroup forms the same values; workgroup 0 records them: (g,
+// alpha, beta) of iterate j-1 go to history slot (j-1) & 1 while slot j & 1 is read.
+// Returns false when the iteration stops.
+template <typename T>
+__device__ __forceinline__ bool cg_coefficients(CgCtrl* w, const CgHist& c, long j, double d, double g, double rr,
+                                                T& alpha_out, T& beta_out) {
+  const double tol2 = j == 1 ? c.rtol2 * rr : c.tol2;
+  int st = CG_RUNNING;
+  double alpha = 0, beta = 0;
+  if (!finite(d) || !finite(g) || !finite(rr)) {
+    st = FE_ERR_NONFINITE;
+  } else if (j == 1 ? rr == 0.0 : rr <= tol2) {
+    st = CG_CONVERGED;
+  } else if (j - 1 >= c.max_it) {
+    st = FE_ERR_NOT_CONVERGED;
+  } else {
+    beta = j == 1 ? 0.0 : g / c.g;
+    const double den = j == 1 ? d : d - beta * g / c.alpha;
+    if (!finite(den)) st = FE_ERR_NONFINITE;
+    else if (den <= 0.0) st = FE_ERR_BREAKDOWN;
+    else alpha = g / den;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int slot = (int)((j - 1) & 1);
+    if (j == 1) {
+      w->bb = rr;
+      w->tol2 = tol2;
+    }
+    w->rr = rr;
+    w->pq = d;
+    w->iters = (int)(j - 1);
+    w->alpha = alpha;
+    w->beta = beta;
+    w->ghist[slot] = g;
+    w->ahist[slot] = alpha;
+    w->bhist[slot] = beta;
+    if (st != CG_RUNNING) w->status = st;
+  }
+  alpha_out = T(alpha);
+  beta_out = T(beta);
+  return st == CG_RUNNING;
+}
+
+// Sums d, g, rr of the [3][CGS_SLOTS] slots of the launch before, over a workgroup of W waves:
+// lane values v[k] = slot k * 64 W + threadIdx (64 slots per wave, so the 12 wave sums are four
+// each of d, g and rr, in a fixed order); sh holds at least 12 doubles, synchronised on return.
+template <int W> constexpr int cg_slots_per_lane() { return (12 + W - 1) / W; }
+template <int W>
+__device__ __forceinline__ void cg_slot_sums(const double v[cg_slots_per_lane<W>()], double* sh, double& d, double& g,
+                                             double& rr) {
+  static_assert(CGS_SLOTS == 256, "four waves per reduced quantity");
+  const int wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < cg_slots_per_lane<W>(); ++k) {
+    const double t = wave_sum_last(v[k]);
+    if ((threadIdx.x & 63) == WAVE_LAST && k * W + wave < 12) sh[k * W + wave] = t;
+  }
+  __syncthreads();
+  d = g = rr = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    d += sh[w];
+    g += sh[4 + w];
+    rr += sh[8 + w];
+  }
+  __syncthreads();  // sh may be reused
+}
+
 // Wavefront-aggregated append: lanes with pred set get consecutive slots of *counter
 // (one atomic per wave).  Valid for any set of active lanes.
 __device__ __forceinline__ unsigned wave_append(unsigned int* counter, bool pred) {
@@ -208,6 +291,20 @@ __device__ __forceinline__ void j2_apply(const T H[3][3], T lp, T mp, T beta, co
   S[1][2] = S[2][1] = mp * g12 - bn * N[3];
   S[0][2] = S[2][0] = mp * g02 - bn * N[4];
   S[0][1] = S[1][0] = mp * g01 - bn * N[5];
+}
+
+// The phase table in LDS (s_mat: 8 doubles per phase): a lane's constants are then one short read
+// after the barrier instead of a dependent trip to memory.  Workgroups of at least 64 lanes.
+__device__ __forceinline__ void stage_phases(const Phases& m, double* s_mat, int tid) {
+  if (tid < 8 * FE_MAX_PHASES && (tid >> 3) < m.n) {
+    const PhaseConst& c = m.ph[tid >> 3];
+    const int k = tid & 7;
+    s_mat[tid] = k == 0 ? c.lam : k == 1 ? c.mu : k == 2 ? c.K : k == 3 ? c.G : k == 4 ? c.sy : k == 5 ? c.H : (double)c.model;
+  }
+}
+__device__ __forceinline__ PhaseConst phase_const(const double* s_mat, int ph) {
+  const double* m = s_mat + 8 * ph;
+  return PhaseConst{(int)m[6], m[0], m[1], m[2], m[3], m[4], m[5]};
 }
 
 // ---- learned surrogate at a plastic-trial J2 point ----------------------------------

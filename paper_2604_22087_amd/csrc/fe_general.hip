@@ -101,9 +101,24 @@ template <typename T> __device__ __forceinline__ void field_grad(const T (*ue)[3
     }
 }
 
+// v of another lane of the aligned group of 8, by DPP (a register move; 32 bits at a time).
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+constexpr int DPP_MIRROR8 = 0x141;  // row_half_mirror: lane q <- 7 - q
+constexpr int DPP_XOR2 = 0x4E;      // quad_perm [2,3,0,1]
+constexpr int DPP_XOR1 = 0xB1;      // quad_perm [1,0,3,2]
+
 // Sum of per-lane values v[8][NV] (node, component) over the 8 lanes of an element (lanes q =
 // lane % 8); afterwards lane q holds node q's total in out[NV].  Recursive halving: each step
-// sends the half the partner keeps and adds the received half to its own.
+// sends the half the partner keeps and adds the received half to its own (the first partner is
+// 7 - q, whose upper bit differs; the others q ^ 2 and q ^ 1).
 template <typename T, int NV> __device__ __forceinline__ void reduce_scatter8(const T v[8][NV], int q, T out[NV]) {
   T h1[4][NV], h2[2][NV];
   const bool b4 = q & 4, b2 = q & 2, b1 = q & 1;
@@ -113,7 +128,7 @@ template <typename T, int NV> __device__ __forceinline__ void reduce_scatter8(co
     for (int c = 0; c < NV; ++c) {
       const T send = b4 ? v[a][c] : v[a + 4][c];
       const T keep = b4 ? v[a + 4][c] : v[a][c];
-      h1[a][c] = keep + __shfl_xor(send, 4, 64);
+      h1[a][c] = keep + dpp_move<DPP_MIRROR8>(send);
     }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -121,13 +136,13 @@ template <typename T, int NV> __device__ __forceinline__ void reduce_scatter8(co
     for (int c = 0; c < NV; ++c) {
       const T send = b2 ? h1[a][c] : h1[a + 2][c];
       const T keep = b2 ? h1[a + 2][c] : h1[a][c];
-      h2[a][c] = keep + __shfl_xor(send, 2, 64);
+      h2[a][c] = keep + dpp_move<DPP_XOR2>(send);
     }
 #pragma unroll
   for (int c = 0; c < NV; ++c) {
     const T send = b1 ? h2[0][c] : h2[1][c];
     const T keep = b1 ? h2[1][c] : h2[0][c];
-    out[c] = keep + __shfl_xor(send, 1, 64);
+    out[c] = keep + dpp_move<DPP_XOR1>(send);
   }
 }
 
@@ -140,7 +155,7 @@ __device__ __forceinline__ double sum8(double v) {
 }
 
 struct GenArgs {
-  const void* coords;     // real [3][n_nodes]
+  const void* coords;     // real [n_nodes][3]
   const int32_t* conn;    // [8][n_el]
   int64_t n_nodes;
 };
@@ -154,18 +169,84 @@ static GenArgs gen_args(const fe_problem* p) {
 }
 
 // ---------------------------------------------------------------------------
+// CG scalars on a general mesh (textbook PCG; see gen_cg_node_kernel).  Sums go through GCG_SLOTS
+// slots per quantity, two sets in turn: node launch j - 1 adds GCG_Q quantities of iterate j,
+// element launch j sums them (every workgroup the same way), and adds (p_j, A p_j) to slots of its
+// own that node launch j sums.
+constexpr int GCG_SLOTS = 64;
+constexpr int GCG_Q = 5;  // (r, M^-1 r), ||r||^2; over constrained dofs (A p = p there) u.u, u.p, p.p with the old p
+static_assert(2 * GCG_Q * GCG_SLOTS + 2 * GCG_SLOTS <= 9 * CGS_SLOTS, "slots fit the problem's partial sums");
+
+struct GenCgScalars {
+  double v[2], rtol2, tol2, rz_old;
+  int max_it;
+  // this lane's slots (of 5 x 64, 256 lanes) and the scalars of the iterate before
+  __device__ __forceinline__ void request(const ElemArgs& a, int tid) {
+    v[0] = a.cg_acc_in[tid];
+    v[1] = tid < GCG_Q * GCG_SLOTS - GBLOCK ? a.cg_acc_in[GBLOCK + tid] : 0.0;
+    const CgCtrl* c = a.ctrl;
+    rtol2 = c->rtol2;
+    tol2 = c->tol2;
+    rz_old = c->rz[(a.cg_j + 1) & 1];
+    max_it = c->max_it;
+    if (blockIdx.x == 0)
+      for (int i = tid; i < GCG_Q * GCG_SLOTS; i += GBLOCK) a.cg_acc_zero[i] = 0.0;  // slots of iterate j + 1
+  }
+  // beta_j, or false at a stop; workgroup 0 records the iterate
+  __device__ __forceinline__ bool direction(const ElemArgs& a, double* sh, double& beta) {
+    static_assert(GCG_SLOTS == 64 && GBLOCK == 256, "one wave per quantity");
+    const int wave = threadIdx.x >> 6;
+    const double s0 = wave_sum_last(v[0]), s1 = wave_sum_last(v[1]);
+    if ((threadIdx.x & 63) == WAVE_LAST) {
+      sh[wave] = s0;
+      if (wave == 0) sh[4] = s1;
+    }
+    __syncthreads();
+    const double rz = sh[0], rr = sh[1], uu = sh[2], up = sh[3], pp = sh[4];
+    __syncthreads();  // sh is reused
+    const long j = a.cg_j;
+    const double t2 = j == 0 ? rtol2 * rr : tol2;
+    int st = CG_RUNNING;
+    if (!finite(rr) || !finite(rz)) st = FE_ERR_NONFINITE;
+    else if (j == 0 ? rr == 0.0 : rr <= t2) st = CG_CONVERGED;
+    else if (j >= max_it) st = FE_ERR_NOT_CONVERGED;
+    beta = j == 0 ? 0.0 : rz / rz_old;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      CgCtrl* w = a.ctrl;
+      if (j == 0) {
+        w->bb = rr;
+        w->tol2 = t2;
+      }
+      w->rr = rr;
+      w->iters = (int)j;
+      w->beta = beta;
+      w->rz[j & 1] = rz;
+      w->pq = uu + 2.0 * beta * up + beta * beta * pp;  // constrained share of (p_j, A p_j)
+      if (st != CG_RUNNING) w->status = st;
+    }
+    return st == CG_RUNNING;
+  }
+};
+
+// ---------------------------------------------------------------------------
 // element kernel: OP_RESID, OP_APPLY, OP_VJP (ElemArgs as for the structured kernels; y
 // zeroed by the caller; constrained dofs receive nothing, see gen_bc_kernel)
 
-template <typename T, int OP, int MS>
+// ELF: the nodal forces go to a.elf ([n_el][8][3], one contiguous run per wave) for
+// gen_cg_node_kernel / gen_gather_kernel instead of being added with atomics, which random node
+// numbers make the whole cost (33^3 FP32 operator: 53 us with them).  CG: the operator launch of a
+// CG iteration, see gen_cg_node_kernel.
+template <typename T, int OP, int MS, bool ELF = false, bool CG = false>
 __global__ __launch_bounds__(GBLOCK) void gen_elem_kernel(GenArgs g, ElemArgs a, const int* stop) {
   constexpr bool APPLY = OP == OP_APPLY;
   constexpr bool NEED_L = OP == OP_VJP;
-  __shared__ T s_c[GEL][8][3];
-  __shared__ T s_x[GEL][8][3];
+  __shared__ alignas(16) T s_c[GEL][8][3];
+  __shared__ alignas(16) T s_x[GEL][8][3];
   __shared__ T s_l[NEED_L ? GEL : 1][8][3];
   __shared__ double s_red[6][GBLOCK / 64];
-  if (stop && *stop) return;
+  const int stopped = stop ? *stop : 0;  // (tested once this lane's gathers are on their way)
+  GenCgScalars cgs;
+  if constexpr (CG) cgs.request(a, threadIdx.x);
   const int tid = threadIdx.x, el = tid >> 3, q = tid & 7;
   const int64_t ne = a.n_el;
   const int64_t e = (int64_t)blockIdx.x * GEL + el;
@@ -177,14 +258,27 @@ __global__ __launch_bounds__(GBLOCK) void gen_elem_kernel(GenArgs g, ElemArgs a,
   // stage node q of element e
   int node = 0;
   if (valid) node = g.conn[(int64_t)q * ne + e];
+  T uv[3], pv[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const int64_t dof = 3 * (int64_t)node + c;
-    s_c[el][q][c] = valid ? C[(int64_t)c * g.n_nodes + node] : T(0);
+    s_c[el][q][c] = valid ? C[dof] : T(0);
     T v = valid ? X[dof] : T(0);
     if (APPLY && bc && valid && a.mask[dof]) v = T(0);
-    s_x[el][q][c] = v;
+    if constexpr (CG) {
+      uv[c] = v;
+      pv[c] = valid ? static_cast<const T*>(a.cg_pvec)[dof] : T(0);
+    } else {
+      s_x[el][q][c] = v;
+    }
     if (NEED_L) s_l[NEED_L ? el : 0][q][c] = valid ? XL[dof] : T(0);
+  }
+  if (stopped) return;
+  if constexpr (CG) {  // p_j = u_j + beta_j p_{j-1}
+    double beta;
+    if (!cgs.direction(a, &s_red[0][0], beta)) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s_x[el][q][c] = uv[c] + T(beta) * pv[c];
   }
   __syncthreads();
 
@@ -313,6 +407,27 @@ __global__ __launch_bounds__(GBLOCK) void gen_elem_kernel(GenArgs g, ElemArgs a,
     }
   }
 
+  if constexpr (ELF) {
+    if (valid) {
+      T* E = static_cast<T*>(a.elf) + 3 * (8 * e + q);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) E[c] = fn[c];
+    }
+    if constexpr (CG) {  // this element's share of (p, A p)
+      double d = 0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) d += (double)fn[c] * (double)s_x[el][q][c];
+      d = wave_sum_last(d);
+      if ((tid & 63) == WAVE_LAST) s_red[0][tid >> 6] = d;
+      __syncthreads();
+      if (tid == 0) {
+        double t = 0;
+        for (int w = 0; w < GBLOCK / 64; ++w) t += s_red[0][w];
+        atomic_add(a.cg_acc_out + (int)(blockIdx.x % GCG_SLOTS), t);
+      }
+    }
+    return;
+  }
   T* Y = static_cast<T*>(a.y);
   if (!Y || !valid) return;
 #pragma unroll
@@ -347,6 +462,173 @@ __global__ __launch_bounds__(VBLOCK) void gen_bc_kernel(int64_t n, const uint8_t
   }
 }
 
+// Sum of the element forces at dof 3 node + c over the node's incidences, in element order.
+template <typename T>
+__device__ __forceinline__ T gather_node(const T* __restrict__ elf, const int32_t* __restrict__ inc, int i0, int i1,
+                                         int c) {
+  T v = 0;
+  int k = i0;
+  for (; k + 4 <= i1; k += 4) {  // (four index loads, then four gathers in flight)
+    const int n0 = inc[k], n1 = inc[k + 1], n2 = inc[k + 2], n3 = inc[k + 3];
+    const T v0 = elf[3 * (int64_t)n0 + c], v1 = elf[3 * (int64_t)n1 + c], v2 = elf[3 * (int64_t)n2 + c],
+            v3 = elf[3 * (int64_t)n3 + c];
+    v += v0;
+    v += v1;
+    v += v2;
+    v += v3;
+  }
+  for (; k < i1; ++k) v += elf[3 * (int64_t)inc[k] + c];
+  return v;
+}
+
+// y = K x from the element forces, y = x on constrained dofs (solver operators other than CG's).
+template <typename T>
+__global__ __launch_bounds__(VBLOCK) void gen_gather_kernel(int64_t n, const int32_t* inc_ptr, const int32_t* inc,
+                                                            const T* elf, const uint8_t* mask, const T* x, T* y,
+                                                            const int* stop) {
+  if (stop && *stop) return;
+  for (int64_t d = (int64_t)blockIdx.x * VBLOCK + threadIdx.x; d < n; d += (int64_t)gridDim.x * VBLOCK) {
+    const int64_t nd = d / 3;
+    const T v = gather_node(elf, inc, inc_ptr[nd], inc_ptr[nd + 1], (int)(d - 3 * nd));
+    y[d] = mask && mask[d] ? x[d] : v;
+  }
+}
+
+// PCG on a general mesh, two launches an iteration and no floating-point atomics but the slot sums:
+//   element launch j: beta_j (or a stop) from the slots of iterate j; p_j = u_j + beta_j p_{j-1} at
+//     the gathered nodes; element forces of A p_j; share of (p_j, A p_j);
+//   node launch j (below): alpha_j; p_j again, as owner; q = A p_j gathered;
+//     x += alpha p, r -= alpha q, u = M^-1 r, and the sums of iterate j + 1.
+// Node launch -1 (FIRST) starts from r = b.  Against four launches (direction, operator with
+// atomics, constrained rows, update) an iteration at 33^3 FP32 takes 27 instead of 64 us (60^3 FP64 168 instead of 292).  The
+// recurrence for A p of the structured launch would save the second reduction, but in FP32 it
+// leaves twice the error (9.6e-7 against 4.9e-7 in x at rtol 1e-6).
+// u and p are stored with their constrained entries 0, as the element kernel wants them (u is
+// re-formed from r here, the constrained p lives in pf).  21 nodes per wave, lane = 3 node + component.
+struct GenCgArgs {
+  int64_t n_nodes;
+  long j;
+  const int32_t* inc_ptr;
+  const int32_t* inc;
+  const void* elf;
+  const uint8_t* mask;
+  const void* b;        // right-hand side (FIRST)
+  void *r, *p, *pf, *x, *u;
+  void* dinv;           // inverse diagonal [n_dof] (FIRST: the diagonal, inverted here) or node blocks [n_nodes][6]
+  CgCtrl* ctrl;
+  const double* pq_in;  // slots of (p_j, A p_j)
+  double *pq_zero, *acc_out;
+};
+
+constexpr int CGN_NODES = 21;
+
+template <typename T, bool BLK, bool FIRST>
+__global__ __launch_bounds__(VBLOCK) void gen_cg_node_kernel(GenCgArgs a) {
+  constexpr int W = VBLOCK / 64;
+  __shared__ double sh[GCG_Q * W];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double pq = 0, rz = 0, pqc = 0, beta_d = 0;
+  int status = 0;
+  if (!FIRST) {
+    pq = a.pq_in[lane];  // (every wave sums the 64 slots)
+    rz = a.ctrl->rz[a.j & 1];
+    pqc = a.ctrl->pq;
+    beta_d = a.ctrl->beta;
+    status = a.ctrl->status;
+  }
+  if (blockIdx.x == 0 && tid < GCG_SLOTS) a.pq_zero[tid] = 0.0;  // slots of element launch j + 1
+  const int64_t nd0 = ((int64_t)blockIdx.x * W + wave) * CGN_NODES + lane / 3;
+  const bool ok = lane < 3 * CGN_NODES && nd0 < a.n_nodes;
+  const int64_t nd = ok ? nd0 : 0;
+  const int c = lane % 3;
+  const int64_t dof = 3 * nd + c;
+  T* R = static_cast<T*>(a.r);
+  T* P = static_cast<T*>(a.p);
+  T* PF = static_cast<T*>(a.pf);
+  T* X = static_cast<T*>(a.x);
+  T* M = static_cast<T*>(a.dinv);
+  const bool fixed = a.mask && a.mask[dof];
+  T m0, m1 = 0, m2 = 0;
+  if (BLK) {  // xx yy zz yz xz xy
+    const T* m = M + 6 * nd;
+    m0 = m[c == 0 ? 0 : (c == 1 ? 5 : 4)];
+    m1 = m[c == 0 ? 5 : (c == 1 ? 1 : 3)];
+    m2 = m[c == 0 ? 4 : (c == 1 ? 3 : 2)];
+  } else {
+    m0 = M[dof];
+    if (FIRST) m0 = T(1) / m0;
+  }
+  const int l0 = lane - c;
+  auto precond = [&](T r) {
+    if (!BLK) return m0 * r;
+    return m0 * __shfl(r, l0, 64) + m1 * __shfl(r, l0 + 1, 64) + m2 * __shfl(r, l0 + 2, 64);
+  };
+  T r, p = 0, x = 0;
+  if (FIRST) {
+    r = static_cast<const T*>(a.b)[dof];
+  } else {
+    r = R[dof];
+    p = fixed ? PF[dof] : P[dof];
+    x = X[dof];
+    const T q0 = gather_node(static_cast<const T*>(a.elf), a.inc, a.inc_ptr[nd], a.inc_ptr[nd + 1], c);
+    if (status) return;
+    pq = wave_sum_last(pq);
+    pq = __shfl(pq, WAVE_LAST, 64) + pqc;
+    const int st = !finite(pq) ? FE_ERR_NONFINITE : (pq <= 0.0 ? FE_ERR_BREAKDOWN : CG_RUNNING);
+    const double alpha = rz / pq;
+    if (blockIdx.x == 0 && tid == 0) {
+      a.ctrl->alpha = alpha;
+      if (st != CG_RUNNING) a.ctrl->status = st;
+    }
+    if (st != CG_RUNNING) return;
+    const T ta = T(alpha);
+    p = precond(r) + T(beta_d) * p;
+    x += ta * p;
+    r -= ta * (fixed ? p : q0);
+  }
+  const T u = precond(r);
+  double q5[GCG_Q] = {};
+  if (ok) {
+    if (FIRST && !BLK) M[dof] = m0;
+    R[dof] = r;
+    X[dof] = x;
+    P[dof] = fixed ? T(0) : p;
+    static_cast<T*>(a.u)[dof] = fixed ? T(0) : u;
+    q5[0] = (double)r * (double)u;
+    q5[1] = (double)r * (double)r;
+    if (fixed) {
+      PF[dof] = p;
+      q5[2] = (double)u * (double)u;
+      q5[3] = (double)u * (double)p;
+      q5[4] = (double)p * (double)p;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < GCG_Q; ++k) {
+    const double t = wave_sum_last(q5[k]);
+    if (lane == WAVE_LAST) sh[W * k + wave] = t;
+  }
+  __syncthreads();
+  if (tid < GCG_Q) {
+    double t = 0;
+    for (int w = 0; w < W; ++w) t += sh[W * tid + w];
+    atomic_add(a.acc_out + tid * GCG_SLOTS + (int)(blockIdx.x % GCG_SLOTS), t);
+  }
+}
+
+// Start of a solve: controls, and the slot sets cleared.
+__global__ void gen_cg_start_kernel(CgCtrl* ctrl, double rtol, int max_it, double* acc) {
+  for (int i = threadIdx.x; i < 2 * (GCG_Q + 1) * GCG_SLOTS; i += blockDim.x) acc[i] = 0.0;
+  if (threadIdx.x == 0) {
+    ctrl->rtol2 = rtol * rtol;
+    ctrl->iters = 0;
+    ctrl->max_it = max_it;
+    ctrl->alpha = ctrl->beta = ctrl->pq = 0;
+    ctrl->rz[0] = ctrl->rz[1] = 0;
+    ctrl->status = CG_RUNNING;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // diagonal (NB = 3) or symmetric 3x3 node blocks (NB = 6: xx yy zz yz xz xy) of K at the
 // stored linearisation, summed over elements (d zeroed before; constrained dofs skipped)
@@ -362,7 +644,7 @@ __global__ __launch_bounds__(GBLOCK) void gen_diag_kernel(GenArgs g, TanArgs ta,
   int node = 0;
   if (valid) node = g.conn[(int64_t)q * ne + e];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) s_c[el][q][c] = valid ? C[(int64_t)c * g.n_nodes + node] : T(0);
+  for (int c = 0; c < 3; ++c) s_c[el][q][c] = valid ? C[3 * (int64_t)node + c] : T(0);
   __syncthreads();
   T v[8][NB];
 #pragma unroll
@@ -493,7 +775,7 @@ __global__ __launch_bounds__(64) void gen_tangent_kernel(GenArgs g, TanArgs ta, 
     if (l < 24) {
       const int a = l / 3, i = l % 3;
       const int node = g.conn[(int64_t)a * ne + e];
-      s_xe[a][i] = static_cast<const T*>(g.coords)[(int64_t)i * g.n_nodes + node];
+      s_xe[a][i] = static_cast<const T*>(g.coords)[3 * (int64_t)node + i];
     }
     __syncthreads();
     {
@@ -762,14 +1044,27 @@ __global__ __launch_bounds__(64) void sym_row_sort_kernel(int64_t n_nodes, const
 // index is adj_ptr[r] + (heads before j); it records the column node, the row node and where
 // its run starts in the sorted code list.
 __global__ __launch_bounds__(64) void sym_pairs_kernel(int64_t n_nodes, const int32_t* ptr, const int32_t* col,
-                                                       const int32_t* adj_ptr, int32_t* adj, int32_t* pair_row,
-                                                       int32_t* src_ptr) {
+                                                       const int32_t* code, const int32_t* adj_ptr, int32_t* adj,
+                                                       int32_t* pair_row, int32_t* src_ptr, int32_t* inc_ptr,
+                                                       int32_t* inc) {
   const int l = threadIdx.x;
   for (int64_t r = blockIdx.x; r < n_nodes; r += gridDim.x) {
     const int b = ptr[r], len = ptr[r + 1] - b;
-    int run = adj_ptr[r];
+    int run = adj_ptr[r], ii = b / 8;  // (8 entries per incidence)
+    if (l == 0) {
+      inc_ptr[r] = b / 8;
+      if (r == n_nodes - 1) inc_ptr[n_nodes] = ptr[n_nodes] / 8;
+    }
     for (int j0 = 0; j0 < len; j0 += 64) {
       const int j = j0 + l;
+      // entries of the row's own column: the elements around the node, in element order
+      const bool self = j < len && col[b + j] == (int32_t)r;
+      const unsigned long long ms = __ballot(self);
+      if (self) {
+        const int32_t cd = code[b + j];  // element * 64 + local row node * 8 + local column node
+        inc[ii + __popcll(ms & ((1ull << l) - 1ull))] = (cd >> 6) * 8 + (cd & 7);
+      }
+      ii += __popcll(ms);
       const bool head = j < len && (j == 0 || col[b + j] != col[b + j - 1]);
       const unsigned long long m = __ballot(head);
       const int before = __popcll(m & ((1ull << l) - 1ull));
@@ -817,7 +1112,7 @@ __global__ __launch_bounds__(GBLOCK) void gen_volume_kernel(GenArgs g, int64_t n
   int node = 0;
   if (valid) node = g.conn[(int64_t)q * ne + e];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) s_c[el][q][c] = valid ? static_cast<const T*>(g.coords)[(int64_t)c * g.n_nodes + node] : T(0);
+  for (int c = 0; c < 3; ++c) s_c[el][q][c] = valid ? static_cast<const T*>(g.coords)[3 * (int64_t)node + c] : T(0);
   __syncthreads();
   double v = 0;
   if (valid) {
@@ -839,7 +1134,7 @@ __global__ void gen_lift_kernel(int64_t n_nodes, const T* coords, const uint8_t*
     if (mask && mask[d]) {
       const int64_t P = d / 3;
       const int c = (int)(d % 3);
-      const double x = coords[P], y = coords[n_nodes + P], z = coords[2 * n_nodes + P];
+      const double x = coords[3 * P], y = coords[3 * P + 1], z = coords[3 * P + 2];
       const double v = c == 0 ? e00 * x + e01 * y + e02 * z : (c == 1 ? e10 * x + e11 * y + e12 * z : e20 * x + e21 * y + e22 * z);
       u[d] = T(v);
     } else if (zero_free) {
@@ -859,9 +1154,10 @@ template <typename T> __global__ void gen_fill_kernel(T* x, int64_t n) {
     x[i] = T(0);
 }
 
-template <typename S, typename D> __global__ void gen_cvt_kernel(const S* a, D* b, int64_t n) {
+// coordinates [3][n] -> [n][3] (an element's gather then touches one place per node, not three)
+template <typename D> __global__ void gen_coords_kernel(const double* a, D* b, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    b[i] = D(a[i]);
+    for (int c = 0; c < 3; ++c) b[3 * i + c] = D(a[c * n + i]);
 }
 
 template <typename T> __global__ void gen_copy_kernel(const T* a, T* b, int64_t n) {
@@ -882,11 +1178,9 @@ hipError_t gen_setup(fe_problem* p, const double* coords, const int32_t* conn, h
   if ((e = hipMemsetAsync(bad, 0, sizeof(int), s)) != hipSuccess) return e;
   hipLaunchKernelGGL(gen_conn_check_kernel, dim3(vblocks(8 * ne)), dim3(256), 0, s, 8 * ne, conn, nn, bad);
   if (p->prec == FE_F64)
-    hipLaunchKernelGGL((gen_cvt_kernel<double, double>), dim3(vblocks(3 * nn)), dim3(256), 0, s, coords,
-                       (double*)p->coords, 3 * nn);
+    hipLaunchKernelGGL(gen_coords_kernel<double>, dim3(vblocks(nn)), dim3(256), 0, s, coords, (double*)p->coords, nn);
   else
-    hipLaunchKernelGGL((gen_cvt_kernel<double, float>), dim3(vblocks(3 * nn)), dim3(256), 0, s, coords,
-                       (float*)p->coords, 3 * nn);
+    hipLaunchKernelGGL(gen_coords_kernel<float>, dim3(vblocks(nn)), dim3(256), 0, s, coords, (float*)p->coords, nn);
   hipLaunchKernelGGL(gen_copy_kernel<int32_t>, dim3(vblocks(8 * ne)), dim3(256), 0, s, conn, p->conn, 8 * ne);
   return hipGetLastError();
 }
@@ -933,8 +1227,8 @@ hipError_t gen_symbolic(fe_problem* p, int32_t* cnt, int32_t* coo_ptr, int32_t* 
 hipError_t gen_pairs(fe_problem* p, const int32_t* coo_ptr, hipStream_t s) {
   const int64_t nn = p->n_nodes;
   const unsigned rows_grid = (unsigned)std::min<int64_t>(nn, 65536);
-  hipLaunchKernelGGL(sym_pairs_kernel, dim3(rows_grid), dim3(64), 0, s, nn, coo_ptr, p->gen_col, p->adj_ptr, p->adj,
-                     p->pair_row, p->pair_src_ptr);
+  hipLaunchKernelGGL(sym_pairs_kernel, dim3(rows_grid), dim3(64), 0, s, nn, coo_ptr, p->gen_col, p->pair_src,
+                     p->adj_ptr, p->adj, p->pair_row, p->pair_src_ptr, p->inc_ptr, p->inc);
   hipLaunchKernelGGL(sym_last_kernel, dim3(1), dim3(1), 0, s, p->pair_src_ptr, p->n_pairs, (int32_t)(64 * p->n_el));
   return hipGetLastError();
 }
@@ -945,8 +1239,101 @@ hipError_t gen_csr_pattern(const fe_problem* p, int32_t* row_ptr, int32_t* col_i
   return hipGetLastError();
 }
 
+// Element kernel with the nodal forces to p->gen_elf.
+template <typename T, bool CG>
+static hipError_t gen_elf_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
+  const GenArgs g = gen_args(p);
+  const dim3 grid(eblocks(p->n_el)), block(GBLOCK);
+  ElemArgs b = a;
+  b.elf = p->gen_elf;
+  switch (p->model_set) {
+    case MS_J2: timed_launch((gen_elem_kernel<T, OP_APPLY, MS_J2, true, CG>), grid, block, 0, s, g, b, stop); break;
+    case MS_NH: timed_launch((gen_elem_kernel<T, OP_APPLY, MS_NH, true, CG>), grid, block, 0, s, g, b, stop); break;
+    default: timed_launch((gen_elem_kernel<T, OP_APPLY, MS_LINEAR, true, CG>), grid, block, 0, s, g, b, stop);
+  }
+  return hipGetLastError();
+}
+
+// Solver operator y = A x through the element forces (the caller owns the problem's workspaces).
+template <typename T>
+static hipError_t gen_solver_operator_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
+  hipError_t e = gen_elf_t<T, false>(p, a, stop, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gen_gather_kernel<T>, dim3(vblocks(p->n_dof)), dim3(VBLOCK), 0, s, p->n_dof, p->inc_ptr, p->inc,
+                     (const T*)p->gen_elf, a.apply_bc ? p->mask : nullptr, (const T*)a.x, (T*)a.y, stop);
+  return hipGetLastError();
+}
+
+// slots of the general CG in the problem's partial sums: GCG_Q quantities of iterate j, (p_j, A p_j)
+static double* gcg_acc(const fe_problem* p, long j) { return p->partials + (j & 1) * GCG_Q * GCG_SLOTS; }
+static double* gcg_pq(const fe_problem* p, long j) { return p->partials + (2 * GCG_Q + (j & 1)) * GCG_SLOTS; }
+
+template <typename T>
+static hipError_t gen_cg_node_t(const fe_problem* p, const void* b, void* x, long j, hipStream_t s) {
+  GenCgArgs a{};
+  a.n_nodes = p->n_nodes;
+  a.j = j;
+  a.inc_ptr = p->inc_ptr;
+  a.inc = p->inc;
+  a.elf = p->gen_elf;
+  a.mask = p->mask;
+  a.b = b;
+  a.r = p->w_r;
+  a.p = p->w_p;
+  a.pf = static_cast<T*>(p->gen_elf) + 24 * p->n_el;
+  a.x = x;
+  a.u = p->w_q;
+  a.dinv = pc_buffer(p);
+  a.ctrl = p->ctrl;
+  a.pq_in = gcg_pq(p, j);
+  a.pq_zero = gcg_pq(p, j + 1);
+  a.acc_out = gcg_acc(p, j + 1);
+  const int64_t waves = (p->n_nodes + CGN_NODES - 1) / CGN_NODES;
+  const dim3 grid((unsigned)((waves + VBLOCK / 64 - 1) / (VBLOCK / 64))), block(VBLOCK);
+  const bool blk = p->precond == FE_PC_BLOCK_JACOBI;
+  if (j < 0) {
+    if (blk) hipLaunchKernelGGL((gen_cg_node_kernel<T, true, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((gen_cg_node_kernel<T, false, true>), grid, block, 0, s, a);
+  } else {
+    if (blk) hipLaunchKernelGGL((gen_cg_node_kernel<T, true, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((gen_cg_node_kernel<T, false, false>), grid, block, 0, s, a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t gen_cgs_init(const fe_problem* p, const void* b, void* x, double rtol, int max_it, hipStream_t s) {
+  hipLaunchKernelGGL(gen_cg_start_kernel, dim3(1), dim3(256), 0, s, p->ctrl, rtol, max_it, p->partials);
+  return p->prec == FE_F64 ? gen_cg_node_t<double>(p, b, x, -1, s) : gen_cg_node_t<float>(p, b, x, -1, s);
+}
+
+hipError_t gen_cgs_operator(const fe_problem* p, long j, hipStream_t s) {
+  ElemArgs a{};
+  a.n_el = p->n_el;
+  a.phase = p->phase;
+  a.scale = p->scale;
+  a.tangent = p->tangent;
+  a.mat = p->mat;
+  a.x = p->w_q;
+  a.cg_j = j;
+  a.cg_pvec = p->w_p;
+  a.ctrl = p->ctrl;
+  a.cg_acc_in = gcg_acc(p, j);
+  a.cg_acc_zero = gcg_acc(p, j + 1);
+  a.cg_acc_out = gcg_pq(p, j);
+  const int* stop = &p->ctrl->status;
+  return p->prec == FE_F64 ? gen_elf_t<double, true>(p, a, stop, s) : gen_elf_t<float, true>(p, a, stop, s);
+}
+
+hipError_t gen_cgs_update(const fe_problem* p, void* x, long j, hipStream_t s) {
+  return p->prec == FE_F64 ? gen_cg_node_t<double>(p, nullptr, x, j, s) : gen_cg_node_t<float>(p, nullptr, x, j, s);
+}
+
 template <typename T, int OP>
 static hipError_t gen_elem_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
+  // operators of a running solver (they pass its status word) own the problem's workspaces; a
+  // plain K x may run beside others of the same problem on other streams and keeps to atomics
+  if constexpr (OP == OP_APPLY)
+    if (stop && p->gen_elf) return gen_solver_operator_t<T>(p, a, stop, s);
   const GenArgs g = gen_args(p);
   const dim3 grid(eblocks(p->n_el)), block(GBLOCK);
   switch (p->model_set) {

@@ -142,7 +142,7 @@ struct ElemArgs {
   int apply_bc;
   int store_tangent;
   Phases mat;
-  unsigned j2_mask;       // bit i: phase i is a J2 phase (set by the launch)
+  unsigned law_mask;      // bit i: phase i has the problem's nonlinear law, J2 or Neo-Hookean (set by the launch)
   // learned surrogate at J2 points whose elastic trial is plastic
   int sur_mode;           // SUR_OFF / SUR_CAPTURE / SUR_CLASSIFY / SUR_CONSUME
   int* sur_map;           // [8][n_el] list slot of each point, -1 if none
@@ -264,7 +264,7 @@ struct fe_problem {
   // general hex8 mesh (fe_problem_create_hex8; n = 0 there)
   bool general = false;
   double volume = 1.0;             // sum over Gauss points of w detJ (the unit cube: 1)
-  void* coords = nullptr;          // real [3][n_nodes]
+  void* coords = nullptr;          // real [n_nodes][3]
   int32_t* conn = nullptr;         // [8][n_el]
   int64_t n_pairs = 0;             // node pairs that share an element (nnz = 9 n_pairs)
   int32_t* adj_ptr = nullptr;      // [n_nodes + 1] first pair of each row node
@@ -273,6 +273,9 @@ struct fe_problem {
   int32_t* pair_src_ptr = nullptr; // [n_pairs + 1] run of each pair in pair_src
   int32_t* pair_src = nullptr;     // [64 n_el] element codes e*64 + a*8 + b sorted by (row, column, code)
   int32_t* gen_col = nullptr;      // [64 n_el] sorted column nodes (work array of the symbolic step)
+  int32_t* inc_ptr = nullptr;      // [n_nodes + 1] first incidence of each node
+  int32_t* inc = nullptr;          // [8 n_el] incidences 8 element + local node, by node, in element order
+  void* gen_elf = nullptr;         // solvers: element nodal forces [n_el][8][3], then CG's p on constrained dofs [n_dof] (on first use)
   void* ke = nullptr;              // element Jacobians [n_el][576] (allocated on the first tangent)
 };
 
@@ -300,6 +303,12 @@ inline void timed_launch(F kernel, dim3 grid, dim3 block, uint32_t shmem, hipStr
   } else {
     hipLaunchKernelGGL(kernel, grid, block, shmem, s, args...);
   }
+}
+
+inline unsigned law_mask(const fe_problem* p) {
+  unsigned m = 0;
+  for (int i = 0; i < p->mat.n; ++i) m |= p->mat.ph[i].model != FE_LINEAR ? 1u << i : 0u;
+  return m;
 }
 
 // kernel launchers (fe_kernels.hip); each returns hipError_t of the launch
@@ -393,6 +402,11 @@ hipError_t gen_pairs(fe_problem* p, const int32_t* coo_ptr, hipStream_t s);
 hipError_t gen_csr_pattern(const fe_problem* p, int32_t* row_ptr, int32_t* col_idx, hipStream_t s);
 hipError_t gen_launch_elem(const fe_problem* p, int op, const ElemArgs& a, const int* stop, hipStream_t s);
 hipError_t gen_cg_operator(const fe_problem* p, hipStream_t s);
+// PCG on a general mesh (needs gen_elf): start, then per iteration j the element launch (test,
+// direction, forces of A p_j) and the node launch (A p_j gathered, update)
+hipError_t gen_cgs_init(const fe_problem* p, const void* b, void* x, double rtol, int max_it, hipStream_t s);
+hipError_t gen_cgs_operator(const fe_problem* p, long j, hipStream_t s);
+hipError_t gen_cgs_update(const fe_problem* p, void* x, long j, hipStream_t s);
 hipError_t gen_diag(const fe_problem* p, void* d, int nb, int apply_bc, const TanArgs& ta, hipStream_t s);
 hipError_t gen_tangent(const fe_problem* p, void* vals, int apply_bc, const TanArgs& ta, hipStream_t s);
 hipError_t gen_lift(const fe_problem* p, const double* E, void* u, int zero_free, hipStream_t s);

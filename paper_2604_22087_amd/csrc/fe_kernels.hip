@@ -36,9 +36,9 @@ constexpr int EBLOCK = 2 * TX * TY * TZ;     // two lanes per element
 constexpr int EWAVES = EBLOCK / 64;
 constexpr int ROWW = 3 * NX, NROWS = NY * NZ;  // a brick's node rows (along x): words per row, rows
 constexpr int ROW_IT = (NROWS + EWAVES - 1) / EWAVES;
-constexpr int NACC = (3 * CGS_SLOTS + EBLOCK - 1) / EBLOCK;  // reduction slots per lane
+constexpr int NACC = cg_slots_per_lane<EWAVES>();  // reduction slots per lane
+static_assert(6 * EWAVES >= 12, "room for the slot sums");
 static_assert(TX == 16 && TY == 4 && ROWW <= 64, "lane layout of the element kernel");
-static_assert(CGS_SLOTS == 256, "four waves per reduced quantity");
 
 
 // CG direction step of iteration k (see the CG section below); false when the
@@ -236,20 +236,10 @@ struct Brick {
 //   p_i = M^-1 r_i + beta_i p_{i-1},  x_{i+1} = x_i + alpha_i p_i  for i = j-2 and j-1,
 // with r_{j-2} read from the buffer that r_j replaces.  cgs_flush makes up the last odd step.
 // u_j goes to s_x (0 on constrained dofs, whose value goes to s_b), s_y is cleared.
-// The scalars of earlier launches that launch j uses (workgroup 0 of launch j writes none of them).
-struct CgHist {
-  double rtol2, tol2, g, alpha, beta;  // g, alpha, beta of iterate j-2
-  int status, max_it;
-};
-
-template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const CgHist& c, const double v_in[NACC],
-                                           double (*sh)[EWAVES], T& alpha_out, T& beta_out);
-
 // (the node's three components sit in adjacent lanes of the row: node-block Jacobi fetches the
 // other two by lane exchange)
 template <typename T, bool BLK, typename Acc, typename Early>
-__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& br, double (*sh)[EWAVES], T* s_x,
+__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& br, double* sh, T* s_x,
                                                Acc* s_y, T* s_b, unsigned& fixed, double& g, double& rr,
                                                Early&& early) {
   // the previous launch's slot sums are requested before the staging loads (loads return in
@@ -262,9 +252,7 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
       if (br.wave + k * EWAVES < 12) acc_v[k] = a.cg_acc_in[k * EBLOCK + threadIdx.x];
   }
   // requested with everything else: one wait instead of a test of the status word before any load
-  const CgCtrl* cc = a.ctrl;
-  const int slot = (int)(a.cg_j & 1);
-  const CgHist ctl = {cc->rtol2, cc->tol2, cc->ghist[slot], cc->ahist[slot], cc->bhist[slot], cc->status, cc->max_it};
+  const CgHist ctl = cg_history(a.ctrl, a.cg_j);
   T alpha = 0, beta = 0;
   const bool two = a.cg_j >= 2 && (a.cg_j & 1) == 0;  // p and x advance
   const T* __restrict__ RO = static_cast<const T*>(a.cg_rold);
@@ -311,7 +299,11 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
   }
   early();
   if (ctl.status) return false;  // the solve has stopped
-  if (prev && !cg_scalars<T>(a, ctl, acc_v, sh, alpha, beta)) return false;
+  if (prev) {  // run redundantly by every workgroup: no inter-workgroup synchronisation in a launch
+    double d, gs, rs;
+    cg_slot_sums<EWAVES>(acc_v, sh, d, gs, rs);
+    if (!cg_coefficients<T>(a.ctrl, ctl, a.cg_j, d, gs, rs, alpha, beta)) return false;
+  }
   const T alpha2 = T(ctl.alpha), beta2 = T(ctl.beta);
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
@@ -360,72 +352,6 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
     }
   }
   return true;
-}
-
-// Start of single-reduction CG launch j >= 1, run redundantly by every workgroup (no
-// inter-workgroup synchronisation inside a launch): sum the slots of launch j-1 in fixed
-// order into d = (u, A u), g = (r, u), rr = ||r||^2 of iterate j-1 and form
-// (Chronopoulos & Gear 1989)
-//   beta_{j-1} = g_{j-1} / g_{j-2},  alpha_{j-1} = g_{j-1} / (d_{j-1} - beta g_{j-1} / alpha_{j-2})
-// (j = 1: beta_0 = 0, alpha_0 = g_0 / d_0), or a stop: ||r_{j-1}|| <= rtol ||b||,
-// j - 1 = max_it, breakdown, non-finite.  Workgroup 0 records the scalars and the status;
-// (g, alpha) of iterate j-1 go to history slot (j-1) & 1 while slot j & 1 is read.
-// Returns false when the iteration stops (every workgroup reaches the same decision).
-template <typename T>
-__device__ __forceinline__ bool cg_scalars(const ElemArgs& a, const CgHist& c, const double v_in[NACC],
-                                           double (*sh)[EWAVES], T& alpha_out, T& beta_out) {
-  const long j = a.cg_j;
-  double v[NACC];  // 64 slots per wave; the 12 wave sums are four each of d, g and rr
-#pragma unroll
-  for (int k = 0; k < NACC; ++k) v[k] = wave_sum_last(v_in[k]);
-  if ((threadIdx.x & 63) == WAVE_LAST)
-#pragma unroll
-    for (int k = 0; k < NACC; ++k) sh[k][threadIdx.x >> 6] = v[k];
-  __syncthreads();
-  double d = 0, g = 0, rr = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    d += (&sh[0][0])[w];
-    g += (&sh[0][0])[4 + w];
-    rr += (&sh[0][0])[8 + w];
-  }
-  __syncthreads();  // sh is reused by the caller
-  const int slot = (int)(j & 1);  // history of iterate j-2
-  const double tol2 = j == 1 ? c.rtol2 * rr : c.tol2;
-  int st = CG_RUNNING;
-  double alpha = 0, beta = 0;
-  if (!finite(d) || !finite(g) || !finite(rr)) {
-    st = FE_ERR_NONFINITE;
-  } else if (j == 1 ? rr == 0.0 : rr <= tol2) {
-    st = CG_CONVERGED;
-  } else if (j - 1 >= c.max_it) {
-    st = FE_ERR_NOT_CONVERGED;
-  } else {
-    beta = j == 1 ? 0.0 : g / c.g;
-    const double den = j == 1 ? d : d - beta * g / c.alpha;
-    if (!finite(den)) st = FE_ERR_NONFINITE;
-    else if (den <= 0.0) st = FE_ERR_BREAKDOWN;
-    else alpha = g / den;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    CgCtrl* w = a.ctrl;
-    if (j == 1) {
-      w->bb = rr;
-      w->tol2 = tol2;
-    }
-    w->rr = rr;
-    w->pq = d;
-    w->iters = (int)(j - 1);
-    w->alpha = alpha;
-    w->beta = beta;
-    w->ghist[slot ^ 1] = g;
-    w->ahist[slot ^ 1] = alpha;
-    w->bhist[slot ^ 1] = beta;
-    if (st != CG_RUNNING) w->status = st;
-  }
-  alpha_out = T(alpha);
-  beta_out = T(beta);
-  return st == CG_RUNNING;
 }
 
 // ---------------------------------------------------------------------------
@@ -484,13 +410,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   const int64_t e4 = e + 4 * r * ne;  // first point of this half in [..][8][n_el] arrays
   const T h = T(a.h);
   const T w0 = r ? T(GB) : T(GA), w1 = r ? T(GA) : T(GB);
-  // the phase table goes to LDS: a lane's constants are then one short read after the barrier
-  // instead of a dependent trip to memory
-  if (tid < 8 * FE_MAX_PHASES && (tid >> 3) < a.mat.n) {
-    const PhaseConst& c = a.mat.ph[tid >> 3];
-    const int k = tid & 7;
-    s_mat[tid] = k == 0 ? c.lam : k == 1 ? c.mu : k == 2 ? c.K : k == 3 ? c.G : k == 4 ? c.sy : k == 5 ? c.H : (double)c.model;
-  }
+  stage_phases(a.mat, s_mat, tid);
   // the element's phase is requested before the staging loads; the operator's first stored-
   // tangent word of every Gauss point right after them (both arrive before they are used)
   const int ph = valid ? (int)a.phase[e] : 0;
@@ -498,7 +418,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   T tq0[4];
   auto early = [&]() {
     if (APPLY_LIKE && J2M) {
-      const bool j2 = valid && ((a.j2_mask >> ph) & 1u);
+      const bool j2 = valid && ((a.law_mask >> ph) & 1u);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) tq0[qq] = j2 ? tang_c[e4 + qq * ne] : T(-1);
     }
@@ -511,8 +431,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     if (blockIdx.x == 0)
       for (int i = tid; i < 3 * CGS_SLOTS; i += EBLOCK) a.cg_acc_zero[i] = 0.0;  // slots of launch j+1
     // (one instance per preconditioner form, so each staging path is branch-free)
-    const bool go = a.cg_block ? cg_stage_brick<T, true>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
-                               : cg_stage_brick<T, false>(a, br, s_red, s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
+    const bool go = a.cg_block ? cg_stage_brick<T, true>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
+                               : cg_stage_brick<T, false>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
     if (!go) return;
     cg_g = wave_sum_last(cg_g);
     cg_rr = wave_sum_last(cg_rr);
@@ -560,12 +480,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   double pq = 0;
 
   if (valid) {
-    PhaseConst pc;
-    {
-      const double* m = s_mat + 8 * ph;
-      pc.lam = m[0], pc.mu = m[1], pc.K = m[2], pc.G = m[3], pc.sy = m[4], pc.H = m[5];
-      pc.model = (int)m[6];
-    }
+    const PhaseConst pc = phase_const(s_mat, ph);
     const T sc = (a.scale && OP != OP_VJP) ? static_cast<const T*>(a.scale)[e] : T(1);
 
     // J2 operator: the first stored-tangent word of every Gauss point arrived with the staging
@@ -918,8 +833,7 @@ template <typename T, int OP>
 static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
   const dim3 grid(elem_grid(p->n)), block(EBLOCK);
   ElemArgs b = a;
-  b.j2_mask = 0;
-  for (int i = 0; i < p->mat.n; ++i) b.j2_mask |= p->mat.ph[i].model == FE_J2 ? 1u << i : 0u;
+  b.law_mask = law_mask(p);
   // J2 problems that may meet surrogate points (their stored tangents, or a surrogate / capture
   // mode of this residual) take the instance with those branches
   const bool sur = p->model_set == MS_J2 && (OP == OP_RESID ? a.sur_mode != SUR_OFF : p->sur_map != nullptr);
@@ -2115,7 +2029,7 @@ static hipError_t cg_operator_t(const fe_problem* p, int op, const int32_t* rp, 
 // Chronopoulos & Gear 1989; exact-arithmetic equivalent of the CG recursion):
 //   launch j forms u_j = M^-1 r_j, w_j = A u_j and the partials of (u_j, w_j),
 //   (r_j, u_j), ||r_j||^2; its staging forms alpha and beta of iterate j-1 or a stop from the
-//   partials of launch j-1 and applies that update (see cg_scalars, cg_stage_brick).
+//   partials of launch j-1 and applies that update (see cg_coefficients, cg_stage_brick).
 // Vectors: x (caller), p (in place, owners only), r in two buffers, s in two, w in three
 // (launch j writes w into the buffer that launch j-1 zeroed).
 
