@@ -711,7 +711,7 @@ static int ipcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci,
   if (int e = detect_csr_structure(p, op, rp, ci, s)) return e;
   if (!p->w_ipcg && alloc(&p->w_ipcg, 4 * real_size(p) * (size_t)p->n_dof)) return FE_ERR_OOM;
   if (!p->ipcg && alloc((void**)&p->ipcg, sizeof(IpcgCtrl))) return FE_ERR_OOM;
-  if (!p->gm_part && alloc((void**)&p->gm_part, (size_t)(GM_MAXM + 1) * GM_GRID * sizeof(double)))
+  if (!p->gm_part && alloc((void**)&p->gm_part, GM_PART_DOUBLES * sizeof(double)))
     return FE_ERR_OOM;
   HIPCHK(ilu_setup(p, rp, ci, vals, s));
   const int* stop = &p->ipcg->status;
@@ -947,7 +947,7 @@ static int gmres_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci
     p->gm_cap = m;
   }
   if (!p->gm_dev && alloc((void**)&p->gm_dev, sizeof(GmresDev))) return FE_ERR_OOM;
-  if (!p->gm_part && alloc((void**)&p->gm_part, (size_t)(GM_MAXM + 1) * GM_GRID * sizeof(double)))
+  if (!p->gm_part && alloc((void**)&p->gm_part, GM_PART_DOUBLES * sizeof(double)))
     return FE_ERR_OOM;
   if (p->precond == FE_PC_ILU0) {
     if (!rp) return arg_error("FE_PC_ILU0 needs the assembled CSR matrix");
@@ -986,11 +986,12 @@ static int gmres_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci
     int j = 0, chunk = 4;
     while (j < m) {
       for (int c = 0; c < chunk && j < m; ++c, ++j) {
-        HIPCHK(gm_step(p, GM_BASIS, j, b, x, s));
+        HIPCHK(gm_step(p, GM_BASIS, j, b, x, s, c > 0 ? 1 : 0));
         if (ilu) HIPCHK(ilu_apply(p, gm_work_z(p), gm_work_z(p), stop, s));
         HIPCHK(apply(gm_work_z(p), gm_work_w(p), stop));
         HIPCHK(gm_step(p, GM_ORTHO, j, b, x, s));
       }
+      HIPCHK(gm_step(p, GM_GIVENS, j - 1, b, x, s));
       if (int e = poll()) return e;
       if (hc->status != CG_RUNNING) break;
       if (chunk < 16) chunk *= 2;

@@ -58,7 +58,6 @@ struct GmresCtrl {
   double rtol, tol;  // tol = rtol ||b|| (set at the first cycle start)
   double bb;         // ||b||^2 (-1 until the first cycle start)
   double res_est;    // |g_k|: residual norm of the current least-squares iterate
-  double inv_norm;   // 1 / ||w|| for the next basis vector
   int status;        // CG_RUNNING, CG_CONVERGED or an fe_status error code
   int iters;         // Arnoldi steps over all cycles
   int max_it;
@@ -73,7 +72,6 @@ struct GmresDev {
   double cs[GM_MAXM], sn[GM_MAXM];
   double g[GM_MAXM + 1];
   double y[GM_MAXM];
-  double c[2][GM_MAXM + 1];        // Gram-Schmidt coefficients of the two passes
 };
 
 // CG with a separately applied preconditioner (ILU(0)), fe_krylov.hip
@@ -86,7 +84,8 @@ struct IpcgCtrl {
 
 enum IpcgStage { IPCG_INIT = 1, IPCG_CHECK_FIRST, IPCG_FIRST_DIRECTION, IPCG_UPDATE, IPCG_CHECK, IPCG_DIRECTION };
 
-enum GmStage { GM_START = 1, GM_BASIS, GM_ORTHO, GM_FINISH, GM_RESIDUAL, GM_ADD_Z };
+enum GmStage { GM_START = 1, GM_BASIS, GM_ORTHO, GM_GIVENS, GM_FINISH, GM_RESIDUAL, GM_ADD_Z };
+constexpr size_t GM_PART_DOUBLES = 2 * (size_t)(GM_MAXM + 1) * GM_GRID;  // partial sums of two passes
 
 // single-reduction CG: slots per reduced quantity that the workgroups of a launch add into
 constexpr int CGS_SLOTS = 256;
@@ -213,7 +212,7 @@ struct fe_problem {
   void* w_gm = nullptr;       // GMRES: basis [gm_cap + 1][n_dof], then w and z [n_dof] each
   int gm_cap = 0;             // restart length w_gm was sized for
   fe::GmresDev* gm_dev = nullptr; // GMRES scalars (device)
-  double* gm_part = nullptr;  // [GM_MAXM + 1][GM_GRID] partial sums
+  double* gm_part = nullptr;  // [2][GM_MAXM + 1][GM_GRID] partial sums
   void* w_cg = nullptr;       // single-reduction CG vectors r_1, s_0, s_1, w_0, w_1, w_2 (allocated on first use)
   void* w_bicg = nullptr;     // BiCGStab vectors r, r_hat, p, v, s, t, p_hat, s_hat (allocated on first use)
   double* bicg_part = nullptr;  // BiCGStab partial sums [8][BICG_GRID]
@@ -365,10 +364,11 @@ hipError_t cg_operator(const fe_problem* p, int op, const int32_t* rp, const int
 hipError_t cg_vectors(const fe_problem* p, int op, void* x, long k, hipStream_t s);
 hipError_t cg_pre(const fe_problem* p, int op, long k, hipStream_t s);  // CSR: direction kernel before the mat-vec
 // restarted GMRES pieces (fe_krylov.hip): setup (x = 0, w = b, preconditioner inverted),
-// then per cycle GM_START, per Arnoldi step j GM_BASIS + operator (z -> w) + GM_ORTHO,
-// GM_FINISH at the cycle end, and A x -> w + GM_RESIDUAL before the next cycle
+// then per cycle GM_START, per Arnoldi step j GM_BASIS (open_step: it closes step j - 1 first) +
+// operator (z -> w) + GM_ORTHO, GM_GIVENS after a step that no basis launch closes, GM_FINISH at
+// the cycle end, and A x -> w + GM_RESIDUAL before the next cycle
 hipError_t gm_setup(const fe_problem* p, const void* b, void* x, double rtol, int max_it, int m, hipStream_t s);
-hipError_t gm_step(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s);
+hipError_t gm_step(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s, int open_step = 0);
 void* gm_work_w(const fe_problem* p);
 void* gm_work_z(const fe_problem* p);
 // z = M^-1 r with the point (diagonal in w_d, not inverted) or node-block (inverted

@@ -1,18 +1,20 @@
 // Restarted GMRES(m) on the device (right preconditioning), for nonsymmetric operators.
 //
 // Fig. 4 compares GMRES with CG and BiCGStab on the assembled system.  One Arnoldi
-// step here: v_j = w / h_{j,j-1} and z = M^-1 v_j (one launch), w = A z (the library's
-// operator), classical Gram-Schmidt run twice (dots, reduce, update; dots, reduce,
-// update + ||w||^2; the second pass restores the orthogonality that one classical pass
-// loses in floating point), then one workgroup applies the Givens rotations to the new
-// Hessenberg column and tests |g_{j+1}| <= rtol ||b||.  All dot products are FP64 and
-// summed in a fixed order (per-workgroup partials, then one workgroup per vector).
+// step here: the Givens rotations of the step before, v_j = w / h_{j,j-1} and z = M^-1 v_j (one
+// launch), w = A z (the library's operator), then classical Gram-Schmidt run twice (the second
+// pass restores the orthogonality that one classical pass loses in floating point) in three
+// launches: the dots of pass 1; w -= V c_1 with the dots of pass 2, which need only the lane's own
+// new entries of w; w -= V c_2 with ||w||^2.  Every workgroup sums the partials of the launch
+// before by itself, so nothing waits for a reduction launch (four launches a step and the operator
+// in place of nine; with 15 vectors at 32^3 FP64 27 us of launches in place of 50).  All dot products are FP64 and summed in a fixed order.
 // Iteration kernels return at once after a stop; the cycle-end kernels (triangular solve,
 // x += M^-1 V y) always run.
 
 #include <cmath>
 
 #include "fe_internal.hpp"
+#include "fe_device.hpp"
 
 namespace fe {
 
@@ -20,19 +22,13 @@ namespace {
 
 constexpr int KB = 256;  // threads per workgroup of every GMRES kernel
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-
 // Sum of part[0..np) by the whole workgroup, in fixed order; valid in every lane.
 __device__ double group_sum(const double* part, int np, double* sh) {
   double v = 0;
   for (int i = threadIdx.x; i < np; i += KB) v += part[i];
-  v = wave_sum(v);
+  v = wave_sum_last(v);
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   double t = 0;
 #pragma unroll
@@ -103,8 +99,8 @@ __global__ __launch_bounds__(KB) void gm_dots_kernel(int64_t n, const T* V, int 
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const double t = wave_sum(acc[u]);
-      if ((threadIdx.x & 63) == 0) sh[u][threadIdx.x >> 6] = t;
+      const double t = wave_sum_last(acc[u]);
+      if ((threadIdx.x & 63) == WAVE_LAST) sh[u][threadIdx.x >> 6] = t;
     }
     __syncthreads();
     if (threadIdx.x < 8 && i0 + (int)threadIdx.x < nv) {
@@ -117,46 +113,138 @@ __global__ __launch_bounds__(KB) void gm_dots_kernel(int64_t n, const T* V, int 
   }
 }
 
-// One workgroup per vector i < nv: c_i = sum of its partials; pass 0 sets the Hessenberg
-// entries H[j][i] = c_i, pass 1 adds the re-orthogonalisation coefficients to them.
-__global__ __launch_bounds__(KB) void gm_reduce_kernel(const double* part, int np, GmresDev* dev, int j, int pass,
-                                                       const int* stop) {
-  if (stop && *stop) return;
-  __shared__ double sh[KB / 64];
-  const int i = blockIdx.x;
-  const double c = group_sum(part + (int64_t)i * np, np, sh);
-  if (threadIdx.x == 0) {
-    dev->c[pass][i] = c;
-    dev->H[j][i] = pass == 0 ? c : dev->H[j][i] + c;
-  }
-}
+// One launch of the Gram-Schmidt of step j over nv vectors:
+//   PASS 0: the dots c_1 = V^T w                            -> part_out
+//   PASS 1: w -= V c_1, then the dots c_2 = V^T w           -> part_out
+//   PASS 2: w -= V c_2, then ||w||^2                        -> part_out
+// c comes from the np partials per vector of the launch before, summed in a fixed order by every
+// workgroup (16 lanes per vector).  A lane's entries of up to GT vectors are requested before that
+// and stay in registers for both the update and the dots: V is read once a launch, and its latency
+// hides behind the sums.  Workgroup 0 records the Hessenberg entries (pass 2 adds the
+// re-orthogonalisation coefficients).
+constexpr int GB = 512;  // lanes: one dof each up to 512 workgroups, then a loop
+constexpr int GT = 32;   // vectors held in registers
 
-// w -= sum_{i<nv} c_i V_i with c = dev->c[pass]; with_norm: part[blockIdx] = partial ||w||^2.
-template <typename T>
-__global__ __launch_bounds__(KB) void gm_update_kernel(int64_t n, const T* V, int nv, T* w, const GmresDev* dev,
-                                                       int pass, int with_norm, double* part, const int* stop) {
-  if (stop && *stop) return;
-  __shared__ double cs[GM_MAXM + 1];
-  __shared__ double sh[KB / 64];
-  for (int i = threadIdx.x; i < nv; i += KB) cs[i] = dev->c[pass][i];
-  __syncthreads();
-  double nrm = 0;
-  for (int64_t d = (int64_t)blockIdx.x * KB + threadIdx.x; d < n; d += (int64_t)gridDim.x * KB) {
-    double t = (double)w[d];
-    for (int i = 0; i < nv; ++i) t -= cs[i] * (double)V[(int64_t)i * n + d];
-    const T tv = T(t);
-    w[d] = tv;
-    nrm += (double)tv * (double)tv;
+template <typename T, int PASS>
+__global__ __launch_bounds__(GB) void gm_pass_kernel(int64_t n, const T* __restrict__ V, int nv, T* w, GmresDev* dev,
+                                                     int j, const double* part_in, int np, double* part_out,
+                                                     const int* stop) {
+  __shared__ double cs[GM_MAXM + GT + 1];
+  __shared__ double sh[GM_MAXM + 1][GB / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int stopped = *stop;
+  const int nt = min(nv, GT);
+  T v[GT];
+  auto request = [&](int64_t d, bool in, int i0, int cnt) {  // entries d of V_{i0} .. V_{i0 + cnt - 1}
+#pragma unroll
+    for (int b = 0; b < GT; b += 8) {
+      if (b < cnt) {  // (uniform: whole groups of 8; past the end the last vector is read again, with c = 0)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[b + u] = in ? V[(int64_t)(i0 + min(b + u, cnt - 1)) * n + d] : T(0);
+      }
+    }
+  };
+  int64_t d = (int64_t)blockIdx.x * GB + tid;
+  request(d, d < n, 0, nt);
+  double wd = d < n ? (double)w[d] : 0.0;
+  if (stopped) return;
+  if (PASS > 0) {
+    for (int i = tid; i < GM_MAXM + GT + 1; i += GB)
+      if (i >= nv) cs[i] = 0.0;
+    for (int i = tid >> 4; i < nv; i += GB / 16) {
+      double c = 0;
+#pragma unroll 4
+      for (int q = tid & 15; q < np; q += 16) c += part_in[(int64_t)i * np + q];
+      c = dpp_add<0x111, 0xf>(c);  // row_shr 1, 2, 4, 8: the 16 lanes' sum in the last of them
+      c = dpp_add<0x112, 0xf>(c);
+      c = dpp_add<0x114, 0xf>(c);
+      c = dpp_add<0x118, 0xf>(c);
+      if ((tid & 15) == 15) cs[i] = c;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0)
+      for (int i = tid; i < nv; i += GB) dev->H[j][i] = PASS == 1 ? cs[i] : dev->H[j][i] + cs[i];
   }
-  if (!with_norm) return;
-  nrm = wave_sum(nrm);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = nrm;
+  double acc[GT], nrm = 0;
+#pragma unroll
+  for (int u = 0; u < GT; ++u) acc[u] = 0;
+  bool first = true;
+  for (; d - tid < n; d += (int64_t)gridDim.x * GB) {
+    const bool in = d < n;
+    if (!first) {
+      request(d, in, 0, nt);
+      wd = in ? (double)w[d] : 0.0;
+    }
+    first = false;
+    if (PASS > 0) {
+      double t = wd;
+#pragma unroll
+      for (int b = 0; b < GT; b += 8)
+        if (b < nt)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) t -= cs[b + u] * (double)v[b + u];
+      for (int i = GT; i < nv; ++i) t -= cs[i] * (double)(in ? V[(int64_t)i * n + d] : T(0));
+      const T tv = T(t);
+      if (in) w[d] = tv;
+      wd = (double)tv;
+      if (PASS == 2) nrm += wd * wd;
+    }
+    if (PASS < 2)
+#pragma unroll
+      for (int b = 0; b < GT; b += 8)
+        if (b < nt)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc[b + u] += (double)v[b + u] * wd;
+  }
+  if (PASS == 2) {
+    nrm = wave_sum_last(nrm);
+    if (lane == WAVE_LAST) sh[0][wave] = nrm;
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0;
+#pragma unroll
+      for (int q = 0; q < GB / 64; ++q) t += sh[0][q];
+      part_out[blockIdx.x] = t;
+    }
+    return;
+  }
+#pragma unroll
+  for (int b = 0; b < GT; b += 8)
+    if (b < nt)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double t = wave_sum_last(acc[b + u]);
+        if (lane == WAVE_LAST) sh[b + u][wave] = t;
+      }
+  for (int i0 = GT; i0 < nv; i0 += GT) {  // longer restarts: the other vectors, w from memory (own entries)
+    const int cnt = min(nv - i0, GT);
+#pragma unroll
+    for (int u = 0; u < GT; ++u) acc[u] = 0;
+    for (d = (int64_t)blockIdx.x * GB + tid; d - tid < n; d += (int64_t)gridDim.x * GB) {
+      const bool in = d < n;
+      request(d, in, i0, cnt);
+      const double x = in ? (double)w[d] : 0.0;
+#pragma unroll
+      for (int b = 0; b < GT; b += 8)
+        if (b < cnt)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc[b + u] += (double)v[b + u] * x;
+    }
+#pragma unroll
+    for (int b = 0; b < GT; b += 8)
+      if (b < cnt)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const double t = wave_sum_last(acc[b + u]);
+          if (lane == WAVE_LAST && b + u < cnt) sh[i0 + b + u][wave] = t;
+        }
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  for (int i = tid; i < nv; i += GB) {
     double t = 0;
 #pragma unroll
-    for (int q = 0; q < KB / 64; ++q) t += sh[q];
-    part[blockIdx.x] = t;
+    for (int q = 0; q < GB / 64; ++q) t += sh[i][q];
+    part_out[(int64_t)i * gridDim.x + blockIdx.x] = t;
   }
 }
 
@@ -183,18 +271,68 @@ __global__ __launch_bounds__(KB) void gm_beta_kernel(const double* part, int np,
     c.status = CG_CONVERGED;
   } else if (c.iters >= c.max_it) {
     c.status = FE_ERR_NOT_CONVERGED;
-  } else {
-    c.inv_norm = 1.0 / beta;
   }
 }
 
+// End of Arnoldi step j (one lane): h_{j+1,j} = ||w||, rotations on column j, new rotation, g
+// update, stopping tests.
+__device__ void givens_step(GmresDev* dev, int j, double hn) {
+  GmresCtrl& c = dev->ctrl;
+  double* h = dev->H[j];
+  h[j + 1] = hn;
+  if (!is_finite(hn)) {
+    c.status = FE_ERR_NONFINITE;
+    return;
+  }
+  double t = h[0];  // the running entry of the column stays in a register
+  for (int i = 0; i < j; ++i) {
+    const double a = dev->cs[i], b = dev->sn[i], hi = h[i + 1];
+    h[i] = a * t + b * hi;
+    t = -b * t + a * hi;
+  }
+  const double rho = std::hypot(t, hn);
+  if (rho == 0.0) {
+    c.status = FE_ERR_BREAKDOWN;
+    return;
+  }
+  const double cj = t / rho, sj = hn / rho, gj = dev->g[j];
+  dev->cs[j] = cj;
+  dev->sn[j] = sj;
+  h[j] = rho;
+  h[j + 1] = 0.0;
+  dev->g[j + 1] = -sj * gj;
+  dev->g[j] = cj * gj;
+  const int iters = c.iters + 1;
+  c.iters = iters;
+  c.k = j + 1;
+  const double res = std::fabs(sj * gj);
+  c.res_est = res;
+  if (res <= c.tol) c.status = CG_CONVERGED;
+  else if (iters >= c.max_it) c.status = FE_ERR_NOT_CONVERGED;
+}
+
+__global__ __launch_bounds__(KB) void gm_givens_kernel(const double* part, int np, GmresDev* dev, int j,
+                                                       const int* stop) {
+  __shared__ double sh[KB / 64];
+  if (stop && *stop) return;
+  const double hn = std::sqrt(group_sum(part, np, sh));
+  if (threadIdx.x == 0) givens_step(dev, j, hn);
+}
+
 // v_j = w / ||w|| (stored as basis vector j) and z = M^-1 v_j, one node per lane; w is
-// cleared for the operator, which adds its face contributions atomically.
+// cleared for the operator, which adds its face contributions atomically.  ||w|| is summed from
+// the np partials of the launch before; with givens, workgroup 0 first closes Arnoldi step j - 1
+// (a stop found there takes effect at the next launch: this one only fills vectors that a stopped
+// cycle does not read).
 template <typename T>
 __global__ __launch_bounds__(KB) void gm_basis_kernel(int64_t n_nodes, T* w, T* vj, T* z, const T* M, int blk,
-                                                      const GmresDev* dev, const int* stop) {
-  if (stop && *stop) return;
-  const T s = T(dev->ctrl.inv_norm);
+                                                      const double* part, int np, GmresDev* dev, int j, int givens,
+                                                      const int* stop) {
+  __shared__ double sh[KB / 64];
+  if (*stop) return;
+  const double hn = std::sqrt(group_sum(part, np, sh));
+  if (givens && blockIdx.x == 0 && threadIdx.x == 0) givens_step(dev, j - 1, hn);
+  const T s = T(1.0 / hn);
   for (int64_t nd = (int64_t)blockIdx.x * KB + threadIdx.x; nd < n_nodes; nd += (int64_t)gridDim.x * KB) {
     T v[3], zz[3];
 #pragma unroll
@@ -209,54 +347,20 @@ __global__ __launch_bounds__(KB) void gm_basis_kernel(int64_t n_nodes, T* w, T* 
   }
 }
 
-// End of Arnoldi step j (one workgroup): h_{j+1,j} = ||w||, rotations on column j,
-// new rotation, g update, stopping tests.
-__global__ __launch_bounds__(KB) void gm_givens_kernel(const double* part, int np, GmresDev* dev, int j,
-                                                       const int* stop) {
-  if (stop && *stop) return;
-  __shared__ double sh[KB / 64];
-  const double hn = std::sqrt(group_sum(part, np, sh));
-  if (threadIdx.x != 0) return;
-  GmresCtrl& c = dev->ctrl;
-  double* h = dev->H[j];
-  h[j + 1] = hn;
-  if (!is_finite(hn)) {
-    c.status = FE_ERR_NONFINITE;
-    return;
+// y = R^-1 g over the k finished columns (one wave; k <= GM_MAXM = 64: lane i holds entry i, column
+// by column from the last).
+__global__ __launch_bounds__(64) void gm_solve_kernel(GmresDev* dev) {
+  static_assert(GM_MAXM <= 64, "one lane per entry");
+  const int k = dev->ctrl.k, i = threadIdx.x;
+  double g = i < k ? dev->g[i] : 0.0;
+  const double d = i < k ? dev->H[i][i] : 1.0;
+  for (int q = k - 1; q >= 0; --q) {
+    const double h = i < q ? dev->H[q][i] : 0.0;
+    const double yq = __shfl(g / d, q, 64);
+    if (i == q) g = yq;
+    else g -= h * yq;
   }
-  for (int i = 0; i < j; ++i) {
-    const double t = dev->cs[i] * h[i] + dev->sn[i] * h[i + 1];
-    h[i + 1] = -dev->sn[i] * h[i] + dev->cs[i] * h[i + 1];
-    h[i] = t;
-  }
-  const double rho = std::hypot(h[j], h[j + 1]);
-  if (rho == 0.0) {
-    c.status = FE_ERR_BREAKDOWN;
-    return;
-  }
-  dev->cs[j] = h[j] / rho;
-  dev->sn[j] = h[j + 1] / rho;
-  h[j] = rho;
-  h[j + 1] = 0.0;
-  dev->g[j + 1] = -dev->sn[j] * dev->g[j];
-  dev->g[j] = dev->cs[j] * dev->g[j];
-  c.iters += 1;
-  c.k = j + 1;
-  c.res_est = std::fabs(dev->g[j + 1]);
-  if (c.res_est <= c.tol) c.status = CG_CONVERGED;
-  else if (c.iters >= c.max_it) c.status = FE_ERR_NOT_CONVERGED;
-  else c.inv_norm = 1.0 / hn;
-}
-
-// y = R^-1 g over the k finished columns (one lane; k <= GM_MAXM).
-__global__ void gm_solve_kernel(GmresDev* dev) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  const int k = dev->ctrl.k;
-  for (int i = k - 1; i >= 0; --i) {
-    double t = dev->g[i];
-    for (int q = i + 1; q < k; ++q) t -= dev->H[q][i] * dev->y[q];
-    dev->y[i] = t / dev->H[i][i];
-  }
+  if (i < k) dev->y[i] = g;
 }
 
 // x += M^-1 (sum_{i<k} y_i V_i), one node per lane (blk = 2: t = sum_i y_i V_i goes to
@@ -307,8 +411,8 @@ __global__ __launch_bounds__(KB) void gm_residual_kernel(int64_t n, const T* b, 
     w[d] = t;
     nrm += (double)t * (double)t;
   }
-  nrm = wave_sum(nrm);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = nrm;
+  nrm = wave_sum_last(nrm);
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[threadIdx.x >> 6] = nrm;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0;
@@ -322,32 +426,40 @@ template <typename T> T* basis(const fe_problem* p, int i) { return static_cast<
 template <typename T> T* work_w(const fe_problem* p) { return basis<T>(p, p->gm_cap + 1); }
 template <typename T> T* work_z(const fe_problem* p) { return basis<T>(p, p->gm_cap + 2); }
 
+// Workgroups of the Gram-Schmidt launches (each of them sums all partials of the one before).
+int gs_grid(const fe_problem* p) { return (int)std::max<int64_t>(1, std::min<int64_t>((p->n_dof + GB - 1) / GB, GM_GRID)); }
+
 int node_grid(const fe_problem* p) {
   return (int)std::min<int64_t>((p->n_nodes + KB - 1) / KB, 4 * GM_GRID);
 }
 
 template <typename T>
-hipError_t gm_step_t(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s) {
+hipError_t gm_step_t(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s, int open_step) {
   const int64_t n = p->n_dof;
   const int* stop = &p->gm_dev->ctrl.status;
   const T* M = static_cast<const T*>(pc_buffer(p));
   switch (stage) {
-    case GM_BASIS:
+    case GM_BASIS:  // ||w|| and, after the cycle's first step, the rotations of step j - 1 if still open
       hipLaunchKernelGGL(gm_basis_kernel<T>, dim3(node_grid(p)), dim3(KB), 0, s, p->n_nodes, work_w<T>(p),
-                         basis<T>(p, j), work_z<T>(p), M, p->precond, p->gm_dev, stop);
+                         basis<T>(p, j), work_z<T>(p), M, p->precond, p->gm_part, j == 0 ? GM_GRID : gs_grid(p),
+                         p->gm_dev, j, open_step, stop);
       break;
-    case GM_ORTHO: {  // two classical Gram-Schmidt passes, then ||w||
-      for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL(gm_dots_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, basis<T>(p, 0), j + 1, work_w<T>(p),
-                           p->gm_part, stop);
-        hipLaunchKernelGGL(gm_reduce_kernel, dim3(j + 1), dim3(KB), 0, s, p->gm_part, GM_GRID, p->gm_dev, j, pass,
-                           stop);
-        hipLaunchKernelGGL(gm_update_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, basis<T>(p, 0), j + 1,
-                           work_w<T>(p), p->gm_dev, pass, pass == 1 ? 1 : 0, p->gm_part, stop);
-      }
-      hipLaunchKernelGGL(gm_givens_kernel, dim3(1), dim3(KB), 0, s, p->gm_part, GM_GRID, p->gm_dev, j, stop);
+    case GM_ORTHO: {  // two classical Gram-Schmidt passes, then ||w||^2
+      const int G = gs_grid(p);
+      double* part2 = p->gm_part + (int64_t)(GM_MAXM + 1) * GM_GRID;
+      const T* V = basis<T>(p, 0);
+      T* w = work_w<T>(p);
+      hipLaunchKernelGGL((gm_pass_kernel<T, 0>), dim3(G), dim3(GB), 0, s, n, V, j + 1, w, p->gm_dev, j,
+                         (const double*)nullptr, 0, p->gm_part, stop);
+      hipLaunchKernelGGL((gm_pass_kernel<T, 1>), dim3(G), dim3(GB), 0, s, n, V, j + 1, w, p->gm_dev, j,
+                         (const double*)p->gm_part, G, part2, stop);
+      hipLaunchKernelGGL((gm_pass_kernel<T, 2>), dim3(G), dim3(GB), 0, s, n, V, j + 1, w, p->gm_dev, j,
+                         (const double*)part2, G, p->gm_part, stop);
       break;
     }
+    case GM_GIVENS:  // closes step j where no basis launch follows at once
+      hipLaunchKernelGGL(gm_givens_kernel, dim3(1), dim3(KB), 0, s, p->gm_part, gs_grid(p), p->gm_dev, j, stop);
+      break;
     case GM_START:  // w holds the residual: ||w|| -> beta, g = beta e_1
       hipLaunchKernelGGL(gm_dots_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, work_w<T>(p), 1, work_w<T>(p),
                          p->gm_part, nullptr);
@@ -415,8 +527,8 @@ __global__ __launch_bounds__(KB) void ipcg_init_kernel(int64_t n, const T* b, T*
     r[d] = t;
     v += (double)t * (double)t;
   }
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  v = wave_sum_last(v);
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0;
@@ -506,8 +618,8 @@ __global__ __launch_bounds__(KB) void ipcg_update_kernel(int64_t n, const T* p, 
     r[d] = t;
     v += (double)t * (double)t;
   }
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  v = wave_sum_last(v);
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0;
@@ -589,8 +701,9 @@ hipError_t pc_apply(const fe_problem* p, const void* r, void* z, hipStream_t s) 
   return p->prec == FE_F64 ? pc_apply_t<double>(p, r, z, s) : pc_apply_t<float>(p, r, z, s);
 }
 
-hipError_t gm_step(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s) {
-  return p->prec == FE_F64 ? gm_step_t<double>(p, stage, j, b, x, s) : gm_step_t<float>(p, stage, j, b, x, s);
+hipError_t gm_step(const fe_problem* p, int stage, int j, const void* b, void* x, hipStream_t s, int open_step) {
+  return p->prec == FE_F64 ? gm_step_t<double>(p, stage, j, b, x, s, open_step)
+                           : gm_step_t<float>(p, stage, j, b, x, s, open_step);
 }
 
 void* gm_work_w(const fe_problem* p) {
