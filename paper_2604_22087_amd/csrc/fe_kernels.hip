@@ -2448,29 +2448,67 @@ hipError_t bicg_step(const fe_problem* p, int stage, void* x, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Path adjoint through the return map (FP64).  Forward-mode dual numbers give the
-// Jacobian of one Gauss point's update (eps, eps_p_n, alpha_n, s) -> (sigma, eps_p,
-// alpha) column by column, from the same j2_update the residual uses; the
-// cotangents are contracted with it.
+// Path adjoint through the return map (FP64): one reverse sweep through the update of a Gauss
+// point (eps, eps_p_n, alpha_n, s) -> (sigma, eps_p, alpha) gives the cotangents of all its inputs.
 
-struct Dual {
-  double v, d;
-  __device__ Dual(double x = 0.0, double y = 0.0) : v(x), d(y) {}
-  __device__ Dual& operator+=(Dual b) { v += b.v; d += b.d; return *this; }
-  __device__ Dual& operator-=(Dual b) { v -= b.v; d -= b.d; return *this; }
-};
-__device__ inline Dual operator+(Dual a, Dual b) { return Dual(a.v + b.v, a.d + b.d); }
-__device__ inline Dual operator-(Dual a, Dual b) { return Dual(a.v - b.v, a.d - b.d); }
-__device__ inline Dual operator-(Dual a) { return Dual(-a.v, -a.d); }
-__device__ inline Dual operator*(Dual a, Dual b) { return Dual(a.v * b.v, a.d * b.v + a.v * b.d); }
-__device__ inline Dual operator/(Dual a, Dual b) { return Dual(a.v / b.v, (a.d * b.v - a.v * b.d) / (b.v * b.v)); }
-__device__ inline Dual sqrt(Dual a) {
-  const double r = ::sqrt(a.v);
-  return Dual(r, r > 0.0 ? a.d / (2.0 * r) : 0.0);
+// Reverse of j2_update at one point.  Cotangents in: sb on the stress [xx,yy,zz,yz,xz,xy], mu on the
+// trial state.  Out: mb on the starting state, eh the history part (of mu alone) on the engineering
+// strain, and the return value on the modulus scale (K = s K0, G = s G0).
+__device__ __forceinline__ double j2_adjoint(const double H[3][3], const double hn[7], double K, double G, double K0,
+                                             double G0, double sy, double Hh, const double sb[6], const double mu[7],
+                                             double mb[7], double eh[6]) {
+  // forward, as j2_update forms it
+  const double e00 = H[0][0] - hn[0], e11 = H[1][1] - hn[1], e22 = H[2][2] - hn[2];
+  const double e12 = 0.5 * (H[1][2] + H[2][1] - hn[3]), e02 = 0.5 * (H[0][2] + H[2][0] - hn[4]),
+               e01 = 0.5 * (H[0][1] + H[1][0] - hn[5]);
+  const double tr = e00 + e11 + e22, m = tr / 3.0, g2 = 2 * G;
+  const double s[6] = {g2 * (e00 - m), g2 * (e11 - m), g2 * (e22 - m), g2 * e12, g2 * e02, g2 * e01};
+  const double sn = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]));
+  const double q = SQRT1_5 * sn;
+  const double f = q - (sy + Hh * hn[6]);
+  double db[6], hb[6] = {0, 0, 0, 0, 0, 0};  // cotangents of s: all, history part
+  double ab = mu[6], Gb = 0;
+  if (f > 0) {
+    const double i3 = 1.0 / (3 * G + Hh), dg = f * i3, iq = 1.0 / q, isn = 1.0 / sn, c = SQRT1_5 * dg;
+    const double theta = 1 - 3 * G * dg * iq;
+    double n[6], cb = 0, tb = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      n[k] = s[k] * isn;
+      cb += (k < 3 ? mu[k] : 2 * mu[k]) * n[k];  // eps_p += c n (engineering shears: 2 c n)
+      tb += sb[k] * s[k];                        // sigma = theta s + p
+    }
+    const double dh = mu[6] + SQRT1_5 * cb;      // cotangent of dgamma from the trial state
+    const double ds = -3 * G * iq * tb;          // and from the stress, through theta
+    const double fh = dh * i3, fs = ds * i3;
+    ab -= Hh * (fh + fs);
+    Gb = -3 * dg * iq * tb - 3 * dg * (fh + fs);
+    const double nh = SQRT1_5 * fh - c * cb * isn;                           // of |s|: history part,
+    const double ns = SQRT1_5 * (fs + 3 * G * dg * iq * iq * tb);            // stress part
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const double w = k < 3 ? 1.0 : 2.0;
+      hb[k] = c * (k < 3 ? mu[k] : 2 * mu[k]) * isn + nh * w * n[k];
+      db[k] = hb[k] + theta * sb[k] + ns * w * n[k];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) db[k] = sb[k];
+  }
+  const double pb = sb[0] + sb[1] + sb[2];
+  double sum = 0;  // s is 2 G times a strain: its cotangent times s / G
+#pragma unroll
+  for (int k = 0; k < 6; ++k) sum += db[k] * s[k];
+  const double td = K * pb - (g2 / 3.0) * (db[0] + db[1] + db[2]), th = -(g2 / 3.0) * (hb[0] + hb[1] + hb[2]);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    // engineering strain: eps of the normal components, half the tensor shear's cotangent
+    eh[k] = k < 3 ? g2 * hb[k] + th : G * hb[k];
+    mb[k] = mu[k] - (k < 3 ? g2 * db[k] + td : G * db[k]);
+  }
+  mb[6] = ab;
+  return (Gb + sum / G) * G0 + pb * tr * K0;
 }
-__device__ inline bool operator>(Dual a, Dual b) { return a.v > b.v; }
-__device__ inline bool operator<(Dual a, Dual b) { return a.v < b.v; }
-__device__ inline bool operator>=(Dual a, Dual b) { return a.v >= b.v; }
 
 struct PathArgs {
   int n;
@@ -2488,112 +2526,151 @@ struct PathArgs {
   double* s_bar;         // += cotangent of the modulus scale [n_el] or null
 };
 
-__global__ __launch_bounds__(256) void path_vjp_kernel(PathArgs a) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= a.n_el) return;
+// One backward step, on the element kernels' bricks and lane split: u and c are staged in LDS, each
+// lane takes four points, the history part of the strain cotangent is pushed to the nodes like a
+// stress.  Bound by its 23 words per point (150 MB at 48^3, the floor 32 us); differentiating the update
+// column by column with dual numbers instead cost 14 updates a point in 256 spilling registers, one
+// element per lane: 482 us at 48^3 against 53.
+__global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) void path_vjp_kernel(PathArgs a) {
+  __shared__ double s_u[NN * 3], s_c[NN * 3], s_y[NN * 3], s_park[18][EBLOCK];
+  __shared__ double s_mat[8 * FE_MAX_PHASES];
   const int n = a.n;
-  const int64_t ne = a.n_el, np1 = n + 1;
-  const int ea = (int)(e % n), eb = (int)((e / n) % n), ec = (int)(e / ((int64_t)n * n));
-  const double inv_h = 1.0 / a.h, w = 0.125 * a.h * a.h * a.h;
-  const PhaseConst pc = a.mat.ph[a.phase[e]];
-  const double sc = a.scale ? a.scale[e] : 1.0;
-  const bool j2 = pc.model == FE_J2;
-  double U[8][3], C[8][3], UB[8][3];
-  int64_t node[8];
+  const int ntx = (n + TX - 1) / TX, nty = (n + TY - 1) / TY, ntz = (n + TZ - 1) / TZ;
+  const int nb = ntx * nty * ntz, per = (nb + 7) >> 3;
+  const int tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (tile >= nb) return;  // padding block of the XCD-aware numbering
+  const Brick br(n, tile, ntx, nty);
+  stage_phases(a.mat, s_mat, threadIdx.x);
+  const int r = br.lane >> 5;
+  const int ex = br.lane & 15, ey = 2 * (br.wave & 1) + ((br.lane >> 4) & 1), ez = br.wave >> 1;
+  const int ga = br.a0 + ex, gb = br.b0 + ey, gc = br.c0 + ez;
+  const bool valid = ga < n && gb < n && gc < n;
+  const int64_t e = valid ? (ga + (int64_t)n * (gb + (int64_t)n * gc)) : 0;
+  const int64_t ne = a.n_el, e4 = e + 4 * r * ne;
+  const double w0 = r ? GB : GA, w1 = r ? GA : GB;
+  const int ph = valid ? (int)a.phase[e] : 0;
+  {
+    double vu[ROW_IT], vc[ROW_IT];
 #pragma unroll
-  for (int l = 0; l < 8; ++l) {
-    node[l] = (ea + (l & 1)) + np1 * ((eb + ((l >> 1) & 1)) + np1 * (ec + (l >> 2)));
+    for (int t = 0; t < ROW_IT; ++t) {
+      vu[t] = vc[t] = 0;
+      const Brick::Row rw = br.row(t);
+      if (!rw.live) continue;
+      vu[t] = a.u[rw.word + br.off];
+      if (a.c) vc[t] = a.c[rw.word + br.off];
+    }
+#pragma unroll
+    for (int t = 0; t < ROW_IT; ++t) {
+      const Brick::Row rw = br.row(t);
+      if (!rw.live || !br.inx) continue;
+      const int i = rw.row * ROWW + br.lane;
+      s_u[i] = vu[t];
+      s_c[i] = vc[t];
+      s_y[i] = 0;
+    }
+  }
+  __syncthreads();
+  const int s0 = 3 * (ex + NX * (ey + NY * ez));
+  if (valid) {
+    const PhaseConst pc = phase_const(s_mat, ph);
+    const double sc = a.scale ? a.scale[e] : 1.0;
+    const bool j2 = pc.model == FE_J2;
+    const double inv_h = 1.0 / a.h, w = 0.125 * a.h * a.h;  // (weight w detJ = h^3/8 times 1/h of the gradient)
+    HalfGrad<double> g, gc_, s;
+    half_gradients<double>([&](int kk, int jj, int ii, int c) { return s_u[s0 + 3 * (ii + NX * (jj + NY * kk)) + c]; }, w0, w1, g);
+    half_gradients<double>([&](int kk, int jj, int ii, int c) { return s_c[s0 + 3 * (ii + NX * (jj + NY * kk)) + c]; }, w0, w1, gc_);
+    double sbar = 0;
+    // the gradients of the points q = 1 wait in LDS (36 registers; 66 us at 48^3 with them held, 53 so)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      U[l][c] = a.u[3 * node[l] + c];
-      C[l][c] = a.c ? a.c[3 * node[l] + c] : 0.0;
-      UB[l][c] = 0.0;
+      s_park[c][threadIdx.x] = g.x[1][c];
+      s_park[3 + c][threadIdx.x] = g.z[1][0][c];
+      s_park[6 + c][threadIdx.x] = g.z[1][1][c];
+      s_park[9 + c][threadIdx.x] = gc_.x[1][c];
+      s_park[12 + c][threadIdx.x] = gc_.z[1][0][c];
+      s_park[15 + c][threadIdx.x] = gc_.z[1][1][c];
     }
-  }
-  double sbar = 0.0;
-  for (int qp = 0; qp < 8; ++qp) {
-    const int p = qp & 1, q = (qp >> 1) & 1, r = qp >> 2;
-    double g[8][3];
+    asm volatile("" ::: "memory");
 #pragma unroll
-    for (int l = 0; l < 8; ++l) basis_grad(l & 1, (l >> 1) & 1, l >> 2, p, q, r, inv_h, g[l]);
-    double H[3][3] = {}, Hc[3][3] = {};
+    for (int q = 0; q < 2; ++q) {
+      if (q == 1) {
 #pragma unroll
-    for (int l = 0; l < 8; ++l)
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-#pragma unroll
-        for (int J = 0; J < 3; ++J) {
-          H[c][J] += U[l][c] * g[l][J];
-          Hc[c][J] += C[l][c] * g[l][J];
+        for (int c = 0; c < 3; ++c) {
+          g.x[1][c] = s_park[c][threadIdx.x];
+          g.z[1][0][c] = s_park[3 + c][threadIdx.x];
+          g.z[1][1][c] = s_park[6 + c][threadIdx.x];
+          gc_.x[1][c] = s_park[9 + c][threadIdx.x];
+          gc_.z[1][0][c] = s_park[12 + c][threadIdx.x];
+          gc_.z[1][1][c] = s_park[15 + c][threadIdx.x];
         }
-    // stress cotangent: c . R = sum_q w (B_q c_e) . sigma_q (engineering-shear pairing)
-    const double sb[6] = {w * Hc[0][0], w * Hc[1][1], w * Hc[2][2], w * (Hc[1][2] + Hc[2][1]),
-                          w * (Hc[0][2] + Hc[2][0]), w * (Hc[0][1] + Hc[1][0])};
-    double mu[7], ebar[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 7; ++k) mu[k] = a.mu_in ? a.mu_in[(int64_t)(k * 8 + qp) * ne + e] : 0.0;
-    if (j2) {
-      double hn[7];
-#pragma unroll
-      for (int k = 0; k < 7; ++k) hn[k] = a.hist ? a.hist[(int64_t)(k * 8 + qp) * ne + e] : 0.0;
-      for (int col = 0; col < 14; ++col) {
-        Dual Hd[3][3], epd[6], ad, Kd(pc.K * sc), Gd(pc.G * sc);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) Hd[i][j] = Dual(H[i][j]);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) epd[k] = Dual(hn[k]);
-        ad = Dual(hn[6]);
-        if (col < 3) {
-          Hd[col][col].d = 1.0;
-        } else if (col < 6) {  // engineering shear strain: half to each off-diagonal entry
-          const int i = col == 3 ? 1 : 0, j = col == 5 ? 1 : 2;
-          Hd[i][j].d = 0.5;
-          Hd[j][i].d = 0.5;
-        } else if (col < 12) {
-          epd[col - 6].d = 1.0;
-        } else if (col == 12) {
-          ad.d = 1.0;
-        } else {
-          Kd.d = pc.K;
-          Gd.d = pc.G;
-        }
-        Dual S[3][3], ep[6], al, tn[6];
-        j2_update(Hd, epd, ad, Kd, Gd, Dual(pc.sy), Dual(pc.H), S, ep, al, tn);
-        const double hon = mu[0] * ep[0].d + mu[1] * ep[1].d + mu[2] * ep[2].d + mu[3] * ep[3].d +
-                           mu[4] * ep[4].d + mu[5] * ep[5].d + mu[6] * al.d;
-        const double tot = hon + sb[0] * S[0][0].d + sb[1] * S[1][1].d + sb[2] * S[2][2].d + sb[3] * S[1][2].d +
-                           sb[4] * S[0][2].d + sb[5] * S[0][1].d;
-        if (col < 6)
-          ebar[col] = hon;
-        else if (col < 13)
-          a.mu_out[(int64_t)((col - 6) * 8 + qp) * ne + e] = tot;
-        else
-          sbar += tot;
       }
-    } else {  // history-free phase: the state passes through; sigma = s D_hat eps
-      double S[3][3];
-      hooke(H, pc.lam, pc.mu, S);
-      sbar += sb[0] * S[0][0] + sb[1] * S[1][1] + sb[2] * S[2][2] + sb[3] * S[1][2] + sb[4] * S[0][2] +
-              sb[5] * S[0][1];
 #pragma unroll
-      for (int k = 0; k < 7; ++k) a.mu_out[(int64_t)(k * 8 + qp) * ne + e] = mu[k];
+      for (int p = 0; p < 2; ++p) {
+        const int64_t at = e4 + (p + 2 * q) * ne;
+        double mu[7], hn[7];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+          mu[k] = a.mu_in ? a.mu_in[at + k * 8 * ne] : 0.0;
+          hn[k] = j2 && a.hist ? a.hist[at + k * 8 * ne] : 0.0;
+        }
+        double H[3][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          H[c][0] = g.x[q][c] * inv_h;
+          H[c][1] = g.y[p][c] * inv_h;
+          H[c][2] = g.z[q][p][c] * inv_h;
+        }
+        // stress cotangent: c . R = sum_q w (B_q c_e) . sigma_q (engineering-shear pairing)
+        const double sb[6] = {w * gc_.x[q][0], w * gc_.y[p][1], w * gc_.z[q][p][2], w * (gc_.z[q][p][1] + gc_.y[p][2]),
+                              w * (gc_.z[q][p][0] + gc_.x[q][2]), w * (gc_.y[p][0] + gc_.x[q][1])};
+        double eh[6] = {0, 0, 0, 0, 0, 0};
+        if (j2) {
+          double mb[7];
+          sbar += j2_adjoint(H, hn, pc.K * sc, pc.G * sc, pc.K, pc.G, pc.sy, pc.H, sb, mu, mb, eh);
+#pragma unroll
+          for (int k = 0; k < 7; ++k) a.mu_out[at + k * 8 * ne] = mb[k];
+        } else {  // history-free phase: the state passes through; sigma = s D_hat eps
+          double S[3][3];
+          hooke(H, pc.lam, pc.mu, S);
+          sbar += sb[0] * S[0][0] + sb[1] * S[1][1] + sb[2] * S[2][2] + sb[3] * S[1][2] + sb[4] * S[0][2] + sb[5] * S[0][1];
+#pragma unroll
+          for (int k = 0; k < 7; ++k) a.mu_out[at + k * 8 * ne] = mu[k];
+        }
+        // d/dH of the engineering strain: symmetric, the shear cotangent in both entries
+        const double Hb[3][3] = {{eh[0], eh[5], eh[4]}, {eh[5], eh[1], eh[3]}, {eh[4], eh[3], eh[2]}};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          s.x[q][c] = p == 0 ? Hb[c][0] : s.x[q][c] + Hb[c][0];
+          s.y[p][c] = q == 0 ? Hb[c][1] : s.y[p][c] + Hb[c][1];
+          s.z[q][p][c] = Hb[c][2];
+        }
+      }
     }
-    if (a.u_bar && j2) {  // d/dH of the engineering strain: symmetric split of the shear entries
-      const double Hb[3][3] = {{ebar[0], ebar[5], ebar[4]}, {ebar[5], ebar[1], ebar[3]}, {ebar[4], ebar[3], ebar[2]}};
+    sbar += __shfl_xor(sbar, 32, 64);  // (both halves of an element are here or neither)
+    if (a.s_bar && r == 0) a.s_bar[e] += sbar;
+    if (a.u_bar) {
+      double F[2][2][3];
+      half_push_back(s, w0, w1, inv_h, F);
+      const int sr = s0 + 3 * NX * NY * r;
 #pragma unroll
-      for (int l = 0; l < 8; ++l)
+      for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) UB[l][c] += Hb[c][0] * g[l][0] + Hb[c][1] * g[l][1] + Hb[c][2] * g[l][2];
+        for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            __hip_atomic_fetch_add(&s_y[sr + 3 * (ii + NX * jj) + c], F[jj][ii][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   }
-  if (a.s_bar) a.s_bar[e] += sbar;
-  if (a.u_bar)
+  if (!a.u_bar) return;
+  __syncthreads();
 #pragma unroll
-    for (int l = 0; l < 8; ++l)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) atomic_add(a.u_bar + 3 * node[l] + c, UB[l][c]);
+  for (int t = 0; t < ROW_IT; ++t) {
+    const Brick::Row rw = br.row(t);
+    if (!rw.live || !br.inx) continue;
+    const double v = s_y[rw.row * ROWW + br.lane];
+    double* at = a.u_bar + rw.word + br.off;
+    atomic_add(at, v);
+  }
 }
 
 hipError_t launch_path_vjp(const fe_problem* p, const void* u, const void* hist, const void* c, const void* mu_in,
@@ -2612,7 +2689,7 @@ hipError_t launch_path_vjp(const fe_problem* p, const void* u, const void* hist,
   a.mu_out = static_cast<double*>(mu_out);
   a.u_bar = static_cast<double*>(u_bar);
   a.s_bar = static_cast<double*>(s_bar);
-  hipLaunchKernelGGL(path_vjp_kernel, dim3((unsigned)((p->n_el + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(path_vjp_kernel, dim3(elem_grid(p->n)), dim3(EBLOCK), 0, s, a);
   return hipGetLastError();
 }
 
