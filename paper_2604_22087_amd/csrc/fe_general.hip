@@ -1057,11 +1057,12 @@ __global__ __launch_bounds__(64) void sym_pairs_kernel(int64_t n_nodes, const in
     }
     for (int j0 = 0; j0 < len; j0 += 64) {
       const int j = j0 + l;
-      // entries of the row's own column: the elements around the node, in element order
-      const bool self = j < len && col[b + j] == (int32_t)r;
+      // entries of the row's own column with equal local nodes: the incidences of the node, in
+      // element order (an element that repeats a node, a collapsed brick, also pairs its copies)
+      const int32_t cd = j < len ? code[b + j] : 0;  // element * 64 + local row node * 8 + local column node
+      const bool self = j < len && col[b + j] == (int32_t)r && (cd >> 3 & 7) == (cd & 7);
       const unsigned long long ms = __ballot(self);
       if (self) {
-        const int32_t cd = code[b + j];  // element * 64 + local row node * 8 + local column node
         inc[ii + __popcll(ms & ((1ull << l) - 1ull))] = (cd >> 6) * 8 + (cd & 7);
       }
       ii += __popcll(ms);
