@@ -582,7 +582,7 @@ int fe_csr_indices(fe_problem* p, int32_t* row_ptr, int32_t* col_idx, void* stre
   return FE_OK;
 }
 
-// General meshes keep every element's dense Jacobian between the matrix-core kernel and the
+// General meshes keep every element's Jacobian between the element kernel and the
 // sorted gather into the CSR values: n_el x 576 reals, allocated on the first tangent.
 static int ensure_ke(fe_problem* p) {
   if (!p->general || p->ke) return FE_OK;

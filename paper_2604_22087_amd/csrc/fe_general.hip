@@ -17,12 +17,10 @@
 //   code), so the whole list is ordered by the int64 key (row, column); runs of equal keys
 //   are the duplicates, their first positions give the node-pair pattern, and the sorted
 //   element codes of each run say which element blocks sum into that pair;
-//   numeric (per tangent): each element's dense 24 x 24 Jacobian K_e = sum_q B_q^T D_q B_q
-//   w detJ is one batched contraction on the FP64 / FP32 matrix cores (v_mfma_*_16x16x4),
-//   written to a per-element buffer; a gather then sums every pair's run in sorted order
-//   into the CSR values (deterministic: the same bits on every run).
-#include <type_traits>
-
+//   numeric (per tangent): the 36 node-pair blocks of each element's symmetric Jacobian
+//   K_e = sum_q B_q^T D_q B_q w detJ are written to a per-element buffer; a gather then sums
+//   every pair's run in sorted order into the CSR values (deterministic: the same bits on
+//   every run).
 #include "fe_internal.hpp"
 #include "fe_device.hpp"
 
@@ -38,24 +36,23 @@ __device__ __forceinline__ int ref_sy(int a) { return (a & 2) ? 1 : -1; }
 __device__ __forceinline__ int ref_sz(int a) { return (a & 4) ? 1 : -1; }
 
 // dN_a / dxi_k of the trilinear basis at Gauss point q = qx + 2 qy + 4 qz (xi = +-1/sqrt 3).
-template <typename T> __device__ __forceinline__ void ref_grad(int q, T dn[8][3]) {
+template <typename T> __device__ __forceinline__ void node_ref_grad(int a, int q, T dn[3]) {
   const T g = T(GAUSS);
   const T xi = (q & 1) ? g : -g, eta = (q & 2) ? g : -g, zeta = (q & 4) ? g : -g;
+  const T sx = T(ref_sx(a)), sy = T(ref_sy(a)), sz = T(ref_sz(a));
+  const T fx = 1 + sx * xi, fy = 1 + sy * eta, fz = 1 + sz * zeta;
+  dn[0] = T(0.125) * sx * fy * fz;
+  dn[1] = T(0.125) * fx * sy * fz;
+  dn[2] = T(0.125) * fx * fy * sz;
+}
+template <typename T> __device__ __forceinline__ void ref_grad(int q, T dn[8][3]) {
 #pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    const T sx = T(ref_sx(a)), sy = T(ref_sy(a)), sz = T(ref_sz(a));
-    const T fx = 1 + sx * xi, fy = 1 + sy * eta, fz = 1 + sz * zeta;
-    dn[a][0] = T(0.125) * sx * fy * fz;
-    dn[a][1] = T(0.125) * fx * sy * fz;
-    dn[a][2] = T(0.125) * fx * fy * sz;
-  }
+  for (int a = 0; a < 8; ++a) node_ref_grad<T>(a, q, dn[a]);
 }
 
-// Physical basis gradients g[a][j] = dN_a/dx_j at Gauss point q of the element with nodal
-// positions xe[a][i]; returns det J (J_ik = dx_i/dxi_k).
-template <typename T> __device__ __forceinline__ T phys_grad(const T (*xe)[3], int q, T g[8][3]) {
-  T dn[8][3];
-  ref_grad<T>(q, dn);
+// Inverse of the isoparametric Jacobian J_ik = dx_i/dxi_k of the element with nodal positions
+// xe[a][i] and reference gradients dn; returns det J.
+template <typename T> __device__ __forceinline__ T jacobian_inverse(const T (*xe)[3], const T dn[8][3], T Ji[3][3]) {
   T J[3][3];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -71,7 +68,6 @@ template <typename T> __device__ __forceinline__ T phys_grad(const T (*xe)[3], i
   const T det = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
   const T id = T(1) / det;
   // (J^-1)_kj = cof(J)_jk / det
-  T Ji[3][3];
   Ji[0][0] = c00 * id;
   Ji[1][0] = c01 * id;
   Ji[2][0] = c02 * id;
@@ -81,6 +77,14 @@ template <typename T> __device__ __forceinline__ T phys_grad(const T (*xe)[3], i
   Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
   Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
   Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
+  return det;
+}
+
+// Physical basis gradients g[a][j] = dN_a/dx_j at Gauss point q; returns det J.
+template <typename T> __device__ __forceinline__ T phys_grad(const T (*xe)[3], int q, T g[8][3]) {
+  T dn[8][3], Ji[3][3];
+  ref_grad<T>(q, dn);
+  const T det = jacobian_inverse<T>(xe, dn, Ji);
 #pragma unroll
   for (int a = 0; a < 8; ++a)
 #pragma unroll
@@ -686,232 +690,246 @@ template <typename T> __global__ void gen_mask_one_kernel(int64_t n, const uint8
 }
 
 // ---------------------------------------------------------------------------
-// element Jacobians on the matrix cores
+// element Jacobians
 //
-// K_e = G^T (D G) with the Gauss points stacked along the contraction: for small strain
-// G = [B_0; ...; B_7] (48 x 24, the Voigt strain-displacement rows) and D = blockdiag(w detJ
-// D_q) (6 x 6 blocks); for finite strain G stacks the 9 x 24 gradient operators
-// (row (i, J) of node b's column (b, k) is delta_ik dN_b/dX_J) and D holds w detJ times the
-// 9 x 9 tangent moduli A_iJkL.  The 24 x 24 result is padded to 32 x 32 = 2 x 2 tiles of the
-// 16 x 16 x 4 MFMA; K_e is symmetric, so the lower-left tile is the transpose of the upper-right
-// one and only three tiles are computed.  Lane layout (16 x 16 x 4, both precisions): lane l
-// holds A[l % 16][l / 16] and B[l / 16][l % 16]; result entry r of lane l sits in column l % 16
-// and row 4 (l / 16) + r for FP32, row l / 16 + 4 r for FP64 (measured on gfx950).
-// One wave per workgroup, one element at a time; the element's basis gradients and scaled
-// moduli are staged in LDS by its 64 lanes (lane = 8 * point + node).
-// Output: ke[e][a][b][i][k] = K_e[(a, i), (b, k)] (a 3 x 3 block per node pair, 576 reals).
+// The 3 x 3 block of nodes a, b is, summed over the Gauss points with their weights w detJ,
+//   small strain  lp g_a g_b^T + mp g_b g_a^T + mp (g_a . g_b) I - beta (N g_a)(N g_b)^T
+//   Neo-Hookean   lam h_a h_b^T + (mu - lam ln J) h_b h_a^T + mu (g_a . g_b) I,  h = F^-T g
+// with the physical basis gradients g: 33 multiply-adds per point and pair, which needs neither
+// the 6 x 6 (9 x 9) moduli nor the padding of a 24 x 24 matrix to matrix-core tiles.  K_e is
+// symmetric, so only the 36 pairs a <= b are formed and kept.
+// A workgroup takes TEL elements: one lane per (element, point) forms the gradients into LDS, then
+// one lane per (element, 2 x 2 tile of nodes) sums its four blocks, and the blocks leave through LDS
+// in whole lines.  Output: ke[e][a][b][i][k] = K_e[(a, i), (b, k)] (576 reals).
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f_t __attribute__((ext_vector_type(4)));
+constexpr int TEL = 16;                // elements per workgroup
+constexpr int TPAIR = 36;              // node pairs a <= b of an element
+constexpr int TBLOCK = 10 * TEL;       // tiles (0,0) (0,1) .. (3,3) of node pairs 2A, 2A + 1
+constexpr int TGS = 25;                // reals per (point, element) row of 8 gradients (odd: no bank conflicts)
+constexpr int TOS = 9 * TPAIR + 1;     // reals per element of the blocks on their way out
 
-__device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ v4f_t mfma16(float a, float b, v4f_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-template <typename T> struct Acc4;
-template <> struct Acc4<double> { typedef v4d type; };
-template <> struct Acc4<float> { typedef v4f_t type; };
+// Pair of local nodes a <= b.
+__device__ __forceinline__ int pair_index(int a, int b) { return a * (15 - a) / 2 + b; }
 
-// Calls f(std::integral_constant<int, i>) for i = 0 .. N-1 (compile-time loop index).
-template <int I, int N, typename F> __device__ __forceinline__ void static_for_impl(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for_impl<I + 1, N>(f);
-  }
-}
-template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) { static_for_impl<0, N>(f); }
-
-// Row of result entry r of lane l (16 x 16 x 4 MFMA).
-template <typename T> __device__ __forceinline__ int mfma_row(int l, int r);
-template <> __device__ __forceinline__ int mfma_row<double>(int l, int r) { return (l >> 4) + 4 * r; }
-template <> __device__ __forceinline__ int mfma_row<float>(int l, int r) { return 4 * (l >> 4) + r; }
-
-// Entry (m, (b, k)) of the stacked gradient operator at one point: Voigt rows
-// [xx yy zz yz xz xy] (DIM 6) or gradient rows (i, J) = 3 i + J (DIM 9).  m is a compile-time
-// row of the unrolled contraction loop and k the lane's component, so this is a pair of selects.
-template <typename T, int DIM, int M> __device__ __forceinline__ T g_entry(int k, const T* gb) {
-  if (DIM == 9) return k == M / 3 ? gb[M % 3] : T(0);
-  if (M < 3) return k == M ? gb[M] : T(0);
-  constexpr int ka = M == 3 ? 1 : 0, da = M == 3 ? 2 : (M == 4 ? 2 : 1);   // shear rows: two components
-  constexpr int kb = M == 5 ? 1 : 2, db = M == 3 ? 1 : 0;
-  return k == ka ? gb[da] : (k == kb ? gb[db] : T(0));
-}
-
-// Rows of B's column (b, k) that are non-zero (Voigt): row k (d/dx_k) and two shear rows n1, n2
-// with the derivative directions g1, g2 -- per lane constants.
-struct VoigtCol {
-  int n1, g1, n2, g2;
-};
-__device__ __forceinline__ VoigtCol voigt_col(int k) {
-  VoigtCol c;
-  c.n1 = k == 0 ? 4 : 3;
-  c.g1 = k == 2 ? 1 : 2;
-  c.n2 = k == 2 ? 4 : 5;
-  c.g2 = k == 0 ? 1 : 0;
-  return c;
-}
-
-// (D G)[m][(b, k)] at one point.
-template <typename T, int DIM, int M>
-__device__ __forceinline__ T dg_entry(const T* D, int k, const VoigtCol& vc, const T* gb) {
-  const T* Dm = D + M * DIM;
-  if (DIM == 9) return Dm[3 * k] * gb[0] + Dm[3 * k + 1] * gb[1] + Dm[3 * k + 2] * gb[2];
-  return Dm[k] * gb[k] + Dm[vc.n1] * gb[vc.g1] + Dm[vc.n2] * gb[vc.g2];
-}
-
+// Bound by the 576 reals per element written (233 MB at 37^3 FP64, 49 us at the copy rate) and its own
+// three phases, which four workgroups per CU overlap: 73 us there against 197 us for one wave per
+// element on matrix cores (padded tiles, 36 or 81 LDS words of moduli per point).  A lane per pair read
+// twice the LDS words (102 us while writing half as much); 32 elements per workgroup left two of
+// them per CU (119 us).
 template <typename T, int MS>
-__global__ __launch_bounds__(64) void gen_tangent_kernel(GenArgs g, TanArgs ta, T* ke) {
-  constexpr int DIM = MS == MS_NH ? 9 : 6;
-  typedef typename Acc4<T>::type acc_t;
-  __shared__ T s_xe[8][3];
-  __shared__ T s_g[8][8][3];          // [point][node][direction]
-  __shared__ T s_D[8][DIM * DIM];     // w detJ times the tangent moduli of each point
-  const int l = threadIdx.x;
-  const int pq = l >> 3, pa = l & 7;  // staging role: point, node
-  const int64_t ne = ta.n_el;
-  for (int64_t e = blockIdx.x; e < ne; e += gridDim.x) {
-    if (l < 24) {
-      const int a = l / 3, i = l % 3;
-      const int node = g.conn[(int64_t)a * ne + e];
-      s_xe[a][i] = static_cast<const T*>(g.coords)[3 * (int64_t)node + i];
+__global__ __launch_bounds__(TBLOCK) __attribute__((amdgpu_waves_per_eu(3))) void gen_tangent_kernel(GenArgs g, TanArgs ta,
+                                                                                                     T* __restrict__ ke) {
+  constexpr int NG = 8 * TEL * TGS;
+  // per point: c1, c2 [, -beta, N] or [, mu, F^-T]
+  constexpr int NCF = MS == MS_LINEAR ? 2 : (MS == MS_J2 ? 9 : 12);
+  __shared__ T s_g[NG];                            // gradients, later the blocks
+  __shared__ T s_cf[NCF][8 * TEL];
+  __shared__ T s_xe[TEL][8][3];
+  static_assert(NG >= TEL / 2 * TOS, "the blocks of half the elements fit");
+  const int tid = threadIdx.x, el = tid % TEL;
+  const int64_t ne = ta.n_el, e0 = (int64_t)blockIdx.x * TEL;
+  const int64_t e = e0 + el < ne ? e0 + el : ne - 1;
+  if (tid < 8 * TEL) {
+    const int q = tid / TEL;
+    const int node = g.conn[(int64_t)q * ne + e];
+    const T* C = static_cast<const T*>(g.coords) + 3 * (int64_t)node;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s_xe[el][q][c] = C[c];
+  }
+  __syncthreads();
+  if (tid < 8 * TEL) {
+    const int q = tid / TEL;
+    QpTangent<T> t;
+    load_qp_tangent<T, MS>(ta, e, q, t);
+    T gr[8][3];
+    const T w = phys_grad<T>(s_xe[el], q, gr);
+    if (MS == MS_NH && t.kind == 1) {
+      s_cf[0][tid] = w * t.lam;
+      s_cf[1][tid] = w * (t.mu - t.lam * t.lnJ);
+      s_cf[2 % NCF][tid] = w * t.mu;
+    } else {
+      s_cf[0][tid] = w * t.lp;
+      s_cf[1][tid] = w * t.mp;
+      if (MS != MS_LINEAR) s_cf[2 % NCF][tid] = MS == MS_NH ? w * t.mp : -w * t.beta;
+    }
+    if (MS == MS_J2)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) s_cf[(3 + k) % NCF][tid] = t.N[k];
+    if (MS == MS_NH)
+#pragma unroll
+      for (int k = 0; k < 9; ++k)
+        s_cf[(3 + k) % NCF][tid] = t.kind == 1 ? t.FiT[k / 3][k % 3] : T(k % 4 == 0 ? 1 : 0);
+    T* sg = s_g + tid * TGS;
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) sg[3 * a + i] = gr[a][i];
+  }
+  __syncthreads();
+  const int tile = tid / TEL;
+  const int ta0 = (tile >= 4) + (tile >= 7) + (tile >= 9), tb0 = tile - ta0 * (7 - ta0) / 2;  // tile (A, B)
+  T K[2][2][3][3];
+#pragma unroll
+  for (int m = 0; m < 36; ++m) K[m / 18][m / 9 % 2][m / 3 % 3][m % 3] = 0;
+#pragma unroll 1
+  for (int q = 0; q < 8; ++q) {
+    const int pt = q * TEL + el;
+    const T* ga = s_g + pt * TGS + 6 * ta0;
+    const T* gb = s_g + pt * TGS + 6 * tb0;
+    T va[2][3], vb[2][3], wa[2][3], wb[2][3];  // w: N g (J2) or h = F^-T g (Neo-Hookean)
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      va[m / 3][m % 3] = ga[m];
+      vb[m / 3][m % 3] = gb[m];
+    }
+    const T c1 = s_cf[0][pt], c2 = s_cf[1][pt], c3 = s_cf[2 % NCF][pt];
+    if (MS != MS_LINEAR) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        T M[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          // Voigt [xx yy zz yz xz xy] of N, or row i of F^-T
+          const int at = MS == MS_NH ? 3 * i + k : (i == k ? i : 6 - i - k);
+          M[k] = s_cf[(3 + at) % NCF][pt];
+        }
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          wa[n][i] = M[0] * va[n][0] + M[1] * va[n][1] + M[2] * va[n][2];
+          wb[n][i] = M[0] * vb[n][0] + M[1] * vb[n][1] + M[2] * vb[n][2];
+        }
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      T x1[3], x2[3], x3[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const T p = MS == MS_NH ? wa[n][i] : va[n][i];
+        x1[i] = c1 * p;
+        x2[i] = c2 * p;
+        if (MS == MS_J2) x3[i] = c3 * wa[n][i];
+        if (MS == MS_NH) x3[i] = c3 * va[n][i];
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const T* pb = MS == MS_NH ? wb[m] : vb[m];
+        const T dot = MS == MS_NH ? x3[0] * vb[m][0] + x3[1] * vb[m][1] + x3[2] * vb[m][2]
+                                  : x2[0] * vb[m][0] + x2[1] * vb[m][1] + x2[2] * vb[m][2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            T v = K[n][m][i][k] + x1[i] * pb[k];
+            v += x2[k] * pb[i];
+            if (MS == MS_J2) v += x3[i] * wb[m][k];
+            if (i == k) v += dot;
+            K[n][m][i][k] = v;
+          }
+      }
+    }
+  }
+  // half the elements at a time; TOUT lanes then hold 576 / TOUT entries of every K_e
+  constexpr int TOUT = 9 * TEL, TENT = 576 / TOUT;
+  int from[TENT];
+#pragma unroll
+  for (int u = 0; u < TENT; ++u) {
+    const int entry = tid + TOUT * u, a = entry / 72, b = entry / 9 % 8, m = entry % 9;
+    from[u] = 9 * (a <= b ? pair_index(a, b) : pair_index(b, a)) + (a <= b ? m : 3 * (m % 3) + m / 3);
+  }
+#pragma unroll 1
+  for (int half = 0; half < 2; ++half) {
+    __syncthreads();  // s_g is read no more
+    if (el / (TEL / 2) == half) {
+      T* so = s_g + (el % (TEL / 2)) * TOS;
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          if (n > m && ta0 == tb0) continue;  // (1, 0) of a diagonal tile
+          T* sb = so + 9 * pair_index(2 * ta0 + n, 2 * tb0 + m);
+#pragma unroll
+          for (int k = 0; k < 9; ++k) sb[k] = K[n][m][k / 3][k % 3];
+        }
     }
     __syncthreads();
-    {
-      T gr[8][3];
-      const T wdet = phys_grad<T>(s_xe, pq, gr);
+    if (tid < TOUT) {
+      const int64_t eh = e0 + half * (TEL / 2);
+      T* out = ke + eh * 576 + tid;
+#pragma unroll 4
+      for (int k = 0; k < TEL / 2; ++k)
+        if (eh + k < ne)
 #pragma unroll
-      for (int a = 0; a < 8; ++a)  // (compile-time register index; lane pa keeps node pa)
-        if (a == pa)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) s_g[pq][a][j] = gr[a][j];
-      QpTangent<T> t;
-      load_qp_tangent<T, MS>(ta, e, pq, t);
-      // every lane forms all entries of its point's moduli with compile-time indices (no
-      // dynamic indexing of the per-point data) and stores every 8th one
-      if (DIM == 6) {
-        // D = lp 1 x 1 + 2 mp I_sym - beta N x N, engineering shear strains, tensor stress
-#pragma unroll
-        for (int m = 0; m < 36; ++m) {
-          const int r = m / 6, c = m % 6;
-          const T v = (r < 3 && c < 3 ? t.lp : T(0)) + (r == c ? (r < 3 ? 2 * t.mp : t.mp) : T(0)) -
-                      t.beta * t.N[r] * t.N[c];
-          if ((m & 7) == pa) s_D[pq][m] = wdet * v;
-        }
-      } else if (t.kind == 1) {
-        // A_iJkL = mu d_ik d_JL + (mu - lam ln J) F^-1_Jk F^-1_Li + lam F^-1_Ji F^-1_Lk, F^-1_Jk = FiT[k][J]
-        const T cc = t.mu - t.lam * t.lnJ;
-#pragma unroll
-        for (int m = 0; m < 81; ++m) {
-          const int r = m / 9, c = m % 9;
-          const int i = r / 3, J = r % 3, k = c / 3, L = c % 3;
-          const T v = (i == k && J == L ? t.mu : T(0)) + cc * t.FiT[k][J] * t.FiT[i][L] +
-                      t.lam * t.FiT[i][J] * t.FiT[k][L];
-          if ((m & 7) == pa) s_D[pq][m] = wdet * v;
-        }
-      } else {
-        // small-strain phase of a finite-strain problem, in gradient form:
-        // A_iJkL = lp d_iJ d_kL + mp (d_ik d_JL + d_iL d_Jk) - beta N_iJ N_kL
-        const T Nt[3][3] = {{t.N[0], t.N[5], t.N[4]}, {t.N[5], t.N[1], t.N[3]}, {t.N[4], t.N[3], t.N[2]}};
-#pragma unroll
-        for (int m = 0; m < 81; ++m) {
-          const int r = m / 9, c = m % 9;
-          const int i = r / 3, J = r % 3, k = c / 3, L = c % 3;
-          const T v = (i == J && k == L ? t.lp : T(0)) +
-                      t.mp * ((i == k && J == L ? T(1) : T(0)) + (i == L && J == k ? T(1) : T(0))) -
-                      t.beta * Nt[i][J] * Nt[k][L];
-          if ((m & 7) == pa) s_D[pq][m] = wdet * v;
-        }
-      }
+          for (int u = 0; u < TENT; ++u) out[576 * k + TOUT * u] = s_g[k * TOS + from[u]];
     }
-    __syncthreads();
-    acc_t c00 = {0, 0, 0, 0}, c01 = {0, 0, 0, 0}, c11 = {0, 0, 0, 0};
-    const int r16 = l & 15;
-    const int ra = r16 / 3, ri = r16 % 3;                 // tile 0 row / column (node, component)
-    const int rb = (16 + r16) / 3, rk = (16 + r16) % 3;   // tile 1 (valid for r16 < 8)
-    const bool t1 = r16 < 8;
-    const VoigtCol va = voigt_col(ri), vb = voigt_col(rk);
-    // contraction index ordered row-major over (m, point): k-step s covers row m = s / 2 of the
-    // points 4 (s % 2) + l / 16, so m is the same on every lane of a step (compile time)
-    auto step = [&](auto mc, int half) {
-      constexpr int M = decltype(mc)::value;
-      const int qp = 4 * half + (l >> 4);
-      const T* Dq = s_D[qp];
-      const T a0 = g_entry<T, DIM, M>(ri, s_g[qp][ra]);
-      const T a1 = t1 ? g_entry<T, DIM, M>(rk, s_g[qp][rb]) : T(0);
-      const T b0 = dg_entry<T, DIM, M>(Dq, ri, va, s_g[qp][ra]);
-      const T b1 = t1 ? dg_entry<T, DIM, M>(Dq, rk, vb, s_g[qp][rb]) : T(0);
-      c00 = mfma16(a0, b0, c00);
-      c01 = mfma16(a0, b1, c01);
-      c11 = mfma16(a1, b1, c11);
-    };
-    static_for<DIM>([&](auto mc) {
-      step(mc, 0);
-      step(mc, 1);
-    });
-    T* K = ke + e * 576;
-    const int col = l & 15;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = mfma_row<T>(l, r);
-      // tile (0,0): rows / columns 0..15
-      {
-        const int ar = row / 3, ir = row % 3, bc = col / 3, kc = col % 3;
-        K[(ar * 8 + bc) * 9 + ir * 3 + kc] = c00[r];
-      }
-      // tile (0,1): rows 0..15, columns 16..23, and its mirror
-      if (col < 8) {
-        const int ar = row / 3, ir = row % 3, bc = (16 + col) / 3, kc = (16 + col) % 3;
-        K[(ar * 8 + bc) * 9 + ir * 3 + kc] = c01[r];
-        K[(bc * 8 + ar) * 9 + kc * 3 + ir] = c01[r];
-      }
-      // tile (1,1): rows / columns 16..23
-      if (row < 8 && col < 8) {
-        const int ar = (16 + row) / 3, ir = (16 + row) % 3, bc = (16 + col) / 3, kc = (16 + col) % 3;
-        K[(ar * 8 + bc) * 9 + ir * 3 + kc] = c11[r];
-      }
-    }
-    __syncthreads();  // LDS reused by the next element
   }
 }
 
-// CSR values: one lane per node pair, its run of element blocks summed in sorted order.
-// Row (a, i) of the pair (a, b) at position k of a's row: value index 9 ptr[a] + 3 i deg(a) + 3 k + c.
+// CSR values: one wave per row node.  The rows of the element Jacobians around the node (72 reals
+// each, contiguous) are staged in LDS, then every lane sums the run of its entry in sorted order:
+// entries of the row are numbered as they lie in vals (3 x 3 deg(a), then k, c), so both the reads and
+// the stores are whole lines.  A node of more than ASM_INC elements reads its runs from memory.
+// Bound by the Jacobians read and the values written (233 + 107 MB at 37^3 FP64, 72 us at the copy rate):
+// 110 us against 158 us with a lane per node pair, whose nine loads and stores each touched 64 lines.
+constexpr int ASM_INC = 8;           // elements around a node of a regular mesh
+constexpr int ASM_WAVES = VBLOCK / 64;
 template <typename T>
-__global__ __launch_bounds__(VBLOCK) void gen_assemble_kernel(int64_t n_pairs, const int32_t* __restrict__ adj_ptr,
+__global__ __launch_bounds__(VBLOCK) void gen_assemble_kernel(int64_t n_nodes, const int32_t* __restrict__ adj_ptr,
                                                               const int32_t* __restrict__ adj,
-                                                              const int32_t* __restrict__ pair_row,
                                                               const int32_t* __restrict__ src_ptr,
                                                               const int32_t* __restrict__ src,
+                                                              const int32_t* __restrict__ inc_ptr,
+                                                              const int32_t* __restrict__ inc,
                                                               const T* __restrict__ ke, const uint8_t* mask,
                                                               int apply_bc, T* __restrict__ vals) {
-  for (int64_t p = (int64_t)blockIdx.x * VBLOCK + threadIdx.x; p < n_pairs; p += (int64_t)gridDim.x * VBLOCK) {
-    T acc[9];
+  __shared__ T s_row[ASM_WAVES][72 * ASM_INC];
+  __shared__ int s_src[ASM_WAVES][8 * ASM_INC];
+  __shared__ int s_ptr[ASM_WAVES][8 * ASM_INC + 1];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t a = (int64_t)blockIdx.x * ASM_WAVES + wave;
+  int i0 = 0, ni = 0, base = 0, deg = 0;
+  if (a < n_nodes) {
+    i0 = inc_ptr[a];
+    ni = inc_ptr[a + 1] - i0;
+    base = adj_ptr[a];
+    deg = adj_ptr[a + 1] - base;
+  }
+  const bool staged = ni <= ASM_INC;
+  if (staged) {
+    const int row = lane < ni ? inc[i0 + lane] : 0;  // 8 element + local node: 72 reals from row * 72
+    if (lane < 8 * ni) s_src[wave][lane] = src[8 * (int64_t)i0 + lane];
+    if (lane < deg) s_ptr[wave][lane] = src_ptr[base + lane] - 8 * i0;
+    if (lane == 0) s_ptr[wave][deg] = 8 * ni;
+    T v[9];
 #pragma unroll
-    for (int j = 0; j < 9; ++j) acc[j] = 0;
-    const int s0 = src_ptr[p], s1 = src_ptr[p + 1];
-    for (int s = s0; s < s1; ++s) {
-      const int code = src[s];  // element * 64 + local row node * 8 + local column node
-      const T* blk = ke + (int64_t)(code >> 6) * 576 + (code & 63) * 9;
-#pragma unroll
-      for (int j = 0; j < 9; ++j) acc[j] += blk[j];
+    for (int t = 0; t < 9; ++t) {
+      const int w = lane + 64 * t, k = w / 72;
+      const int from = __shfl(row, k, 64);
+      v[t] = w < 72 * ni ? ke[(int64_t)from * 72 + (w - 72 * k)] : T(0);
     }
-    const int a = pair_row[p], b = adj[p];
-    const int base = adj_ptr[a], deg = adj_ptr[a + 1] - base;
-    const int64_t k = p - base;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int64_t rdof = 3 * (int64_t)a + i;
-      const int64_t pos = 9 * (int64_t)base + 3 * (int64_t)i * deg + 3 * k;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int64_t cdof = 3 * (int64_t)b + c;
-        T v = acc[3 * i + c];
-        if (apply_bc && mask && (mask[rdof] || mask[cdof])) v = (rdof == cdof) ? T(1) : T(0);
-        vals[pos + c] = v;
+    for (int t = 0; t < 9; ++t) s_row[wave][lane + 64 * t] = v[t];
+  }
+  __syncthreads();
+  const bool bc = apply_bc && mask;
+  for (int o = lane; o < 9 * deg; o += 64) {
+    const int i = (o >= 3 * deg) + (o >= 6 * deg), rem = o - 3 * deg * i, k = rem / 3, c = rem - 3 * k, j = 3 * i + c;
+    T acc = 0;
+    if (staged) {
+      const int s1 = s_ptr[wave][k + 1];
+      for (int s = s_ptr[wave][k]; s < s1; ++s) acc += s_row[wave][9 * s_src[wave][s] + j];
+    } else {
+      const int s1 = src_ptr[base + k + 1];
+      for (int s = src_ptr[base + k]; s < s1; ++s) {
+        const int code = src[s];  // 8 incidence + local column node
+        acc += ke[(int64_t)inc[i0 + (code >> 3)] * 72 + 9 * (code & 7) + j];
       }
     }
+    if (bc) {
+      const int64_t rdof = 3 * a + i, cdof = 3 * (int64_t)adj[base + k] + c;
+      if (mask[rdof] || mask[cdof]) acc = rdof == cdof ? T(1) : T(0);
+    }
+    vals[9 * (int64_t)base + o] = acc;
   }
 }
 
@@ -1042,11 +1060,13 @@ __global__ __launch_bounds__(64) void sym_row_sort_kernel(int64_t n_nodes, const
 
 // Pair arrays from the sorted buckets: for each run head at sorted position j of row r, its pair
 // index is adj_ptr[r] + (heads before j); it records the column node, the row node and where
-// its run starts in the sorted code list.
+// its run starts in the sorted code list.  The codes then become 8 incidence + local column node, the
+// incidence counted among those of the row (at most 128).
 __global__ __launch_bounds__(64) void sym_pairs_kernel(int64_t n_nodes, const int32_t* ptr, const int32_t* col,
-                                                       const int32_t* code, const int32_t* adj_ptr, int32_t* adj,
+                                                       int32_t* code, const int32_t* adj_ptr, int32_t* adj,
                                                        int32_t* pair_row, int32_t* src_ptr, int32_t* inc_ptr,
                                                        int32_t* inc) {
+  __shared__ int s_inc[SYM_MAXROW / 8];
   const int l = threadIdx.x;
   for (int64_t r = blockIdx.x; r < n_nodes; r += gridDim.x) {
     const int b = ptr[r], len = ptr[r + 1] - b;
@@ -1063,7 +1083,8 @@ __global__ __launch_bounds__(64) void sym_pairs_kernel(int64_t n_nodes, const in
       const bool self = j < len && col[b + j] == (int32_t)r && (cd >> 3 & 7) == (cd & 7);
       const unsigned long long ms = __ballot(self);
       if (self) {
-        inc[ii + __popcll(ms & ((1ull << l) - 1ull))] = (cd >> 6) * 8 + (cd & 7);
+        const int k = ii + __popcll(ms & ((1ull << l) - 1ull));
+        inc[k] = s_inc[k - b / 8] = (cd >> 6) * 8 + (cd & 7);
       }
       ii += __popcll(ms);
       const bool head = j < len && (j == 0 || col[b + j] != col[b + j - 1]);
@@ -1077,6 +1098,18 @@ __global__ __launch_bounds__(64) void sym_pairs_kernel(int64_t n_nodes, const in
       }
       run += __popcll(m);
     }
+    __syncthreads();
+    for (int j = l; j < len; j += 64) {
+      const int32_t cd = code[b + j], mine = cd >> 3;
+      int lo = 0, hi = len / 8 - 1;  // mine is one of s_inc, which ascends
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s_inc[mid] < mine) lo = mid + 1;
+        else hi = mid;
+      }
+      code[b + j] = 8 * lo + (cd & 7);
+    }
+    __syncthreads();
   }
 }
 
@@ -1429,14 +1462,15 @@ template <typename T>
 static hipError_t gen_tangent_t(const fe_problem* p, T* vals, int apply_bc, const TanArgs& ta, hipStream_t s) {
   const GenArgs g = gen_args(p);
   T* ke = static_cast<T*>(p->ke);
-  const unsigned grid = (unsigned)std::min<int64_t>(p->n_el, 8192);
+  const dim3 grid((unsigned)((p->n_el + TEL - 1) / TEL)), block(TBLOCK);
   switch (p->model_set) {
-    case MS_J2: timed_launch((gen_tangent_kernel<T, MS_J2>), dim3(grid), dim3(64), 0, s, g, ta, ke); break;
-    case MS_NH: timed_launch((gen_tangent_kernel<T, MS_NH>), dim3(grid), dim3(64), 0, s, g, ta, ke); break;
-    default: timed_launch((gen_tangent_kernel<T, MS_LINEAR>), dim3(grid), dim3(64), 0, s, g, ta, ke);
+    case MS_J2: timed_launch((gen_tangent_kernel<T, MS_J2>), grid, block, 0, s, g, ta, ke); break;
+    case MS_NH: timed_launch((gen_tangent_kernel<T, MS_NH>), grid, block, 0, s, g, ta, ke); break;
+    default: timed_launch((gen_tangent_kernel<T, MS_LINEAR>), grid, block, 0, s, g, ta, ke);
   }
-  hipLaunchKernelGGL(gen_assemble_kernel<T>, dim3(vblocks(p->n_pairs)), dim3(VBLOCK), 0, s, p->n_pairs, p->adj_ptr,
-                     p->adj, p->pair_row, p->pair_src_ptr, p->pair_src, (const T*)ke, p->mask, apply_bc, vals);
+  const unsigned ablocks = (unsigned)((p->n_nodes + ASM_WAVES - 1) / ASM_WAVES);
+  hipLaunchKernelGGL(gen_assemble_kernel<T>, dim3(ablocks), dim3(VBLOCK), 0, s, p->n_nodes, p->adj_ptr, p->adj,
+                     p->pair_src_ptr, p->pair_src, p->inc_ptr, p->inc, (const T*)ke, p->mask, apply_bc, vals);
   return hipGetLastError();
 }
 

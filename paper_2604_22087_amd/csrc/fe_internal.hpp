@@ -270,7 +270,7 @@ struct fe_problem {
   int32_t* adj = nullptr;          // [n_pairs] column node of each pair, ascending within a row
   int32_t* pair_row = nullptr;     // [n_pairs] row node of each pair
   int32_t* pair_src_ptr = nullptr; // [n_pairs + 1] run of each pair in pair_src
-  int32_t* pair_src = nullptr;     // [64 n_el] element codes e*64 + a*8 + b sorted by (row, column, code)
+  int32_t* pair_src = nullptr;     // [64 n_el] 8 incidence of the row + local column node, by (row, column, element)
   int32_t* gen_col = nullptr;      // [64 n_el] sorted column nodes (work array of the symbolic step)
   int32_t* inc_ptr = nullptr;      // [n_nodes + 1] first incidence of each node
   int32_t* inc = nullptr;          // [8 n_el] incidences 8 element + local node, by node, in element order

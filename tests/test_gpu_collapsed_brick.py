@@ -27,13 +27,27 @@ def _wedge_mesh(n):
     return out, new[to[conn]]
 
 
+def _fan_mesh(m, layers):
+    """m wedges around the z axis in each of `layers` layers: an axis node is in up to 2 m elements,
+    twice in each, and the assembly's rows of more than 8 incidences are read in place."""
+    ang = 2 * np.pi * np.arange(m) / m
+    ring = np.stack([np.cos(ang), np.sin(ang)], axis=1)
+    coords = [np.array([[0, 0, z]] + [[x, y, z] for x, y in ring], dtype=float) for z in np.linspace(0, 1, layers + 1)]
+    conn = []
+    for k in range(layers):
+        for i in range(m):
+            bot = [0, 1 + i, 1 + (i + 1) % m, 0]
+            conn.append([k * (m + 1) + v for v in bot] + [(k + 1) * (m + 1) + v for v in bot])
+    return np.concatenate(coords), np.array(conn)
+
+
 @pytest.mark.parametrize("prec", ["f64", "f32"])
-@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("n", [2, 3, 5, 12])
 def test_collapsed_bricks(n, prec):
     import torch
     from paper_2604_22087_amd import fe
     print(f"[collapsed brick] n={n} prec={prec}", flush=True)
-    coords, conn = _wedge_mesh(n)
+    coords, conn = _wedge_mesh(n) if n <= 3 else _fan_mesh(n, 2)
     assert any(len(set(c)) < 8 for c in conn.tolist())
     nd = 3 * len(coords)
     rng = np.random.default_rng(n)
