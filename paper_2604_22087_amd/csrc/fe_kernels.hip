@@ -1054,7 +1054,325 @@ hipError_t launch_csr_pattern(const fe_problem* p, int32_t* row_ptr, int32_t* co
   return hipGetLastError();
 }
 
-// CSR values (linear, J2 with the surrogate's Voigt tangents, Neo-Hookean): a workgroup takes
+// CSR values of the symmetric laws (linear, J2, Neo-Hookean).  A workgroup owns the 4 x 4 x 2 nodes of a
+// tile and, of each node's 27 neighbours, itself and the 13 after it: it writes such a block K_ab into row a and its
+// transpose into row b.  All elements that share a and b hold a, so a block is whole where it is
+// formed (no atomics, fixed order).
+// Phase 1: the Gauss-point coefficients of the 5 x 5 x 3 elements around the tile go to LDS, scaled by
+// the weight and 1/h^2: (lp, mp, -beta, N) of the small-strain laws; lam, mu, a flag, F^-T, ln J of
+// Neo-Hookean problems.  Phase 2: ten lanes per node, each one (neighbour offset d, element offset o)
+// of the y and z axes, (-1, -1), (0, -1), (0, 0) or (1, 0) per axis (element = node + o): four with
+// d_z = 1, two with d_z = 0 and d_y = 1, four of the node's own line; along x a lane takes both elements
+// and their two columns each, whose gradients they share, summed over the 8 points into the blocks
+// d_x = -1, 0, 1.  The two lanes of a (d_y, d_z) are 32 apart and meet in registers.  Phase 3: three lanes
+// per block and direction, one per row of three entries.
+// At 64^3 FP64 J2 505 us against 600 with one lane per (neighbour, element) task of every ordered pair
+// (78 instructions per block and point, 55 here): about 210 us of it the point loop (its FP64 instructions
+// alone 155), 120 the 534 MB of values written, the rest loads and barriers of the three phases, which the
+// three workgroups of a CU overlap only in part.
+constexpr int TS_X = 4, TS_Y = 4, TS_Z = 2, TS_NODES = TS_X * TS_Y * TS_Z;
+constexpr int TS_EX = TS_X + 1, TS_EY = TS_Y + 1, TS_EL = TS_EX * TS_EY * (TS_Z + 1);  // elements around the tile
+constexpr int TS_BX = TS_X + 2, TS_BY = TS_Y + 2, TS_BOX = TS_BX * TS_BY * (TS_Z + 1);  // its nodes and neighbours
+constexpr int TS_BLOCK = 10 * TS_NODES;
+constexpr int TS_PART = 6 * 27 + 1;       // reals per node between the phases: (d_y, d_z) lines of 3 blocks (odd: no bank conflicts)
+constexpr int TS_ITEMS = 3 * 14 + 3 * 13; // rows of three entries per node: its own blocks, their transposes
+constexpr int TS_OUT = TS_BLOCK / TS_ITEMS;  // nodes written at a time
+static_assert(TS_NODES == 32, "a node per lane of half a wave");
+
+template <typename T, int MS>
+__global__ __launch_bounds__(TS_BLOCK) __attribute__((amdgpu_waves_per_eu(MS == MS_J2 ? 4 : 2))) void tangent_sym_kernel(
+    TanArgs a, T* __restrict__ vals, int apply_bc) {
+  constexpr bool J2M = MS == MS_J2;
+  constexpr int NCO = MS == MS_NH ? 13 : (J2M ? 9 : 2), NQ = MS == MS_LINEAR ? 1 : 8;
+  constexpr int NSET = NQ * TS_EL, NIT = NQ == 8 ? 2 : 1, NQL = NQ / NIT;  // a lane takes NIT points of an element
+  constexpr int NBUF = NCO * NSET > TS_NODES * TS_PART ? NCO * NSET : TS_NODES * TS_PART;
+  __shared__ T s_buf[NBUF];                         // coefficients [NCO][point][element], later [node][TS_PART]
+  __shared__ alignas(8) uint8_t s_flag[8 * TS_EL];  // [element][point]: not the phase's elastic moduli
+  __shared__ int s_start[TS_BOX];                   // first value of a node's rows, -1 outside the mesh
+  __shared__ unsigned s_info[TS_BOX];               // bits 0-2 constrained dofs; 3-8 has a neighbour at -x +x -y +y -z +z
+  __shared__ double s_mat[8 * FE_MAX_PHASES];
+  const int n = a.n, tid = threadIdx.x;
+  const int64_t np1 = n + 1, ne = a.n_el;
+  // consecutive tiles on one XCD (workgroups are dealt round-robin over the 8): they share lines of the
+  // stored tangent and of the values
+  const int bx = (n + TS_X) / TS_X, by = (n + TS_Y) / TS_Y, bz = (n + TS_Z) / TS_Z;
+  const int tile = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+  if (tile >= bx * by * bz) return;
+  const int i0 = tile % bx * TS_X, j0 = tile / bx % by * TS_Y, k0 = tile / (bx * by) * TS_Z;
+
+  // phase 1: every load is issued before any is used
+  constexpr int NW = MS == MS_NH ? 10 : (J2M ? 6 : 1);
+  T tn[NIT][NW], sc = 1;
+  int ph = 0;
+  const int q0 = tid / TS_EL, el = tid - q0 * TS_EL;
+  const bool set_lane = tid < NQL * TS_EL;
+  bool in_el = false;
+  {
+    const int ez = el / (TS_EX * TS_EY), er = el - ez * (TS_EX * TS_EY), ey = er / TS_EX, ex = er - ey * TS_EX;
+    const int ea = i0 - 1 + ex, eb = j0 - 1 + ey, ec = k0 - 1 + ez;
+    in_el = set_lane && ea >= 0 && ea < n && eb >= 0 && eb < n && ec >= 0 && ec < n;
+    const int64_t e = in_el ? ea + (int64_t)n * (eb + (int64_t)n * ec) : 0;
+    ph = a.phase[e];
+    if (a.scale) sc = static_cast<const T*>(a.scale)[e];
+    if (MS != MS_LINEAR) {  // (read for every element: the words exist for all of them)
+      const T* tg = static_cast<const T*>(a.tangent) + (in_el ? q0 : 0) * ne + e;
+#pragma unroll
+      for (int u = 0; u < NIT; ++u)
+#pragma unroll
+        for (int q = 0; q < NW; ++q) tn[u][q] = tg[(int64_t)(q * 8 + NQL * u) * ne];
+    }
+  }
+  stage_phases(a.mat, s_mat, tid);
+  bool plain = true;
+  if (tid < TS_BOX) {
+    const int nz = tid / (TS_BX * TS_BY), nr = tid - nz * (TS_BX * TS_BY), ny = nr / TS_BX, nx = nr - ny * TS_BX;
+    const int gx = i0 - 1 + nx, gy = j0 - 1 + ny, gz = k0 + nz;
+    const bool in = gx >= 0 && gx <= n && gy >= 0 && gy <= n && gz <= n;
+    unsigned info = (gx > 0) << 3 | (gx < n) << 4 | (gy > 0) << 5 | (gy < n) << 6 | (gz > 0) << 7 | (gz < n) << 8;
+    if (in && apply_bc && a.mask) {
+      const uint8_t* m = a.mask + 3 * (gx + np1 * (gy + np1 * (int64_t)gz));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) info |= (m[c] ? 1u : 0u) << c;
+    }
+    s_info[tid] = info;
+    s_start[tid] = in ? (int)node_row_start(gx, gy, gz, n) : -1;
+    plain = in && info == 0x1f8;
+  }
+  // every node of the box has all 27 neighbours and none is constrained
+  const bool regular = __syncthreads_and(plain);
+  const T wq = T(0.125 * a.h);  // w / h^2
+  if (set_lane) {
+    const PhaseConst pc = phase_const(s_mat, ph);
+#pragma unroll
+    for (int u = 0; u < NIT; ++u) {
+      const int qp = q0 + NQL * u, si = tid + u * (NQL * TS_EL);
+      T lp = T(pc.lam) * sc, mp = T(pc.mu) * sc;
+      uint8_t flag = 0;
+      if (J2M) {
+        T beta = 0, N[6] = {0, 0, 0, 0, 0, 0};
+        if (pc.model == FE_J2) {
+          T t6[6];
+#pragma unroll
+          for (int q = 0; q < 6; ++q) t6[q] = tn[u][q % NW];
+          j2_tangent_coeffs(t6, T(pc.K) * sc, T(pc.G) * sc, T(pc.H), lp, mp, beta, N);
+          flag = t6[0] < T(0) ? 0 : 1;
+        }
+        // (points that only take part with weight 0 must still be finite)
+        if (!flag || !in_el)
+#pragma unroll
+          for (int q = 0; q < 6; ++q) N[q] = 0;
+        s_buf[(2 % NCO) * NSET + si] = -wq * beta;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) s_buf[((3 + q) % NCO) * NSET + si] = N[q];
+      }
+      if (MS == MS_NH) {
+        flag = pc.model == FE_NEOHOOKE ? 1 : 0;
+        s_buf[(2 % NCO) * NSET + si] = T(flag);
+#pragma unroll
+        for (int q = 0; q < NW; ++q) s_buf[((3 + q) % NCO) * NSET + si] = tn[u][q];
+      }
+      s_buf[si] = wq * lp;
+      s_buf[NSET + si] = wq * mp;
+      if (MS != MS_LINEAR) s_flag[8 * el + qp] = flag;
+    }
+  }
+  __syncthreads();
+
+  // phase 2
+  const int node = tid % TS_NODES, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = (tid >> 5) & 1;
+  const int nx = node % TS_X, ny = node / TS_X % TS_Y, nz = node / (TS_X * TS_Y);
+  const int dz = wave < 2 ? 1 : 0, dy = wave == 0 ? 2 * half - 1 : (wave == 2 ? 1 : 0);
+  const int oz = wave < 2 ? 0 : (wave == 2 ? half - 1 : wave - 4), oy = wave == 2 ? 0 : half - 1;
+  T acc[3][3][3];
+#pragma unroll
+  for (int m = 0; m < 27; ++m) acc[m / 9][m / 3 % 3][m % 3] = 0;
+  {
+    const int i = i0 + nx, j = j0 + ny, k = k0 + nz, eb = j + oy, ec = k + oz;
+    const bool yz = j <= n && k <= n && eb >= 0 && eb < n && ec >= 0 && ec < n;
+    const int el0 = nx + TS_EX * (ny + oy + 1 + TS_EY * (nz + oz + 1));  // element o = 0 (x offset -1); o = 1 is the next
+    const int ay = -oy, by = dy - oy, az = -oz, bz = dz - oz;
+    const T say = ay ? T(1) : T(-1), sby = by ? T(1) : T(-1), saz = az ? T(1) : T(-1), sbz = bz ? T(1) : T(-1);
+    bool general[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const bool ok = yz && i + o - 1 >= 0 && i + o - 1 < n;
+      const bool uni = MS == MS_LINEAR || !ok || *reinterpret_cast<const unsigned long long*>(s_flag + 8 * (el0 + o)) == 0;
+      general[o] = ok && !uni;
+      if (!ok || !uni) continue;
+      // elastic at all 8 points: the sum in closed form.  With A = sum_q ga gb^T (geometry only),
+      // B = lp A + mp (tr(A) I + A^T); per axis the Gauss sums of the two corners' 1-D factors are
+      // S = sum_p phi_a(g_p) phi_b(g_p) (GA^2 + GB^2 on equal corners, 2 GA GB otherwise) and
+      // sum_p phi(g_p) = 1
+      const T lp = s_buf[el0 + o], mp = s_buf[NSET + el0 + o];
+      const T Sy = ay == by ? T(GA * GA + GB * GB) : T(2 * GA * GB), Sz = az == bz ? T(GA * GA + GB * GB) : T(2 * GA * GB);
+      const T ax = o ? T(-1) : T(1);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const T bx = m ? T(1) : T(-1);
+        const T Sx = 1 - o == m ? T(GA * GA + GB * GB) : T(2 * GA * GB);
+        const T sa[3] = {ax, say, saz}, sb[3] = {bx, sby, sbz}, S[3] = {Sx, Sy, Sz};
+        T A[3][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            A[c][d] = sa[c] * sb[d] * (c == d ? 2 * S[(c + 1) % 3] * S[(c + 2) % 3] : S[3 - c - d]);
+        const T tr = mp * (A[0][0] + A[1][1] + A[2][2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int d = 0; d < 3; ++d) acc[o + m][c][d] += lp * A[c][d] + mp * A[d][c] + (c == d ? tr : T(0));
+      }
+    }
+    if (MS != MS_LINEAR && (general[0] || general[1])) {
+#pragma unroll 1
+      for (int qr = 0; qr < 4; ++qr) {
+        const int q = qr & 1, r = qr >> 1;
+        const T ya = ay == q ? T(GA) : T(GB), yb = by == q ? T(GA) : T(GB);
+        const T za = az == r ? T(GA) : T(GB), zb = bz == r ? T(GA) : T(GB);
+        const T a0 = ya * za, a1 = say * za, a2 = ya * saz, b0 = yb * zb, b1 = sby * zb, b2 = yb * sbz;
+#pragma unroll
+        for (int px = 0; px < 2; ++px) {
+#pragma unroll
+          for (int o = 0; o < 2; ++o) {
+            if (!J2M && !general[o]) continue;
+            if (J2M) asm volatile("" ::: "memory");  // one set of coefficients in registers at a time
+            const T* co = s_buf + (px + 2 * qr) * TS_EL + el0 + o;
+            const T X = px == 1 - o ? T(GA) : T(GB);
+            const T ga[3] = {o ? -a0 : a0, X * a1, X * a2};  // h times the gradients
+            T lp = co[0], mp = co[NSET], va[3], x3[3], c3 = 0, lnJ = 0, M[9];
+            // J2 problems run every lane through the plastic term, elements in closed form or outside with
+            // weight 0: branches at each point cost more than they save
+            const bool second = J2M || co[(2 % NCO) * NSET] != T(0);
+            if (J2M) {
+              c3 = co[(2 % NCO) * NSET];
+#pragma unroll
+              for (int m = 0; m < 9; ++m)
+                M[m] = co[((3 + (m / 3 == m % 3 ? m / 3 : 6 - m / 3 - m % 3)) % NCO) * NSET];
+              if (!general[o]) lp = mp = c3 = 0;
+            }
+            if (MS == MS_NH) {
+#pragma unroll
+              for (int m = 0; m < 9; ++m) M[m] = co[((3 + m) % NCO) * NSET];
+              lnJ = co[(12 % NCO) * NSET];
+            }
+            if (second) {
+#pragma unroll
+              for (int c = 0; c < 3; ++c) {
+                va[c] = M[3 * c] * ga[0] + M[3 * c + 1] * ga[1] + M[3 * c + 2] * ga[2];
+                x3[c] = c3 * va[c];
+              }
+            }
+            T x1[3], x2[3];
+            const bool nh = MS == MS_NH && second;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              x1[c] = lp * (nh ? va[c] : ga[c]);
+              x2[c] = (nh ? mp - lp * lnJ : mp) * (nh ? va[c] : ga[c]);
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+              const T Xb = px == m ? T(GA) : T(GB);
+              const T gb[3] = {m ? b0 : -b0, Xb * b1, Xb * b2};
+              T vb[3];
+              if (second)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) vb[c] = M[3 * c] * gb[0] + M[3 * c + 1] * gb[1] + M[3 * c + 2] * gb[2];
+              const T t = mp * (ga[0] * gb[0] + ga[1] * gb[1] + ga[2] * gb[2]);
+              T pb[3];
+#pragma unroll
+              for (int c = 0; c < 3; ++c) pb[c] = nh ? vb[c] : gb[c];
+#pragma unroll
+              for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                  T v = acc[o + m][c][d] + x1[c] * pb[d];
+                  v += x2[d] * pb[c];
+                  if (c == d) v += t;
+                  acc[o + m][c][d] = v;
+                }
+              if (J2M && second)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+#pragma unroll
+                  for (int d = 0; d < 3; ++d) acc[o + m][c][d] += x3[c] * vb[d];
+            }
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();  // the coefficients are read no more
+  // lines 0: (d_y, d_z) = (-1, 1), 1: (0, 1), 2: (1, 1), 3: (1, 0), 4 and 5: (0, 0) with o_z = -1 and 0.  From
+  // wave 1 on the halves share a line: the lower one gets the sums of the even words, the upper one of the odd
+  T* line = s_buf + node * TS_PART + 27 * (wave == 0 ? 2 * half : (wave == 1 ? 1 : wave + 1));
+  if (wave == 0) {
+#pragma unroll
+    for (int m = 0; m < 27; ++m) line[m] = acc[m / 9][m / 3 % 3][m % 3];
+  } else {
+#pragma unroll
+    for (int m = 0; m < 26; m += 2) line[m + half] = half_sum(acc[m / 9][m / 3 % 3][m % 3], acc[(m + 1) / 9][(m + 1) / 3 % 3][(m + 1) % 3]);
+    const T v = half_sum(acc[2][2][2], acc[2][2][2]);
+    if (half == 0) line[26] = v;
+  }
+  __syncthreads();
+
+  // phase 3: this lane's item (the same for every node): block, direction and row
+  const int item = tid % TS_ITEMS;
+  const bool transposed = item >= 42;
+  const int r = (transposed ? item - 42 : item) / (transposed ? 13 : 14);
+  const int blk = (transposed ? item - 42 : item) - r * (transposed ? 13 : 14) + (transposed ? 1 : 0);
+  // blocks in column order: 0 itself, 1 (1,0,0), 2-4 (d_x,1,0), 5-13 (d_x,d_y,1)
+  const int bzz = blk >= 5 ? 1 : 0, byy = blk >= 5 ? (blk - 5) / 3 - 1 : (blk >= 2 ? 1 : 0);
+  const int bxx = blk >= 5 ? (blk - 5) % 3 - 1 : (blk >= 2 ? blk - 3 : blk);
+  const int from = 27 * (blk >= 5 ? byy + 1 : (blk >= 2 ? 3 : 4)) + 9 * (bxx + 1) + (transposed ? r : 3 * r);
+  const int stride = transposed ? 3 : 1, off = bxx + TS_BX * (byy + TS_BY * bzz);
+  const int sx = transposed ? -bxx : bxx, sy = transposed ? -byy : byy, sz = transposed ? -bzz : bzz;
+  const int nd0 = tid < TS_OUT * TS_ITEMS ? tid / TS_ITEMS : TS_NODES;
+  if (regular) {
+    T* at = vals + 3 * (27 * r + (sz * 3 + sy) * 3 + sx + 13);
+    const int own0 = 1 + TS_BX + (transposed ? off : 0);
+    for (int nd = nd0; nd < TS_NODES; nd += TS_OUT) {
+      const T* part = s_buf + nd * TS_PART + from;
+      T v[3];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) v[m] = part[m * stride];
+      if (blk < 2)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) v[m] += part[27 + m * stride];
+      T* out = at + s_start[own0 + nd % TS_X + TS_BX * (nd / TS_X % TS_Y + TS_BY * (nd / (TS_X * TS_Y)))];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) out[m] = v[m];
+    }
+    return;
+  }
+  for (int nd = nd0; nd < TS_NODES; nd += TS_OUT) {
+    const int ba = nd % TS_X + 1 + TS_BX * (nd / TS_X % TS_Y + 1 + TS_BY * (nd / (TS_X * TS_Y))), bb = ba + off;
+    const int own = transposed ? bb : ba, other = transposed ? ba : bb;
+    const int start = s_start[own];
+    if (start < 0 || s_start[other] < 0) continue;
+    const unsigned fo = s_info[own], ft = s_info[other];
+    const T* part = s_buf + nd * TS_PART + from;
+    T v[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      v[m] = part[m * stride];
+      if (blk < 2) v[m] += part[27 + m * stride];
+    }
+    const int lox = fo >> 3 & 1, loy = fo >> 5 & 1, loz = fo >> 7 & 1;
+    const int cx = 1 + lox + (fo >> 4 & 1), cy = 1 + loy + (fo >> 6 & 1), cz = 1 + loz + (fo >> 8 & 1);
+    const int rank = ((sz + loz) * cy + sy + loy) * cx + sx + lox;
+    T* out = vals + start + 3 * (r * (cx * cy * cz) + rank);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      if ((fo >> r | ft >> m) & 1) v[m] = blk == 0 && r == m ? T(1) : T(0);
+      out[m] = v[m];
+    }
+  }
+}
+
+// CSR values, all ordered node pairs: problems with surrogate points, whose Voigt tangents need not be
+// symmetric, and meshes too small to fill the chip with tiles.  A workgroup takes
 // TR_NODES consecutive nodes of one x-row of nodes, whose CSR rows are one contiguous segment.
 // Phase 1 forms the Gauss-point coefficients of the elements around the tile once into LDS
 // ((lp, mp, beta, N) of the small-strain laws; lam, mu, F^-T, ln J at Neo-Hookean points).  Phase 2: lane (node, task), one wave per node; the 64 tasks
@@ -1297,26 +1615,36 @@ __global__ __launch_bounds__(256) void tangent_rows_kernel(TanArgs a, T* vals, i
   }
 }
 
+// About a tile per CU: below that the longer chain of a tile costs more than its fewer instructions save (FP64 J2,
+// rows against tiles: 14^3 24 and 29 us, 16^3 28 and 30, 18^3 36 and 34, 20^3 40 and 38).
+constexpr int64_t TS_MIN_TILES = 240;
+template <typename T>
+static void launch_tangent_csr_t(const fe_problem* p, T* v, int apply_bc, hipStream_t s) {
+  const TanArgs a = tan_args(p);
+  const int np1 = p->n + 1;
+  const int64_t tiles = (int64_t)((np1 + TS_X - 1) / TS_X) * ((np1 + TS_Y - 1) / TS_Y) * ((np1 + TS_Z - 1) / TS_Z);
+  const bool sur = p->model_set == MS_J2 && p->sur_map;
+  if (sur || tiles < TS_MIN_TILES) {
+    const dim3 grid((unsigned)((int64_t)np1 * np1 * ((np1 + TR_NODES - 1) / TR_NODES))), block(256);
+    switch (p->model_set) {
+      case MS_J2: timed_launch((tangent_rows_kernel<T, MS_J2>), grid, block, 0, s, a, v, apply_bc); break;
+      case MS_NH: timed_launch((tangent_rows_kernel<T, MS_NH>), grid, block, 0, s, a, v, apply_bc); break;
+      default: timed_launch((tangent_rows_kernel<T, MS_LINEAR>), grid, block, 0, s, a, v, apply_bc);
+    }
+    return;
+  }
+  const dim3 grid((unsigned)(8 * ((tiles + 7) / 8))), block(TS_BLOCK);
+  switch (p->model_set) {
+    case MS_J2: timed_launch((tangent_sym_kernel<T, MS_J2>), grid, block, 0, s, a, v, apply_bc); break;
+    case MS_NH: timed_launch((tangent_sym_kernel<T, MS_NH>), grid, block, 0, s, a, v, apply_bc); break;
+    default: timed_launch((tangent_sym_kernel<T, MS_LINEAR>), grid, block, 0, s, a, v, apply_bc);
+  }
+}
+
 hipError_t launch_tangent_csr(const fe_problem* p, void* vals, int apply_bc, hipStream_t s) {
   if (p->general) return gen_tangent(p, vals, apply_bc, tan_args(p), s);
-  const TanArgs a = tan_args(p);
-  const int64_t np1 = p->n + 1;
-  const dim3 grid((unsigned)(np1 * np1 * ((np1 + TR_NODES - 1) / TR_NODES))), block(256);
-  if (p->prec == FE_F64) {
-    double* v = (double*)vals;
-    switch (p->model_set) {
-      case MS_J2: timed_launch((tangent_rows_kernel<double, MS_J2>), grid, block, 0, s, a, v, apply_bc); break;
-      case MS_NH: timed_launch((tangent_rows_kernel<double, MS_NH>), grid, block, 0, s, a, v, apply_bc); break;
-      default: timed_launch((tangent_rows_kernel<double, MS_LINEAR>), grid, block, 0, s, a, v, apply_bc);
-    }
-  } else {
-    float* v = (float*)vals;
-    switch (p->model_set) {
-      case MS_J2: timed_launch((tangent_rows_kernel<float, MS_J2>), grid, block, 0, s, a, v, apply_bc); break;
-      case MS_NH: timed_launch((tangent_rows_kernel<float, MS_NH>), grid, block, 0, s, a, v, apply_bc); break;
-      default: timed_launch((tangent_rows_kernel<float, MS_LINEAR>), grid, block, 0, s, a, v, apply_bc);
-    }
-  }
+  if (p->prec == FE_F64) launch_tangent_csr_t(p, (double*)vals, apply_bc, s);
+  else launch_tangent_csr_t(p, (float*)vals, apply_bc, s);
   return hipGetLastError();
 }
 
