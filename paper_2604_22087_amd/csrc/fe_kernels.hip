@@ -357,14 +357,15 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
 // ---------------------------------------------------------------------------
 // element brick kernel
 
-// (waves per SIMD asked of the compiler; the lane split leaves every instance but the FP64 residuals
-// of J2 and Neo-Hookean problems room for four: see elem_waves)
-// ACC32 (FP32 problems only): the nodal sums accumulate in FP32 LDS as well; by default they
-// are formed in FP64 in both precisions.
+// (waves per SIMD asked of the compiler: four without spills, but for the branches of surrogate points and
+// the FP64 J2 residual, where the history words in flight are worth more than a fourth wave: 141 us
+// at 64^3 with four waves and 13 spilled registers, 126 with three)
 template <typename T, int OP, int MS> constexpr int elem_waves() {
-  return MS == MS_SUR ? 2 : 4;
+  return MS == MS_SUR ? 2 : (OP == OP_RESID && MS == MS_J2 && sizeof(T) == 8 ? 3 : 4);
 }
 
+// ACC32 (FP32 problems only): the nodal sums accumulate in FP32 LDS as well; by default they
+// are formed in FP64 in both precisions.
 template <typename T, int OP, int MS, bool ACC32 = false>
 __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_waves<T, OP, MS>()))) void elem_kernel(
     ElemArgs a, const int* stop) {
@@ -510,6 +511,20 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     };
     if (APPLY_LIKE && MS == MS_NH) load_nh(0, nw[0]);
 
+    // J2 residual: history words are requested two points ahead and before the point's own stores.  Loads and
+    // stores retire in one order, so words requested after stores wait for those as well (64^3 FP64
+    // with state and tangent stored, 334 MB: 149 us at each point's turn, 126 one point ahead, 123 two)
+    const T* st_in = static_cast<const T*>(a.state_in);
+    T hist[2][7];
+    auto load_hist = [&](int q4) {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) hist[q4 & 1][k] = st_in ? st_in[e4 + (k * 8 + q4) * ne] : T(0);
+    };
+    if (OP == OP_RESID && J2M) {
+      load_hist(0);
+      load_hist(1);
+    }
+
     HalfGrad<T> g, s;  // gradients (times h), stress sums
     half_gradients<T>([&](int k, int j, int i, int c) { return s_x[s0 + 3 * (i + NX * (j + NY * k)) + c]; }, w0, w1, g);
     if constexpr (PARK) {
@@ -524,7 +539,6 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     // the operators are linear in the gradient, so 1/h goes into the final factor there
     const T inv_h = APPLY_LIKE ? T(1) : T(1.0 / a.h);
 
-    const T* st_in = static_cast<const T*>(a.state_in);
     T* st_out = static_cast<T*>(a.state_out);
     T* tang = static_cast<T*>(a.tangent);
 
@@ -572,10 +586,11 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
         } else if constexpr (OP == OP_RESID && J2M) {
           if (pc.model == FE_J2) {
             const T Kb = T(pc.K) * sc, Gs = T(pc.G) * sc, sy = T(pc.sy), Hh = T(pc.H);
-            T epn[6], an = 0, ep[6], al, tn[6];
+            T ep[6], al, tn[6];
+            T epn[6];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) epn[k] = st_in ? st_in[e4 + (k * 8 + q4) * ne] : T(0);
-            if (st_in) an = st_in[e4 + (6 * 8 + q4) * ne];
+            for (int k = 0; k < 6; ++k) epn[k] = hist[q4 & 1][k];
+            const T an = hist[q4 & 1][6];
             j2_update(H, epn, an, Kb, Gs, sy, Hh, S, ep, al, tn);
             if (SUR) {
               const int64_t pidx = e4 + q4 * ne;
@@ -624,6 +639,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
                 wave_count(a.sur_stats + 1, fallback);
               }
             }
+            if (q4 < 2) load_hist(q4 + 2);
             if (st_out) {
 #pragma unroll
               for (int k = 0; k < 6; ++k) st_out[e4 + (k * 8 + q4) * ne] = ep[k];
@@ -635,10 +651,13 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
             }
           } else {
             hooke(H, T(pc.lam) * sc, T(pc.mu) * sc, S);
+            T keep[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) keep[k] = hist[q4 & 1][k];
+            if (q4 < 2) load_hist(q4 + 2);
             if (st_out) {  // non-J2 phase: state passes through
 #pragma unroll
-              for (int k = 0; k < 7; ++k)
-                st_out[e4 + (k * 8 + q4) * ne] = st_in ? st_in[e4 + (k * 8 + q4) * ne] : T(0);
+              for (int k = 0; k < 7; ++k) st_out[e4 + (k * 8 + q4) * ne] = keep[k];
             }
           }
         } else {
