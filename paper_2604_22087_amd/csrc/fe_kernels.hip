@@ -2877,7 +2877,7 @@ struct PathArgs {
 // lane takes four points, the history part of the strain cotangent is pushed to the nodes like a
 // stress.  Bound by its 23 words per point (150 MB at 48^3, the floor 32 us); differentiating the update
 // column by column with dual numbers instead cost 14 updates a point in 256 spilling registers, one
-// element per lane: 482 us at 48^3 against 53.
+// element per lane: 482 us at 48^3 against 47.
 __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) void path_vjp_kernel(PathArgs a) {
   __shared__ double s_u[NN * 3], s_c[NN * 3], s_y[NN * 3], s_park[18][EBLOCK];
   __shared__ double s_mat[8 * FE_MAX_PHASES];
@@ -2923,11 +2923,22 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
     const double sc = a.scale ? a.scale[e] : 1.0;
     const bool j2 = pc.model == FE_J2;
     const double inv_h = 1.0 / a.h, w = 0.125 * a.h * a.h;  // (weight w detJ = h^3/8 times 1/h of the gradient)
+    // a point's words are requested before the point before it stores its own (loads and stores retire in
+    // one order: 52 us at 48^3 at each point's turn, 47 so)
+    double mu[7], hn[7];
+    auto load_words = [&](int q4) {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) {
+        mu[k] = a.mu_in ? a.mu_in[e4 + (k * 8 + q4) * ne] : 0.0;
+        hn[k] = j2 && a.hist ? a.hist[e4 + (k * 8 + q4) * ne] : 0.0;
+      }
+    };
+    load_words(0);
     HalfGrad<double> g, gc_, s;
     half_gradients<double>([&](int kk, int jj, int ii, int c) { return s_u[s0 + 3 * (ii + NX * (jj + NY * kk)) + c]; }, w0, w1, g);
     half_gradients<double>([&](int kk, int jj, int ii, int c) { return s_c[s0 + 3 * (ii + NX * (jj + NY * kk)) + c]; }, w0, w1, gc_);
     double sbar = 0;
-    // the gradients of the points q = 1 wait in LDS (36 registers; 66 us at 48^3 with them held, 53 so)
+    // the gradients of the points q = 1 wait in LDS (36 registers; 66 us at 48^3 with them held, 52 so)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       s_park[c][threadIdx.x] = g.x[1][c];
@@ -2954,12 +2965,6 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const int64_t at = e4 + (p + 2 * q) * ne;
-        double mu[7], hn[7];
-#pragma unroll
-        for (int k = 0; k < 7; ++k) {
-          mu[k] = a.mu_in ? a.mu_in[at + k * 8 * ne] : 0.0;
-          hn[k] = j2 && a.hist ? a.hist[at + k * 8 * ne] : 0.0;
-        }
         double H[3][3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -2970,19 +2975,19 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
         // stress cotangent: c . R = sum_q w (B_q c_e) . sigma_q (engineering-shear pairing)
         const double sb[6] = {w * gc_.x[q][0], w * gc_.y[p][1], w * gc_.z[q][p][2], w * (gc_.z[q][p][1] + gc_.y[p][2]),
                               w * (gc_.z[q][p][0] + gc_.x[q][2]), w * (gc_.y[p][0] + gc_.x[q][1])};
-        double eh[6] = {0, 0, 0, 0, 0, 0};
+        double eh[6] = {0, 0, 0, 0, 0, 0}, mb[7];
         if (j2) {
-          double mb[7];
           sbar += j2_adjoint(H, hn, pc.K * sc, pc.G * sc, pc.K, pc.G, pc.sy, pc.H, sb, mu, mb, eh);
-#pragma unroll
-          for (int k = 0; k < 7; ++k) a.mu_out[at + k * 8 * ne] = mb[k];
         } else {  // history-free phase: the state passes through; sigma = s D_hat eps
           double S[3][3];
           hooke(H, pc.lam, pc.mu, S);
           sbar += sb[0] * S[0][0] + sb[1] * S[1][1] + sb[2] * S[2][2] + sb[3] * S[1][2] + sb[4] * S[0][2] + sb[5] * S[0][1];
 #pragma unroll
-          for (int k = 0; k < 7; ++k) a.mu_out[at + k * 8 * ne] = mu[k];
+          for (int k = 0; k < 7; ++k) mb[k] = mu[k];
         }
+        if (p + 2 * q < 3) load_words(p + 2 * q + 1);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) a.mu_out[at + k * 8 * ne] = mb[k];
         // d/dH of the engineering strain: symmetric, the shear cotangent in both entries
         const double Hb[3][3] = {{eh[0], eh[5], eh[4]}, {eh[5], eh[1], eh[3]}, {eh[4], eh[3], eh[2]}};
 #pragma unroll
