@@ -417,7 +417,16 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   const int ph = valid ? (int)a.phase[e] : 0;
   const T* tang_c = static_cast<const T*>(a.tangent);
   T tq0[4];
+  // FP32 Neo-Hookean K u: the first point's ten words as well (64^3 32.2 -> 30.4 us, 80^3 63.5 -> 62.0; the
+  // CG launch, whose staging is longer, lost by it: 128^3 292 -> 300)
+  constexpr bool NH_EARLY = MS == MS_NH && OP == OP_APPLY && sizeof(T) == 4;
+  T nw[NHB][10];
   auto early = [&]() {
+    if (NH_EARLY) {
+      const bool nh = valid && ((a.law_mask >> ph) & 1u);
+#pragma unroll
+      for (int k = 0; k < 10; ++k) nw[0][k] = nh ? tang_c[e4 + k * 8 * ne] : T(0);
+    }
     if (APPLY_LIKE && J2M) {
       const bool j2 = valid && ((a.law_mask >> ph) & 1u);
 #pragma unroll
@@ -503,13 +512,12 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
       for (int q0 = 0; q0 < PF; ++q0) load_pw(q0, pw[q0]);
     // Neo-Hookean operator: F^-T and ln J of the linearisation, stored by the residual per
     // Gauss point ([10][8][n_el]), requested one point ahead of their use
-    T nw[NHB][10];
     const bool nh_el = MS == MS_NH && pc.model == FE_NEOHOOKE;
     auto load_nh = [&](int q4, T* w) {
 #pragma unroll
       for (int k = 0; k < 10; ++k) w[k] = nh_el ? tang_c[e4 + (k * 8 + q4) * ne] : T(0);
     };
-    if (APPLY_LIKE && MS == MS_NH) load_nh(0, nw[0]);
+    if (APPLY_LIKE && MS == MS_NH && !NH_EARLY) load_nh(0, nw[0]);
 
     // J2 residual: history words are requested two points ahead and before the point's own stores.  Loads and
     // stores retire in one order, so words requested after stores wait for those as well (64^3 FP64
