@@ -2817,7 +2817,8 @@ __device__ __forceinline__ double j2_adjoint(const double H[3][3], const double 
   const double e12 = 0.5 * (H[1][2] + H[2][1] - hn[3]), e02 = 0.5 * (H[0][2] + H[2][0] - hn[4]),
                e01 = 0.5 * (H[0][1] + H[1][0] - hn[5]);
   const double tr = e00 + e11 + e22, m = tr / 3.0, g2 = 2 * G;
-  const double s[6] = {g2 * (e00 - m), g2 * (e11 - m), g2 * (e22 - m), g2 * e12, g2 * e02, g2 * e01};
+  const double d[6] = {e00 - m, e11 - m, e22 - m, e12, e02, e01};
+  const double s[6] = {g2 * d[0], g2 * d[1], g2 * d[2], g2 * d[3], g2 * d[4], g2 * d[5]};
   const double sn = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]));
   const double q = SQRT1_5 * sn;
   const double f = q - (sy + Hh * hn[6]);
@@ -2851,9 +2852,9 @@ __device__ __forceinline__ double j2_adjoint(const double H[3][3], const double 
     for (int k = 0; k < 6; ++k) db[k] = sb[k];
   }
   const double pb = sb[0] + sb[1] + sb[2];
-  double sum = 0;  // s is 2 G times a strain: its cotangent times s / G
+  double sum = 0;  // s = 2 G d (d, not s / G: the modulus of a void element is 0)
 #pragma unroll
-  for (int k = 0; k < 6; ++k) sum += db[k] * s[k];
+  for (int k = 0; k < 6; ++k) sum += db[k] * d[k];
   const double td = K * pb - (g2 / 3.0) * (db[0] + db[1] + db[2]), th = -(g2 / 3.0) * (hb[0] + hb[1] + hb[2]);
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
@@ -2862,7 +2863,7 @@ __device__ __forceinline__ double j2_adjoint(const double H[3][3], const double 
     mb[k] = mu[k] - (k < 3 ? g2 * db[k] + td : G * db[k]);
   }
   mb[6] = ab;
-  return (Gb + sum / G) * G0 + pb * tr * K0;
+  return (Gb + 2 * sum) * G0 + pb * tr * K0;
 }
 
 struct PathArgs {
