@@ -1091,7 +1091,9 @@ extern "C" int fe_pcg(fe_problem* p, int op, const int32_t* row_ptr, const int32
   }
   if (!(rtol >= 0) || max_it < 0) return arg_error("rtol must be >= 0 and max_it >= 0");
   if (op == FE_OP_MATFREE) row_ptr = nullptr, col_idx = nullptr, vals = nullptr;
-  return pcg_run(p, op, row_ptr, col_idx, vals, b, x, rtol, max_it, info, S(stream), nullptr);
+  const int st = pcg_run(p, op, row_ptr, col_idx, vals, b, x, rtol, max_it, info, S(stream), nullptr);
+  HIPCHK(hipStreamSynchronize(S(stream)));  // (an odd number of structured updates ends in a launch behind the last poll)
+  return st;
 }
 
 extern "C" int fe_vjp(fe_problem* p, const void* u, const void* lambda, void* out, void* stream) {
