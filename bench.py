@@ -574,8 +574,9 @@ def main():
                      "kernel": "elem_kernel<double, OP_CG_APPLY, MS_J2> (single-reduction CG launch: vector "
                                "updates, M^-1, matrix-free K*u and three dot products)",
                      "avg_launch_us": 1e3 * ku_avg_ms, "launches": cnt,
-                     "sampling": f"HIP event pairs on operator launches 0, {CG_TIMING_STRIDE}, "
-                                 f"{2 * CG_TIMING_STRIDE}, ... of every CG solve in the timed region",
+                     "sampling": f"HIP event pairs on operator launches 0, {CG_TIMING_STRIDE - 1}, "
+                                 f"{2 * CG_TIMING_STRIDE}, {3 * CG_TIMING_STRIDE - 1}, ... of every CG solve in "
+                                 f"the timed region (even and odd launches in turn: they move different bytes)",
                      "bytes_per_launch": byts / max(cnt, 1)},
         "ku_kernel_gdofs": P.n_dof / (ku_avg_ms * 1e-3) / 1e9,
         "qp_evals_per_s": P.n_qp / (rms / max(rcnt, 1) * 1e-3),

@@ -378,7 +378,10 @@ int fe_mean_stress(fe_problem* p, const void* u, const void* state_in, double* s
  * mat-vec (fe_apply_csr_nodal).  enable = 1 clears previous records; enable = 0
  * stops recording; enable = k > 1 is enable = 1 except that inside a CG solve
  * only operator launches 0, k, 2k, ... are timed (an event pair costs several
- * microseconds of issue time per launch); enable < 0 is FE_ERR_ARG.
+ * microseconds of issue time per launch; the structured matrix-free solve, whose
+ * even launches also advance x, takes 0, k - 1, 2k, 3k - 1, ... for an even k and
+ * charges every launch the mean bytes of an even and an odd one); enable < 0 is
+ * FE_ERR_ARG.
  * fe_profile_read synchronises the device and writes, for
  * c = 0..4, out_host[3*c] = launches, out_host[3*c+1] = summed milliseconds,
  * out_host[3*c+2] = summed algorithmic bytes of those launches for classes 0, 1

@@ -798,10 +798,16 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
   const size_t rec0 = p->prof_recs.size();
   const int cls = op == FE_OP_CSR ? 1 : 0;
   const long stride = p->prof ? p->prof_stride : 1;
-  long n_op = 0;  // operator launches of this solve; every stride-th one is timed
+  // operator launches of this solve: one of every `stride` is timed.  The structured form moves more in its
+  // even launches (see below), so an even stride takes launches 0, stride - 1, 2 stride, 3 stride - 1, ...
+  long n_op = 0;
+  auto timed_op = [&](long j) {
+    if (!sfused || stride % 2) return j % stride == 0;
+    return j % (2 * stride) == 0 || (j + 1) % (2 * stride) == stride;
+  };
 #define CG_OPERATOR(expr)                \
   do {                                   \
-    if (n_op++ % stride == 0)            \
+    if (timed_op(n_op++))                \
       PROF(p, s, cls, expr);             \
     else                                 \
       HIPCHK(expr);                      \
@@ -838,15 +844,16 @@ static int pcg_run(fe_problem* p, int op, const int32_t* rp, const int32_t* ci, 
   const size_t executed = (size_t)c.iters + (sfused ? 1 : 0) +
                           (!sfused && (status == FE_ERR_BREAKDOWN || status == FE_ERR_NONFINITE) ? 1 : 0);
 #undef CG_OPERATOR
-  if (p->prof) {  // timed launches among the executed ones: 0, stride, 2 stride, ...
-    const size_t kept = (executed + (size_t)stride - 1) / (size_t)stride;
+  if (p->prof) {  // timed launches among the executed ones
+    size_t kept = 0;
+    for (long j = 0; j < (long)executed; ++j) kept += timed_op(j) ? 1 : 0;
     if (p->prof_recs.size() > rec0 + kept) p->prof_recs.resize(rec0 + kept);
     const size_t timed = p->prof_recs.size() - rec0;
     double b = 0;
     if (int e = operator_bytes(p, op, s, &b)) return e;
     // the fused matrix-free CG launch reads r, w, s and M^-1 (1 or 2 reals per dof) and writes
     // r, s and the zeroed w instead of reading x; every second launch also reads r_{j-2}, p and x
-    // and writes p and x
+    // and writes p and x: each timed launch is charged the mean of the two
     if (sfused) b += (p->precond == FE_PC_BLOCK_JACOBI ? 9.5 : 8.5) * (double)real_size(p) * (double)p->n_dof;
     p->prof_bytes[cls] += b * (double)timed;
   }
