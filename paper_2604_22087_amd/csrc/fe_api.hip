@@ -197,7 +197,7 @@ static int alloc_common(fe_problem* p) {
       (st = alloc(&p->w_q, vec)) || (st = alloc(&p->w_d, vec)) ||
       (st = alloc((void**)&p->partials, n_part * sizeof(double))) ||
       (st = alloc((void**)&p->counter, sizeof(unsigned int))) || (st = alloc((void**)&p->ctrl, sizeof(CgCtrl))) ||
-      (st = alloc((void**)&p->stress_sum, 8 * sizeof(double))) || (st = alloc((void**)&p->flags, sizeof(int)))) {
+      (st = alloc((void**)&p->stress_sum, 8 * STRESS_SLOTS * sizeof(double))) || (st = alloc((void**)&p->flags, sizeof(int)))) {
     fe_problem_destroy(p);
     return st;
   }
@@ -205,7 +205,7 @@ static int alloc_common(fe_problem* p) {
   if ((e = hipMemset(p->phase, 0, p->n_el)) != hipSuccess || (e = hipMemset(p->counter, 0, sizeof(unsigned int))) ||
       (e = hipMemset(p->flags, 0, sizeof(int))) || (e = hipMemset(p->ctrl, 0, sizeof(CgCtrl))) ||
       (e = hipHostMalloc((void**)&p->host_ctrl, sizeof(CgCtrl), hipHostMallocDefault)) ||
-      (e = hipHostMalloc((void**)&p->host_buf, 64 * sizeof(double), hipHostMallocDefault))) {
+      (e = hipHostMalloc((void**)&p->host_buf, 8 * STRESS_SLOTS * sizeof(double), hipHostMallocDefault))) {
     fe_problem_destroy(p);
     return hip_fail(e, "fe_problem_create");
   }
@@ -525,12 +525,16 @@ int fe_residual(fe_problem* p, const void* u, const void* state_in, void* state_
 int fe_mean_stress(fe_problem* p, const void* u, const void* state_in, double* sigma, void* stream) {
   CHKP(p);
   if (!u || !sigma) return arg_error("u and sigma are required");
-  HIPCHK(hipMemsetAsync(p->stress_sum, 0, 6 * sizeof(double), S(stream)));
+  HIPCHK(hipMemsetAsync(p->stress_sum, 0, 8 * STRESS_SLOTS * sizeof(double), S(stream)));
   int st = residual_impl(p, u, state_in, nullptr, nullptr, 0, p->stress_sum, S(stream));
   if (st) return st;
-  HIPCHK(hipMemcpyAsync(p->host_buf, p->stress_sum, 6 * sizeof(double), hipMemcpyDeviceToHost, S(stream)));
+  HIPCHK(hipMemcpyAsync(p->host_buf, p->stress_sum, 8 * STRESS_SLOTS * sizeof(double), hipMemcpyDeviceToHost, S(stream)));
   HIPCHK(hipStreamSynchronize(S(stream)));
-  for (int k = 0; k < 6; ++k) sigma[k] = p->host_buf[k] / p->volume;
+  for (int k = 0; k < 6; ++k) {
+    double v = 0;
+    for (int i = 0; i < STRESS_SLOTS; ++i) v += p->host_buf[8 * i + k];
+    sigma[k] = v / p->volume;
+  }
   return FE_OK;
 }
 

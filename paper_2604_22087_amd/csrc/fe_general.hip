@@ -407,7 +407,7 @@ __global__ __launch_bounds__(GBLOCK) void gen_elem_kernel(GenArgs g, ElemArgs a,
     if (tid < 6) {
       double v = 0;
       for (int w = 0; w < GBLOCK / 64; ++w) v += s_red[tid][w];
-      atomic_add(a.stress_sum + tid, v);
+      atomic_add(a.stress_sum + 8 * (blockIdx.x % STRESS_SLOTS) + tid, v);
     }
   }
 

@@ -812,7 +812,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   if (OP == OP_RESID && a.stress_sum && tid < 6) {
     double v = 0;
     for (int w = 0; w < EWAVES; ++w) v += s_red[tid][w];
-    atomic_add(a.stress_sum + tid, v);
+    atomic_add(a.stress_sum + 8 * (blockIdx.x % STRESS_SLOTS) + tid, v);
   }
 
   T* Y = static_cast<T*>(a.y);
