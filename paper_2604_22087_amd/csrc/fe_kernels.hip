@@ -522,7 +522,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     // J2 residual: history words are requested two points ahead and before the point's own stores.  Loads and
     // stores retire in one order, so words requested after stores wait for those as well (64^3 FP64
     // with state and tangent stored, 334 MB: 149 us at each point's turn, 126 one point ahead, 123 two)
-    const T* st_in = static_cast<const T*>(a.state_in);
+    // (elements without history only pass it through: nothing to read unless a trial state is written)
+    const T* st_in = a.state_out || pc.model == FE_J2 ? static_cast<const T*>(a.state_in) : nullptr;
     T hist[2][7];
     auto load_hist = [&](int q4) {
 #pragma unroll
