@@ -510,7 +510,10 @@ static int residual_impl(fe_problem* p, const void* u, const void* state_in, voi
     a.sur_salt = p->cap_salt++ * 0x9E3779B9u;
   }
   PROF(p, s, 2, launch_elem(p, OP_RESID, a, s));
-  if (a.store_tangent) p->lin_valid = true;
+  if (a.store_tangent) {
+    p->lin_valid = true;
+    p->lin_sur = a.sur_mode == SUR_CONSUME;
+  }
   return FE_OK;
 }
 

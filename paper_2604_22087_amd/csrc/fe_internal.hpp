@@ -200,6 +200,7 @@ struct fe_problem {
   uint8_t* mask = nullptr;    // [n_dof] or null
   void* tangent = nullptr;    // stored linearisation [6 (J2) or 10 (Neo-Hookean)][8][n_el], then TANGENT_PAD zeros
   bool lin_valid = false;
+  bool lin_sur = false;       // the stored linearisation may hold surrogate tangents (its residual consumed them)
   // solver workspace
   void* w_r = nullptr;
   void* w_p = nullptr;

@@ -862,9 +862,9 @@ static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const in
   const dim3 grid(elem_grid(p->n)), block(EBLOCK);
   ElemArgs b = a;
   b.law_mask = law_mask(p);
-  // J2 problems that may meet surrogate points (their stored tangents, or a surrogate / capture
+  // J2 problems that meet surrogate points (in the stored linearisation, or a surrogate / capture
   // mode of this residual) take the instance with those branches
-  const bool sur = p->model_set == MS_J2 && (OP == OP_RESID ? a.sur_mode != SUR_OFF : p->sur_map != nullptr);
+  const bool sur = p->model_set == MS_J2 && (OP == OP_RESID ? a.sur_mode != SUR_OFF : p->lin_sur);
   const int ms = OP != OP_VJP && sur ? (int)MS_SUR : p->model_set;
   if constexpr (sizeof(T) == 4 && OP != OP_VJP) {
     if (p->acc32) {
@@ -1651,7 +1651,7 @@ static void launch_tangent_csr_t(const fe_problem* p, T* v, int apply_bc, hipStr
   const TanArgs a = tan_args(p);
   const int np1 = p->n + 1;
   const int64_t tiles = (int64_t)((np1 + TS_X - 1) / TS_X) * ((np1 + TS_Y - 1) / TS_Y) * ((np1 + TS_Z - 1) / TS_Z);
-  const bool sur = p->model_set == MS_J2 && p->sur_map;
+  const bool sur = p->model_set == MS_J2 && p->lin_sur;
   if (sur || tiles < TS_MIN_TILES) {
     const dim3 grid((unsigned)((int64_t)np1 * np1 * ((np1 + TR_NODES - 1) / TR_NODES))), block(256);
     switch (p->model_set) {
