@@ -473,6 +473,8 @@ static int residual_impl(fe_problem* p, const void* u, const void* state_in, voi
       }
   }
   if (j2 && p->sur_W) {
+    // (the slots and tangents of the stored linearisation stay: a residual that stores none lists apart)
+    int* map = p->sur_map + (a.store_tangent ? 0 : 8 * p->n_el);
     // 1) list the points whose elastic trial is plastic, with their network inputs
     HIPCHK(hipMemsetAsync(p->sur_count, 0, 3 * sizeof(unsigned int), s));
     ElemArgs c = a;
@@ -481,7 +483,7 @@ static int residual_impl(fe_problem* p, const void* u, const void* state_in, voi
     c.store_tangent = 0;
     c.stress_sum = nullptr;
     c.sur_mode = SUR_CLASSIFY;
-    c.sur_map = p->sur_map;
+    c.sur_map = map;
     c.sur_count = p->sur_count;
     c.sur_cap = p->sur_cap;
     c.sur_x = p->sur_x;
@@ -493,7 +495,7 @@ static int residual_impl(fe_problem* p, const void* u, const void* state_in, voi
     if (int st = fe_mlp_forward(p->sur_W, p->sur_x, p->sur_y, p->sur_jac, nullptr, listed, s)) return st;
     // 3) residual with the network's stresses where the local check passes
     a.sur_mode = SUR_CONSUME;
-    a.sur_map = p->sur_map;
+    a.sur_map = map;
     a.sur_y = p->sur_y;
     a.sur_jac = p->sur_jac;
     a.sur_D = p->sur_D;
@@ -1434,7 +1436,7 @@ extern "C" int fe_set_surrogate(fe_problem* p, const float* W, double tol) {
       return FE_ERR_OOM;
     p->sur_cap = c;
   }
-  if (!p->sur_map && alloc((void**)&p->sur_map, sizeof(int) * 8 * p->n_el)) return FE_ERR_OOM;
+  if (!p->sur_map && alloc((void**)&p->sur_map, sizeof(int) * 16 * p->n_el)) return FE_ERR_OOM;
   if (!p->sur_count && alloc((void**)&p->sur_count, 4 * sizeof(unsigned int))) return FE_ERR_OOM;
   p->sur_W = W;
   p->sur_tol = tol;

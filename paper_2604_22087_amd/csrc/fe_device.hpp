@@ -366,6 +366,7 @@ __device__ __forceinline__ bool sur_consume(const T H[3][3], const T epn[6], T a
   S[1][2] = S[2][1] = sig[3];
   S[0][2] = S[2][0] = sig[4];
   S[0][1] = S[1][0] = sig[5];
+  if (!Dsym) return true;
   const T f = T(s_out) / T(s_in);
 #pragma unroll
   for (int i = 0; i < 6; ++i)

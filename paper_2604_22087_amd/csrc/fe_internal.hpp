@@ -246,7 +246,7 @@ struct fe_problem {
   double sur_tol = 0;
   int sur_full = 0;                 // fe_set_surrogate_tangent
   int64_t sur_cap = 0;
-  int* sur_map = nullptr;
+  int* sur_map = nullptr;           // [2][8][n_el]: slots of the stored linearisation; of a residual that stores none
   float* sur_x = nullptr;
   float* sur_y = nullptr;
   float* sur_jac = nullptr;

@@ -628,7 +628,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
                 bool accepted = false, fallback = false;
                 if (ptrial && slot >= 0) {
                   T Ss[3][3], eps2[6], al2;
-                  float* Dsym = static_cast<float*>(a.sur_D) + (int64_t)slot * 36;
+                  float* Dsym = a.store_tangent ? static_cast<float*>(a.sur_D) + (int64_t)slot * 36 : nullptr;
                   accepted = sur_consume(H, epn, an, Kb, Gs, sy, Hh, a.sur_y + (int64_t)slot * 6,
                                          a.sur_jac + (int64_t)slot * 36, a.sur_sin, a.sur_sout, a.sur_tol, tn,
                                          Ss, eps2, al2, Dsym, a.sur_full);
