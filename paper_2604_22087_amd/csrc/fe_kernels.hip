@@ -1,12 +1,13 @@
 // HIP kernels of libfe for gfx950 (MI355X).
 //
 // Element kernels work on bricks of TX x TY x TZ = 16 x 4 x 2 elements, two lanes per element
-// (lane half r takes the four Gauss points of reference layer z = r), 256 lanes per workgroup:
+// (lane half r takes the four Gauss points of reference layer z = r), 256 lanes per workgroup (or 16 x 4 x 4 with
+// one lane per element where that is faster, see one_lane_instance):
 //   1. the brick's (TX+1)(TY+1)(TZ+1) nodal values are staged in LDS, one wave per node row
 //      (the row's address and its place in the brick are scalars, the lane is the offset);
-//   2. each lane forms the displacement gradient at its 4 Gauss points by sum factorisation of
-//      the trilinear basis (an x-derivative only depends on the point's (y,z) position, so 24
-//      interpolated nodal differences give all 36 gradient entries);
+//   2. each lane forms the displacement gradient at its 4 Gauss points (8, one layer after the other) by sum
+//      factorisation of the trilinear basis (an x-derivative only depends on the point's (y,z) position, so
+//      24 interpolated nodal differences give all 36 gradient entries of a layer);
 //   3. the constitutive law turns each gradient into a stress, which is pushed back to the
 //      nodes by the transposed factorisation; the two halves of an element exchange their
 //      shares in registers (v_permlane32_swap), after which half r holds the four nodes k = r;
@@ -14,8 +15,8 @@
 //      nodes owned by the brick alone are stored, nodes on the brick's faces are
 //      added with hardware FP atomics.
 // What bounds them is latency more than bytes (staging loads, then a serial chain of points), so
-// the split aims at waves in flight: one lane per element needs 231 registers for its 72 table
-// entries (two waves per SIMD, the FP64 J2 residual spilled), half an element fits in 128.  Small
+// the split aims at waves in flight: in FP64 one lane per element needs 231 registers for its 72 table
+// entries (two waves per SIMD, the J2 residual spilled), half an element fits in 128.  Small
 // workgroups keep the phases of a CU's residents apart: CG launch at 64^3 FP64 with bricks of 4, 2
 // and 1 element layers 37.5, 34.0 and 50.1 us (halo 1.66, 1.99, 2.66 nodes staged per element).
 // Bricks are numbered so that consecutive bricks land on one XCD (workgroups
@@ -30,12 +31,15 @@ LaunchEvents& launch_events() {
   return ev;
 }
 
-constexpr int TX = 16, TY = 4, TZ = 2;
-constexpr int NX = TX + 1, NY = TY + 1, NZ = TZ + 1, NN = NX * NY * NZ;
-constexpr int EBLOCK = 2 * TX * TY * TZ;     // two lanes per element
+constexpr int TX = 16, TY = 4;
+constexpr int NX = TX + 1, NY = TY + 1;
+constexpr int EBLOCK = 256;                  // lanes of a workgroup
 constexpr int EWAVES = EBLOCK / 64;
-constexpr int ROWW = 3 * NX, NROWS = NY * NZ;  // a brick's node rows (along x): words per row, rows
-constexpr int ROW_IT = (NROWS + EWAVES - 1) / EWAVES;
+constexpr int ROWW = 3 * NX;                 // a brick's node rows (along x): words per row
+template <int LPE> struct Layout {           // LPE lanes per element
+  static constexpr int TZ = EBLOCK / (LPE * TX * TY), NZ = TZ + 1, NN = NX * NY * NZ;
+  static constexpr int NROWS = NY * NZ, ROW_IT = (NROWS + EWAVES - 1) / EWAVES;  // node rows, of one wave
+};
 constexpr int NACC = cg_slots_per_lane<EWAVES>();  // reduction slots per lane
 static_assert(6 * EWAVES >= 12, "room for the slot sums");
 static_assert(TX == 16 && TY == 4 && ROWW <= 64, "lane layout of the element kernel");
@@ -103,13 +107,14 @@ template <typename T> __device__ __forceinline__ void interp2(const T D[2][2], T
 // Gradient tables of the Gauss layer r of a nodal field u(k, j, i, c) (node (i,j,k) of the brick
 // element), times h: at point (p,q) of the layer h du_c/dx = x[q][c], h du_c/dy = y[p][c],
 // h du_c/dz = z[q][p][c].  w0, w1: the layer's weights of the nodes k = 0, 1.  Nodal differences
-// are taken first (a large rigid part cancels before anything is rounded).
+// are taken first (a large rigid part cancels before anything is rounded).  z is the same for both
+// layers (with_z: formed).
 template <typename T> struct HalfGrad {
   T x[2][3], y[2][3], z[2][2][3];
 };
 
 template <typename T, typename F>
-__device__ __forceinline__ void half_gradients(F&& u, T w0, T w1, HalfGrad<T>& g) {
+__device__ __forceinline__ void half_gradients(F&& u, T w0, T w1, HalfGrad<T>& g, bool with_z = true) {
   const T a = T(GA), b = T(GB);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -128,6 +133,7 @@ __device__ __forceinline__ void half_gradients(F&& u, T w0, T w1, HalfGrad<T>& g
     e1 = w0 * (U[0][1][1] - U[0][0][1]) + w1 * (U[1][1][1] - U[1][0][1]);
     g.y[0][c] = a * e0 + b * e1;
     g.y[1][c] = b * e0 + a * e1;
+    if (!with_z) continue;
     T D[2][2], G[2][2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -180,8 +186,36 @@ __device__ __forceinline__ void half_push_back(const HalfGrad<T>& s, T w0, T w1,
   }
 }
 
+// The same from the sums of both layers, held by one lane: sx[k], sy[k] the sums of s.x and s.y over the
+// layers with their weights of the nodes k, sz those of s.z; F[k][j][i][c].
+template <typename T>
+__device__ __forceinline__ void full_push_back(const T sx[2][2][3], const T sy[2][2][3], const T sz[2][2][3], T f,
+                                               T F[2][2][2][3]) {
+  const T a = T(GA), b = T(GB);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    T D[2][2], Z[2][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) D[q][p] = sz[q][p][c];
+    interp2(D, Z);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const T x0 = a * sx[k][0][c] + b * sx[k][1][c], x1 = b * sx[k][0][c] + a * sx[k][1][c];
+      const T y0 = a * sy[k][0][c] + b * sy[k][1][c], y1 = b * sy[k][0][c] + a * sy[k][1][c];
+      const T A[2][2] = {{-x0 - y0, x0 - y1}, {y0 - x1, x1 + y1}};
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) F[k][j][i][c] = f * (k ? A[j][i] + Z[j][i] : A[j][i] - Z[j][i]);
+    }
+  }
+}
+
 // The brick of a workgroup, its node rows and this lane's word of a row.
-struct Brick {
+template <int LPE> struct Brick {
+  static constexpr int TZ = Layout<LPE>::TZ, NROWS = Layout<LPE>::NROWS;
   int n, a0, b0, c0;
   int wave, lane;         // wave index (scalar), lane
   bool inx, ownx, privx;  // this word is in the mesh; owned / private as far as x decides it
@@ -238,10 +272,11 @@ struct Brick {
 // u_j goes to s_x (0 on constrained dofs, whose value goes to s_b), s_y is cleared.
 // (the node's three components sit in adjacent lanes of the row: node-block Jacobi fetches the
 // other two by lane exchange)
-template <typename T, bool BLK, typename Acc, typename Early>
-__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& br, double* sh, T* s_x,
+template <typename T, bool BLK, int LPE, typename Acc, typename Early>
+__device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick<LPE>& br, double* sh, T* s_x,
                                                Acc* s_y, T* s_b, unsigned& fixed, double& g, double& rr,
                                                Early&& early) {
+  constexpr int ROW_IT = Layout<LPE>::ROW_IT;
   // the previous launch's slot sums are requested before the staging loads (loads return in
   // order), so the scalar reduction overlaps the staging traffic
   double acc_v[NACC] = {};
@@ -274,7 +309,7 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
   for (int t = 0; t < ROW_IT; ++t) {
     ro[t] = wo[t] = so[t] = r2[t] = po[t] = xo[t] = T(0);
     mk[t] = 0;
-    const Brick::Row r = br.row(t);
+    const auto r = br.row(t);
     if (!r.live) continue;
     const int64_t dof = r.word + br.off;
     ro[t] = RO[dof];
@@ -307,7 +342,7 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
   const T alpha2 = T(ctl.alpha), beta2 = T(ctl.beta);
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
-    const Brick::Row r = br.row(t);
+    const auto r = br.row(t);
     if (!r.live) continue;
     int mkv = mk[t];
     asm volatile("" : "+v"(mkv));  // keeps the flag test here, after every load was issued
@@ -360,14 +395,15 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick& b
 // (waves per SIMD asked of the compiler: four without spills, but for the branches of surrogate points and
 // the FP64 J2 residual, where the history words in flight are worth more than a fourth wave: 141 us
 // at 64^3 with four waves and 13 spilled registers, 126 with three)
-template <typename T, int OP, int MS> constexpr int elem_waves() {
+template <typename T, int OP, int MS, int LPE> constexpr int elem_waves() {
+  if (LPE == 1 && (sizeof(T) == 8 || MS == MS_J2)) return 2;
   return MS == MS_SUR ? 2 : (OP == OP_RESID && MS == MS_J2 && sizeof(T) == 8 ? 3 : 4);
 }
 
 // ACC32 (FP32 problems only): the nodal sums accumulate in FP32 LDS as well; by default they
 // are formed in FP64 in both precisions.
-template <typename T, int OP, int MS, bool ACC32 = false>
-__global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_waves<T, OP, MS>()))) void elem_kernel(
+template <typename T, int OP, int MS, int LPE, bool ACC32 = false>
+__global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_waves<T, OP, MS, LPE>()))) void elem_kernel(
     ElemArgs a, const int* stop) {
   static_assert(!ACC32 || sizeof(T) == 4, "FP32 accumulation is an FP32-problem variant");
   using Acc = typename std::conditional<ACC32, float, double>::type;
@@ -375,6 +411,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   constexpr bool NEED_L = OP == OP_VJP;
   constexpr bool SUR = MS == MS_SUR, J2M = MS == MS_J2 || SUR;
   constexpr int NHB = sizeof(T) == 8 ? 1 : 2;  // register sets of Neo-Hookean words in flight
+  constexpr int TZ = Layout<LPE>::TZ, NN = Layout<LPE>::NN, ROW_IT = Layout<LPE>::ROW_IT;
+  constexpr int HALVES = 2 / LPE, NPT = 4 * HALVES;  // Gauss layers and points of a lane
   __shared__ T s_x[NN * 3];
   __shared__ Acc s_y[OP == OP_VJP ? 1 : NN * 3];  // nodal sums
   __shared__ T s_l[NEED_L ? NN * 3 : 1];
@@ -384,7 +422,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   // FP64 laws with stored words: the gradients of the points q = 1 wait here while those of q = 0
   // are worked on, then the stress sums of q = 0 do (18 registers less at the peak: no spills at
   // four waves per SIMD; one slot per lane, so no barrier)
-  constexpr bool PARK = sizeof(T) == 8 && MS != MS_LINEAR;
+  constexpr bool PARK = sizeof(T) == 8 && MS != MS_LINEAR && LPE == 2;
   __shared__ T s_park[PARK ? 9 : 1][PARK ? EBLOCK : 1];
 
   if (OP != OP_CG_APPLY && stop && *stop) return;  // (the CG launch tests its status after requesting its data)
@@ -398,25 +436,26 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
       if (a.stress_part && a.stress_sum && threadIdx.x < 6) a.stress_part[(int64_t)blockIdx.x * 6 + threadIdx.x] = 0.0;
     return;
   }
-  const Brick br(n, tile, ntx, nty);
+  const Brick<LPE> br(n, tile, ntx, nty);
   const int tid = threadIdx.x;
   const T* X = static_cast<const T*>(a.x);
-  // element of this lane: 32 of a wave's 64 lanes are two x-runs of the brick; upper half: r = 1
-  const int r = br.lane >> 5;
-  const int ex = br.lane & 15, ey = 2 * (br.wave & 1) + ((br.lane >> 4) & 1), ez = br.wave >> 1;
+  // element of this lane: with two lanes each, 32 of a wave's 64 lanes are two x-runs of the brick (upper half:
+  // r = 1); otherwise a wave holds the 16 x 4 elements of one layer
+  const int r = LPE == 2 ? br.lane >> 5 : 0;
+  const int ex = br.lane & 15, ey = LPE == 2 ? 2 * (br.wave & 1) + ((br.lane >> 4) & 1) : br.lane >> 4;
+  const int ez = LPE == 2 ? br.wave >> 1 : br.wave;
   const int ga = br.a0 + ex, gb = br.b0 + ey, gc = br.c0 + ez;
   const bool valid = ga < n && gb < n && gc < n;
   const int64_t e = valid ? (ga + (int64_t)n * (gb + (int64_t)n * gc)) : 0;
   const int64_t ne = a.n_el;
-  const int64_t e4 = e + 4 * r * ne;  // first point of this half in [..][8][n_el] arrays
+  const int64_t e4 = e + 4 * r * ne;  // first point of this lane in [..][8][n_el] arrays
   const T h = T(a.h);
-  const T w0 = r ? T(GB) : T(GA), w1 = r ? T(GA) : T(GB);
   stage_phases(a.mat, s_mat, tid);
   // the element's phase is requested before the staging loads; the operator's first stored-
   // tangent word of every Gauss point right after them (both arrive before they are used)
   const int ph = valid ? (int)a.phase[e] : 0;
   const T* tang_c = static_cast<const T*>(a.tangent);
-  T tq0[4];
+  T tq0[NPT];
   // FP32 Neo-Hookean K u: the first point's ten words as well (64^3 32.2 -> 30.4 us, 80^3 63.5 -> 62.0; the
   // CG launch, whose staging is longer, lost by it: 128^3 292 -> 300)
   constexpr bool NH_EARLY = MS == MS_NH && OP == OP_APPLY && sizeof(T) == 4;
@@ -430,7 +469,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     if (APPLY_LIKE && J2M) {
       const bool j2 = valid && ((a.law_mask >> ph) & 1u);
 #pragma unroll
-      for (int qq = 0; qq < 4; ++qq) tq0[qq] = j2 ? tang_c[e4 + qq * ne] : T(-1);
+      for (int qq = 0; qq < NPT; ++qq) tq0[qq] = j2 ? tang_c[e4 + qq * ne] : T(-1);
     }
   };
 
@@ -441,8 +480,8 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     if (blockIdx.x == 0)
       for (int i = tid; i < 3 * CGS_SLOTS; i += EBLOCK) a.cg_acc_zero[i] = 0.0;  // slots of launch j+1
     // (one instance per preconditioner form, so each staging path is branch-free)
-    const bool go = a.cg_block ? cg_stage_brick<T, true>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
-                               : cg_stage_brick<T, false>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
+    const bool go = a.cg_block ? cg_stage_brick<T, true, LPE>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early)
+                               : cg_stage_brick<T, false, LPE>(a, br, &s_red[0][0], s_x, s_y, s_b, fixed, cg_g, cg_rr, early);
     if (!go) return;
     cg_g = wave_sum_last(cg_g);
     cg_rr = wave_sum_last(cg_rr);
@@ -459,7 +498,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     for (int t = 0; t < ROW_IT; ++t) {
       v[t] = vl[t] = T(0);
       mk[t] = 0;
-      const Brick::Row rw = br.row(t);
+      const auto rw = br.row(t);
       if (!rw.live) continue;
       const int64_t dof = rw.word + br.off;
       v[t] = X[dof];
@@ -469,7 +508,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     early();
 #pragma unroll
     for (int t = 0; t < ROW_IT; ++t) {
-      const Brick::Row rw = br.row(t);
+      const auto rw = br.row(t);
       if (!rw.live) continue;
       int mkv = mk[t];
       asm volatile("" : "+v"(mkv));  // (the flag test stays here, see cg_stage_brick)
@@ -484,7 +523,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   }
   __syncthreads();
 
-  T F[2][2][3];  // nodal forces of the nodes (i, j, k = r), [j][i][c]
+  T F[HALVES][2][2][3];  // nodal forces of the nodes (i, j, k), [k][j][i][c]; two lanes per element: k = r alone
   double ssum[6] = {0, 0, 0, 0, 0, 0};
   const int s0 = 3 * (ex + NX * (ey + NY * ez));  // LDS word of the element's node (0,0,0)
   double pq = 0;
@@ -494,14 +533,24 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     const T sc = (a.scale && OP != OP_VJP) ? static_cast<const T*>(a.scale)[e] : T(1);
 
     // J2 operator: the first stored-tangent word of every Gauss point arrived with the staging
-    // (tq0); the five plastic-point words are requested PF Gauss points ahead of their use.  An
+    // (tq0); the five plastic-point words are requested PF Gauss points ahead of their use.  In FP64 an
     // elastic point reads the zero word behind the array instead: a branch around the loads costs
-    // the FP64 instance 30 spilled registers, and its own words would be traffic
+    // that instance 30 spilled registers, and its own words would be traffic.  FP32 has the registers
+    // for the branch and a second point ahead (K u 80^3 35.4 -> 34.2 us, CG 50.4 -> 48.6)
     const int64_t zero_at = J2_TANGENT_WORDS * 8 * ne;
-    constexpr int PF = 1;
+    constexpr int PF = sizeof(T) == 8 ? 1 : 2;
     T pw[PF + 1][5];
     auto load_pw = [&](int q4, T* w) {
       const bool pl = tq0[q4] >= 0;
+      if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) w[k] = 0;
+        if (pl) {
+#pragma unroll
+          for (int k = 0; k < 5; ++k) w[k] = tang_c[e4 + ((k + 1) * 8 + q4) * ne];
+        }
+        return;
+      }
       const T* at = tang_c + (pl ? e4 + q4 * ne : zero_at);
       const int64_t st = pl ? 8 * ne : 0;
 #pragma unroll
@@ -535,198 +584,219 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     }
 
     HalfGrad<T> g, s;  // gradients (times h), stress sums
-    half_gradients<T>([&](int k, int j, int i, int c) { return s_x[s0 + 3 * (i + NX * (j + NY * k)) + c]; }, w0, w1, g);
-    if constexpr (PARK) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        s_park[c][tid] = g.x[1][c];
-        s_park[3 + c][tid] = g.z[1][0][c];
-        s_park[6 + c][tid] = g.z[1][1][c];
-      }
-      asm volatile("" ::: "memory");  // (the values are to be read back, not kept)
-    }
-    // the operators are linear in the gradient, so 1/h goes into the final factor there
-    const T inv_h = APPLY_LIKE ? T(1) : T(1.0 / a.h);
-
+    T fx[2][2][3], fy[2][2][3], fz[2][2][3];  // (one lane per element: sums of both layers, see full_push_back)
     T* st_out = static_cast<T*>(a.state_out);
     T* tang = static_cast<T*>(a.tangent);
-
+    // the operators are linear in the gradient, so 1/h goes into the final factor there
+    const T inv_h = APPLY_LIKE ? T(1) : T(1.0 / a.h);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int hh = 0; hh < HALVES; ++hh) {
+      const int layer = LPE == 2 ? r : hh;
+      const T w0 = layer ? T(GB) : T(GA), w1 = layer ? T(GA) : T(GB);
+      half_gradients<T>([&](int k, int j, int i, int c) { return s_x[s0 + 3 * (i + NX * (j + NY * k)) + c]; }, w0, w1, g,
+                        hh == 0);
       if constexpr (PARK) {
-        if (q == 1) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          s_park[c][tid] = g.x[1][c];
+          s_park[3 + c][tid] = g.z[1][0][c];
+          s_park[6 + c][tid] = g.z[1][1][c];
+        }
+        asm volatile("" ::: "memory");  // (the values are to be read back, not kept)
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if constexpr (PARK) {
+          if (q == 1) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              g.x[1][c] = s_park[c][tid];
+              g.z[1][0][c] = s_park[3 + c][tid];
+              g.z[1][1][c] = s_park[6 + c][tid];
+              s_park[c][tid] = s.x[0][c];
+              s_park[3 + c][tid] = s.z[0][0][c];
+              s_park[6 + c][tid] = s.z[0][1][c];
+            }
+            asm volatile("" ::: "memory");
+          }
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int q4 = p + 2 * q + 4 * hh;
+          if (APPLY_LIKE && J2M && q4 + PF < NPT) load_pw(q4 + PF, pw[(q4 + PF) % (PF + 1)]);
+          if (APPLY_LIKE && MS == MS_NH && NHB == 2 && q4 < NPT - 1) load_nh(q4 + 1, nw[(q4 + 1) % NHB]);
+          T H[3][3], S[3][3];
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            g.x[1][c] = s_park[c][tid];
-            g.z[1][0][c] = s_park[3 + c][tid];
-            g.z[1][1][c] = s_park[6 + c][tid];
-            s_park[c][tid] = s.x[0][c];
-            s_park[3 + c][tid] = s.z[0][0][c];
-            s_park[6 + c][tid] = s.z[0][1][c];
+            H[c][0] = APPLY_LIKE ? g.x[q][c] : g.x[q][c] * inv_h;
+            H[c][1] = APPLY_LIKE ? g.y[p][c] : g.y[p][c] * inv_h;
+            H[c][2] = APPLY_LIKE ? g.z[q][p][c] : g.z[q][p][c] * inv_h;
           }
-          asm volatile("" ::: "memory");
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int q4 = p + 2 * q;
-        if (APPLY_LIKE && J2M && q4 + PF < 4) load_pw(q4 + PF, pw[(q4 + PF) % (PF + 1)]);
-        if (APPLY_LIKE && MS == MS_NH && NHB == 2 && q4 < 3) load_nh(q4 + 1, nw[(q4 + 1) % NHB]);
-        T H[3][3], S[3][3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          H[c][0] = APPLY_LIKE ? g.x[q][c] : g.x[q][c] * inv_h;
-          H[c][1] = APPLY_LIKE ? g.y[p][c] : g.y[p][c] * inv_h;
-          H[c][2] = APPLY_LIKE ? g.z[q][p][c] : g.z[q][p][c] * inv_h;
-        }
-        if constexpr (APPLY_LIKE && J2M) {
-          // one path for all points: a linear phase is an elastic point (tq0 = -1, N = 0)
-          const T K = T(pc.K) * sc, G = T(pc.G) * sc;
-          if (SUR && tq0[q4] < T(-1.5)) {  // surrogate tangent of this point
-            const int slot = a.sur_map[e4 + q4 * ne];
-            general_apply(H, static_cast<const float*>(a.sur_D) + (int64_t)slot * 36, S);
-          } else {
-            T lp, mp, beta;
-            const T(&w)[5] = pw[q4 % (PF + 1)];
-            const T N[6] = {w[0], w[1], -(w[0] + w[1]), w[2], w[3], w[4]};
-            j2_tangent_coeffs(tq0[q4], K, G, T(pc.H), lp, mp, beta);
-            j2_apply(H, lp, mp, beta, N, S);
-          }
-        } else if constexpr (OP == OP_RESID && J2M) {
-          if (pc.model == FE_J2) {
-            const T Kb = T(pc.K) * sc, Gs = T(pc.G) * sc, sy = T(pc.sy), Hh = T(pc.H);
-            T ep[6], al, tn[6];
-            T epn[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) epn[k] = hist[q4 & 1][k];
-            const T an = hist[q4 & 1][6];
-            j2_update(H, epn, an, Kb, Gs, sy, Hh, S, ep, al, tn);
-            if (SUR) {
-              const int64_t pidx = e4 + q4 * ne;
-              const bool ptrial = tn[0] >= 0;  // elastic trial is plastic: the surrogate's domain
-              if (a.sur_mode == SUR_CAPTURE) {
-                const bool keep = ptrial && (((unsigned)pidx * 2654435761u + a.sur_salt) % a.sur_stride == 0);
-                const unsigned slot = wave_append(a.sur_count, keep);
-                if (keep && slot < a.sur_cap) {
-                  sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
-                  const T rt2 = T(1.41421356237309504880), is = T(1) / T(a.sur_sout);
-                  float* yo = a.sur_y + (int64_t)slot * 6;
-                  yo[0] = float(S[0][0] * is);
-                  yo[1] = float(S[1][1] * is);
-                  yo[2] = float(S[2][2] * is);
-                  yo[3] = float(S[1][2] * rt2 * is);
-                  yo[4] = float(S[0][2] * rt2 * is);
-                  yo[5] = float(S[0][1] * rt2 * is);
-                }
-              } else if (a.sur_mode == SUR_CLASSIFY) {
-                const unsigned slot = wave_append(a.sur_count, ptrial);
-                const bool listed = ptrial && slot < a.sur_cap;
-                a.sur_map[pidx] = listed ? (int)slot : -1;
-                if (listed) sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
-              } else if (a.sur_mode == SUR_CONSUME) {
-                const int slot = a.sur_map[pidx];
-                bool accepted = false, fallback = false;
-                if (ptrial && slot >= 0) {
-                  T Ss[3][3], eps2[6], al2;
-                  float* Dsym = a.store_tangent ? static_cast<float*>(a.sur_D) + (int64_t)slot * 36 : nullptr;
-                  accepted = sur_consume(H, epn, an, Kb, Gs, sy, Hh, a.sur_y + (int64_t)slot * 6,
-                                         a.sur_jac + (int64_t)slot * 36, a.sur_sin, a.sur_sout, a.sur_tol, tn,
-                                         Ss, eps2, al2, Dsym, a.sur_full);
-                  fallback = !accepted;
-                  if (accepted) {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i)
-#pragma unroll
-                      for (int j = 0; j < 3; ++j) S[i][j] = Ss[i][j];
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) ep[k] = eps2[k];
-                    al = al2;
-                    tn[0] = T(SUR_FLAG);
-                  }
-                }
-                wave_count(a.sur_stats, accepted);
-                wave_count(a.sur_stats + 1, fallback);
-              }
-            }
-            if (q4 < 2) load_hist(q4 + 2);
-            if (st_out) {
-#pragma unroll
-              for (int k = 0; k < 6; ++k) st_out[e4 + (k * 8 + q4) * ne] = ep[k];
-              st_out[e4 + (6 * 8 + q4) * ne] = al;
-            }
-            if (a.store_tangent) {
-#pragma unroll
-              for (int k = 0; k < 6; ++k) tang[e4 + (k * 8 + q4) * ne] = tn[k];
-            }
-          } else {
-            hooke(H, T(pc.lam) * sc, T(pc.mu) * sc, S);
-            T keep[7];
-#pragma unroll
-            for (int k = 0; k < 7; ++k) keep[k] = hist[q4 & 1][k];
-            if (q4 < 2) load_hist(q4 + 2);
-            if (st_out) {  // non-J2 phase: state passes through
-#pragma unroll
-              for (int k = 0; k < 7; ++k) st_out[e4 + (k * 8 + q4) * ne] = keep[k];
-            }
-          }
-        } else {
-          const T lam = T(pc.lam) * sc, mu = T(pc.mu) * sc;
-          if (MS == MS_NH && pc.model == FE_NEOHOOKE) {
-            if constexpr (APPLY_LIKE) {
-              const T(&w)[10] = nw[q4 % NHB];
-              const T FiT[3][3] = {{w[0], w[1], w[2]}, {w[3], w[4], w[5]}, {w[6], w[7], w[8]}};
-              nh_apply(H, FiT, w[9], lam, mu, S);
+          if constexpr (APPLY_LIKE && J2M) {
+            // one path for all points: a linear phase is an elastic point (tq0 = -1, N = 0)
+            const T K = T(pc.K) * sc, G = T(pc.G) * sc;
+            if (SUR && tq0[q4] < T(-1.5)) {  // surrogate tangent of this point
+              const int slot = a.sur_map[e4 + q4 * ne];
+              general_apply(H, static_cast<const float*>(a.sur_D) + (int64_t)slot * 36, S);
             } else {
-              T FiT[3][3], lnJ;
-              if (!nh_kin(H, FiT, lnJ) && a.flags) atomicOr(a.flags, 1);
-              nh_stress(H, FiT, lnJ, lam, mu, S);
-              if (OP == OP_RESID && a.store_tangent) {
+              T lp, mp, beta;
+              const T(&w)[5] = pw[q4 % (PF + 1)];
+              const T N[6] = {w[0], w[1], -(w[0] + w[1]), w[2], w[3], w[4]};
+              j2_tangent_coeffs(tq0[q4], K, G, T(pc.H), lp, mp, beta);
+              j2_apply(H, lp, mp, beta, N, S);
+            }
+          } else if constexpr (OP == OP_RESID && J2M) {
+            if (pc.model == FE_J2) {
+              const T Kb = T(pc.K) * sc, Gs = T(pc.G) * sc, sy = T(pc.sy), Hh = T(pc.H);
+              T ep[6], al, tn[6];
+              T epn[6];
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+              for (int k = 0; k < 6; ++k) epn[k] = hist[q4 & 1][k];
+              const T an = hist[q4 & 1][6];
+              j2_update(H, epn, an, Kb, Gs, sy, Hh, S, ep, al, tn);
+              if (SUR) {
+                const int64_t pidx = e4 + q4 * ne;
+                const bool ptrial = tn[0] >= 0;  // elastic trial is plastic: the surrogate's domain
+                if (a.sur_mode == SUR_CAPTURE) {
+                  const bool keep = ptrial && (((unsigned)pidx * 2654435761u + a.sur_salt) % a.sur_stride == 0);
+                  const unsigned slot = wave_append(a.sur_count, keep);
+                  if (keep && slot < a.sur_cap) {
+                    sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
+                    const T rt2 = T(1.41421356237309504880), is = T(1) / T(a.sur_sout);
+                    float* yo = a.sur_y + (int64_t)slot * 6;
+                    yo[0] = float(S[0][0] * is);
+                    yo[1] = float(S[1][1] * is);
+                    yo[2] = float(S[2][2] * is);
+                    yo[3] = float(S[1][2] * rt2 * is);
+                    yo[4] = float(S[0][2] * rt2 * is);
+                    yo[5] = float(S[0][1] * rt2 * is);
+                  }
+                } else if (a.sur_mode == SUR_CLASSIFY) {
+                  const unsigned slot = wave_append(a.sur_count, ptrial);
+                  const bool listed = ptrial && slot < a.sur_cap;
+                  a.sur_map[pidx] = listed ? (int)slot : -1;
+                  if (listed) sur_inputs(H, epn, an, a.sur_sin, a.sur_x + (int64_t)slot * 13);
+                } else if (a.sur_mode == SUR_CONSUME) {
+                  const int slot = a.sur_map[pidx];
+                  bool accepted = false, fallback = false;
+                  if (ptrial && slot >= 0) {
+                    T Ss[3][3], eps2[6], al2;
+                    float* Dsym = a.store_tangent ? static_cast<float*>(a.sur_D) + (int64_t)slot * 36 : nullptr;
+                    accepted = sur_consume(H, epn, an, Kb, Gs, sy, Hh, a.sur_y + (int64_t)slot * 6,
+                                           a.sur_jac + (int64_t)slot * 36, a.sur_sin, a.sur_sout, a.sur_tol, tn,
+                                           Ss, eps2, al2, Dsym, a.sur_full);
+                    fallback = !accepted;
+                    if (accepted) {
 #pragma unroll
-                  for (int j = 0; j < 3; ++j) tang[e4 + ((3 * i + j) * 8 + q4) * ne] = FiT[i][j];
-                tang[e4 + (9 * 8 + q4) * ne] = lnJ;
+                      for (int i = 0; i < 3; ++i)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) S[i][j] = Ss[i][j];
+#pragma unroll
+                      for (int k = 0; k < 6; ++k) ep[k] = eps2[k];
+                      al = al2;
+                      tn[0] = T(SUR_FLAG);
+                    }
+                  }
+                  wave_count(a.sur_stats, accepted);
+                  wave_count(a.sur_stats + 1, fallback);
+                }
+              }
+              if (q4 < NPT - 2) load_hist(q4 + 2);
+              if (st_out) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) st_out[e4 + (k * 8 + q4) * ne] = ep[k];
+                st_out[e4 + (6 * 8 + q4) * ne] = al;
+              }
+              if (a.store_tangent) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) tang[e4 + (k * 8 + q4) * ne] = tn[k];
+              }
+            } else {
+              hooke(H, T(pc.lam) * sc, T(pc.mu) * sc, S);
+              T keep[7];
+#pragma unroll
+              for (int k = 0; k < 7; ++k) keep[k] = hist[q4 & 1][k];
+              if (q4 < NPT - 2) load_hist(q4 + 2);
+              if (st_out) {  // non-J2 phase: state passes through
+#pragma unroll
+                for (int k = 0; k < 7; ++k) st_out[e4 + (k * 8 + q4) * ne] = keep[k];
               }
             }
           } else {
-            hooke(H, lam, mu, S);
+            const T lam = T(pc.lam) * sc, mu = T(pc.mu) * sc;
+            if (MS == MS_NH && pc.model == FE_NEOHOOKE) {
+              if constexpr (APPLY_LIKE) {
+                const T(&w)[10] = nw[q4 % NHB];
+                const T FiT[3][3] = {{w[0], w[1], w[2]}, {w[3], w[4], w[5]}, {w[6], w[7], w[8]}};
+                nh_apply(H, FiT, w[9], lam, mu, S);
+              } else {
+                T FiT[3][3], lnJ;
+                if (!nh_kin(H, FiT, lnJ) && a.flags) atomicOr(a.flags, 1);
+                nh_stress(H, FiT, lnJ, lam, mu, S);
+                if (OP == OP_RESID && a.store_tangent) {
+#pragma unroll
+                  for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) tang[e4 + ((3 * i + j) * 8 + q4) * ne] = FiT[i][j];
+                  tang[e4 + (9 * 8 + q4) * ne] = lnJ;
+                }
+              }
+            } else {
+              hooke(H, lam, mu, S);
+            }
+            if (APPLY_LIKE && MS == MS_NH && NHB == 1 && q4 < NPT - 1) load_nh(q4 + 1, nw[0]);
           }
-          if (APPLY_LIKE && MS == MS_NH && NHB == 1 && q4 < 3) load_nh(q4 + 1, nw[0]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            s.x[q][c] = p == 0 ? S[c][0] : s.x[q][c] + S[c][0];
+            s.y[p][c] = q == 0 ? S[c][1] : s.y[p][c] + S[c][1];
+            s.z[q][p][c] = S[c][2];
+          }
+          if (OP == OP_RESID && sizeof(T) == 4 && a.stress_sum) {
+            ssum[0] += S[0][0];
+            ssum[1] += S[1][1];
+            ssum[2] += S[2][2];
+            ssum[3] += S[1][2];
+            ssum[4] += S[0][2];
+            ssum[5] += S[0][1];
+          }
         }
+      }
+      if constexpr (PARK) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          s.x[q][c] = p == 0 ? S[c][0] : s.x[q][c] + S[c][0];
-          s.y[p][c] = q == 0 ? S[c][1] : s.y[p][c] + S[c][1];
-          s.z[q][p][c] = S[c][2];
-        }
-        if (OP == OP_RESID && sizeof(T) == 4 && a.stress_sum) {
-          ssum[0] += S[0][0];
-          ssum[1] += S[1][1];
-          ssum[2] += S[2][2];
-          ssum[3] += S[1][2];
-          ssum[4] += S[0][2];
-          ssum[5] += S[0][1];
+          s.x[0][c] = s_park[c][tid];
+          s.z[0][0][c] = s_park[3 + c][tid];
+          s.z[0][1][c] = s_park[6 + c][tid];
         }
       }
-    }
-    if constexpr (PARK) {
+      if (OP == OP_RESID && sizeof(T) == 8 && a.stress_sum) {  // the point sums hold every stress entry
+        ssum[0] += s.x[0][0] + s.x[1][0];
+        ssum[1] += s.y[0][1] + s.y[1][1];
+        ssum[2] += (s.z[0][0][2] + s.z[0][1][2]) + (s.z[1][0][2] + s.z[1][1][2]);
+        ssum[3] += (s.z[0][0][1] + s.z[0][1][1]) + (s.z[1][0][1] + s.z[1][1][1]);
+        ssum[4] += (s.z[0][0][0] + s.z[0][1][0]) + (s.z[1][0][0] + s.z[1][1][0]);
+        ssum[5] += s.y[0][0] + s.y[1][0];
+      }
+      // w_q detJ = h^3/8, physical derivative factor 1/h (and the operators' gradient factor 1/h)
+      const T f = APPLY_LIKE ? T(0.125) * h : T(0.125) * h * h;
+      if constexpr (LPE == 2) {
+        half_push_back(s, w0, w1, f, F[0]);
+      } else {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        s.x[0][c] = s_park[c][tid];
-        s.z[0][0][c] = s_park[3 + c][tid];
-        s.z[0][1][c] = s_park[6 + c][tid];
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            fx[0][m][c] = hh == 0 ? w0 * s.x[m][c] : fx[0][m][c] + w0 * s.x[m][c];
+            fx[1][m][c] = hh == 0 ? w1 * s.x[m][c] : fx[1][m][c] + w1 * s.x[m][c];
+            fy[0][m][c] = hh == 0 ? w0 * s.y[m][c] : fy[0][m][c] + w0 * s.y[m][c];
+            fy[1][m][c] = hh == 0 ? w1 * s.y[m][c] : fy[1][m][c] + w1 * s.y[m][c];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) fz[m][p][c] = hh == 0 ? s.z[m][p][c] : fz[m][p][c] + s.z[m][p][c];
+          }
+        if (hh == 1) full_push_back(fx, fy, fz, f, F);
       }
     }
-    if (OP == OP_RESID && sizeof(T) == 8 && a.stress_sum) {  // the point sums hold every stress entry
-      ssum[0] = s.x[0][0] + s.x[1][0];
-      ssum[1] = s.y[0][1] + s.y[1][1];
-      ssum[2] = (s.z[0][0][2] + s.z[0][1][2]) + (s.z[1][0][2] + s.z[1][1][2]);
-      ssum[3] = (s.z[0][0][1] + s.z[0][1][1]) + (s.z[1][0][1] + s.z[1][1][1]);
-      ssum[4] = (s.z[0][0][0] + s.z[0][1][0]) + (s.z[1][0][0] + s.z[1][1][0]);
-      ssum[5] = s.y[0][0] + s.y[1][0];
-    }
-    // w_q detJ = h^3/8, physical derivative factor 1/h (and the operators' gradient factor 1/h)
-    half_push_back(s, w0, w1, APPLY_LIKE ? T(0.125) * h : T(0.125) * h * h, F);
   }
 
   if (OP == OP_RESID && a.stress_sum) {
@@ -745,11 +815,13 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
       if (valid) {
         T* E = static_cast<T*>(a.elf);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int k = 0; k < HALVES; ++k)
 #pragma unroll
-          for (int i = 0; i < 2; ++i)
+          for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) E[(int64_t)(3 * (i + 2 * j + 4 * r) + c) * ne + e] = F[j][i][c];
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) E[(int64_t)(3 * (i + 2 * j + 4 * (r + k)) + c) * ne + e] = F[k][j][i][c];
       }
       if (OP == OP_RESID && a.stress_sum) {
         __syncthreads();
@@ -778,14 +850,16 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
 #pragma unroll
             for (int c = 0; c < 3; ++c) lm[c] += (double)s_l[s0 + 3 * (i + NX * (j + NY * k)) + c];
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int k = 0; k < HALVES; ++k)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
-            d += (double)F[j][i][c] * ((double)s_l[s0 + 3 * (i + NX * (j + NY * r)) + c] - 0.125 * lm[c]);
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+              d += (double)F[k][j][i][c] * ((double)s_l[s0 + 3 * (i + NX * (j + NY * (r + k))) + c] - 0.125 * lm[c]);
     }
-    d += __shfl_xor(d, 32, 64);
+    if (LPE == 2) d += __shfl_xor(d, 32, 64);
     if (valid && r == 0) static_cast<T*>(a.out_el)[e] = T(d);
     return;
   }
@@ -798,15 +872,17 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
     // CG: element part of p.Ap = sum_e p_e . K_e p_e (p masked on constrained dofs)
     const int sr = s0 + 3 * NX * NY * r;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int k = 0; k < HALVES; ++k)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const int w = sr + 3 * (i + NX * j) + c;
-          if (OP == OP_CG_APPLY) pq += (double)F[j][i][c] * (double)s_x[w];
-          __hip_atomic_fetch_add(&s_y[w], (Acc)F[j][i][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const int w = sr + 3 * (i + NX * (j + NY * k)) + c;
+            if (OP == OP_CG_APPLY) pq += (double)F[k][j][i][c] * (double)s_x[w];
+            __hip_atomic_fetch_add(&s_y[w], (Acc)F[k][j][i][c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
   }
   __syncthreads();
 
@@ -820,7 +896,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   if (!Y) return;
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
-    const Brick::Row rw = br.row(t);
+    const auto rw = br.row(t);
     if (!rw.live || !br.inx) continue;
     const int i = rw.row * ROWW + br.lane;
     const int64_t dof = rw.word + br.off;
@@ -852,14 +928,68 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   }
 }
 
-static int elem_grid(int n) {
-  const int nb = ((n + TX - 1) / TX) * ((n + TY - 1) / TY) * ((n + TZ - 1) / TZ);
+static int elem_grid(int n, int lpe = 2) {
+  const int tz = lpe == 1 ? Layout<1>::TZ : Layout<2>::TZ;
+  const int nb = ((n + TX - 1) / TX) * ((n + TY - 1) / TY) * ((n + tz - 1) / tz);
   return 8 * ((nb + 7) / 8);
+}
+
+// One lane per element (bricks of 16 x 4 x 4, each lane both Gauss layers) does less work in all: the node
+// differences, the z gradients and the push-back serve both layers, and fewer halo nodes are staged.  Two lanes per
+// element (16 x 4 x 2) have half the chain and half the registers, which wins while the mesh is small and
+// wherever FP64 would spill.  Which instances have the one-lane form, and where it takes over (us, one / two
+// lanes per element):
+//   CG, FP32: where its bricks need fewer rounds (one round: all workgroups of the instance that the chip holds at
+//     once).  Linear 48^3 14.4 / 14.4, 52^3 17.0 / 19.0, 64^3 20.0 / 22.9, 128^3 130 / 145; Neo-Hookean 64^3
+//     30.8 / 33.2, 128^3 264 / 290; J2 (three of its waves per SIMD against four) 48^3 15.5 / 15.6, 52^3 20.3 / 22.6,
+//     64^3 (two rounds each) 29.8 / 27.3, 80^3 47.1 / 48.6, 128^3 227 / 249
+//   K u, FP32 linear and Neo-Hookean: more than 2048 bricks.  Linear 80^3 25.2 / 24.7, 96^3 35.4 / 37.0, 128^3
+//     70.0 / 76.0; Neo-Hookean 80^3 45.4 / 44.3, 96^3 93 / 95, 128^3 207 / 220
+//   K u, FP64 linear: 1024 bricks.  56^3 17.8 / 18.0, 64^3 19.2 / 20.6, 128^3 100 / 109
+//   residual, FP64 linear: fewer rounds.  52^3 14.5 / 16.2, 64^3 (two each) 20.6 / 20.0, 80^3 32.0 / 34.3,
+//     128^3 108 / 116
+//   VJP: more than a brick per CU.  FP64 linear 48^3 7.9 / 8.5, 128^3 63 / 91; FP64 Neo-Hookean 45^3
+//     13.7 / 15.4, 128^3 168 / 186; FP32 linear 45^3 7.8 / 7.2, 64^3 8.5 / 10.5, 128^3 46 / 57
+template <typename T, int OP, int MS> constexpr bool one_lane_instance() {
+  if (OP == OP_CG_APPLY) return sizeof(T) == 4 && MS != MS_SUR;
+  if (OP == OP_APPLY) return sizeof(T) == 4 ? MS == MS_LINEAR || MS == MS_NH : MS == MS_LINEAR;
+  if (OP == OP_RESID) return sizeof(T) == 8 && MS == MS_LINEAR;
+  return MS == MS_LINEAR || MS == MS_NH;
+}
+
+// Workgroups of an instance that the chip holds at once (a property of the code, looked up once).
+constexpr int CUS = 256;
+template <auto Kernel> static int resident_workgroups() {
+  static const int n = [] {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, Kernel, EBLOCK, 0) != hipSuccess || per_cu < 1) per_cu = 4;
+    return CUS * per_cu;
+  }();
+  return n;
+}
+
+template <typename T, int OP, int MS, bool ACC32> static bool use_one_lane(const fe_problem* p) {
+  if (p->deterministic) return false;  // (its stress partials are laid out for the other form)
+  const int one = elem_grid(p->n, 1), two = elem_grid(p->n, 2);
+  if (OP == OP_APPLY) return sizeof(T) == 4 ? one > 8 * CUS : one >= 4 * CUS;
+  if (OP == OP_VJP) return one > CUS;
+  const int r1 = resident_workgroups<&elem_kernel<T, OP, MS, 1, ACC32>>();
+  const int r2 = resident_workgroups<&elem_kernel<T, OP, MS, 2, ACC32>>();
+  return (one + r1 - 1) / r1 < (two + r2 - 1) / r2;
+}
+
+template <typename T, int OP, int MS, bool ACC32 = false>
+static void launch_elem_ms(const fe_problem* p, const ElemArgs& b, const int* stop, hipStream_t s) {
+  if constexpr (one_lane_instance<T, OP, MS>())
+    if (use_one_lane<T, OP, MS, ACC32>(p)) {
+      timed_launch((elem_kernel<T, OP, MS, 1, ACC32>), dim3(elem_grid(p->n, 1)), dim3(EBLOCK), 0, s, b, stop);
+      return;
+    }
+  timed_launch((elem_kernel<T, OP, MS, 2, ACC32>), dim3(elem_grid(p->n)), dim3(EBLOCK), 0, s, b, stop);
 }
 
 template <typename T, int OP>
 static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const int* stop, hipStream_t s) {
-  const dim3 grid(elem_grid(p->n)), block(EBLOCK);
   ElemArgs b = a;
   b.law_mask = law_mask(p);
   // J2 problems that meet surrogate points (in the stored linearisation, or a surrogate / capture
@@ -869,21 +999,21 @@ static hipError_t launch_elem_t(const fe_problem* p, const ElemArgs& a, const in
   if constexpr (sizeof(T) == 4 && OP != OP_VJP) {
     if (p->acc32) {
       switch (ms) {
-        case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2, true>), grid, block, 0, s, b, stop); break;
-        case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH, true>), grid, block, 0, s, b, stop); break;
-        case MS_SUR: timed_launch((elem_kernel<T, OP, MS_SUR, true>), grid, block, 0, s, b, stop); break;
-        default: timed_launch((elem_kernel<T, OP, MS_LINEAR, true>), grid, block, 0, s, b, stop);
+        case MS_J2: launch_elem_ms<T, OP, MS_J2, true>(p, b, stop, s); break;
+        case MS_NH: launch_elem_ms<T, OP, MS_NH, true>(p, b, stop, s); break;
+        case MS_SUR: launch_elem_ms<T, OP, MS_SUR, true>(p, b, stop, s); break;
+        default: launch_elem_ms<T, OP, MS_LINEAR, true>(p, b, stop, s);
       }
       return hipGetLastError();
     }
   }
   switch (ms) {
-    case MS_J2: timed_launch((elem_kernel<T, OP, MS_J2>), grid, block, 0, s, b, stop); break;
-    case MS_NH: timed_launch((elem_kernel<T, OP, MS_NH>), grid, block, 0, s, b, stop); break;
+    case MS_J2: launch_elem_ms<T, OP, MS_J2>(p, b, stop, s); break;
+    case MS_NH: launch_elem_ms<T, OP, MS_NH>(p, b, stop, s); break;
     case MS_SUR:
-      if constexpr (OP != OP_VJP) timed_launch((elem_kernel<T, OP, MS_SUR>), grid, block, 0, s, b, stop);
+      if constexpr (OP != OP_VJP) launch_elem_ms<T, OP, MS_SUR>(p, b, stop, s);
       break;
-    default: timed_launch((elem_kernel<T, OP, MS_LINEAR>), grid, block, 0, s, b, stop);
+    default: launch_elem_ms<T, OP, MS_LINEAR>(p, b, stop, s);
   }
   return hipGetLastError();
 }
@@ -2889,6 +3019,7 @@ struct PathArgs {
 // column by column with dual numbers instead cost 14 updates a point in 256 spilling registers, one
 // element per lane: 482 us at 48^3 against 47.
 __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) void path_vjp_kernel(PathArgs a) {
+  constexpr int TZ = Layout<2>::TZ, NN = Layout<2>::NN, ROW_IT = Layout<2>::ROW_IT;
   __shared__ double s_u[NN * 3], s_c[NN * 3], s_y[NN * 3], s_park[18][EBLOCK];
   __shared__ double s_mat[8 * FE_MAX_PHASES];
   const int n = a.n;
@@ -2896,7 +3027,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
   const int nb = ntx * nty * ntz, per = (nb + 7) >> 3;
   const int tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (tile >= nb) return;  // padding block of the XCD-aware numbering
-  const Brick br(n, tile, ntx, nty);
+  const Brick<2> br(n, tile, ntx, nty);
   stage_phases(a.mat, s_mat, threadIdx.x);
   const int r = br.lane >> 5;
   const int ex = br.lane & 15, ey = 2 * (br.wave & 1) + ((br.lane >> 4) & 1), ez = br.wave >> 1;
@@ -2911,14 +3042,14 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
     for (int t = 0; t < ROW_IT; ++t) {
       vu[t] = vc[t] = 0;
-      const Brick::Row rw = br.row(t);
+      const auto rw = br.row(t);
       if (!rw.live) continue;
       vu[t] = a.u[rw.word + br.off];
       if (a.c) vc[t] = a.c[rw.word + br.off];
     }
 #pragma unroll
     for (int t = 0; t < ROW_IT; ++t) {
-      const Brick::Row rw = br.row(t);
+      const auto rw = br.row(t);
       if (!rw.live || !br.inx) continue;
       const int i = rw.row * ROWW + br.lane;
       s_u[i] = vu[t];
@@ -3027,7 +3158,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(2))) voi
   __syncthreads();
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
-    const Brick::Row rw = br.row(t);
+    const auto rw = br.row(t);
     if (!rw.live || !br.inx) continue;
     const double v = s_y[rw.row * ROWW + br.lane];
     double* at = a.u_bar + rw.word + br.off;
