@@ -393,11 +393,11 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick<LP
 // element brick kernel
 
 // (waves per SIMD asked of the compiler: four without spills, but for the branches of surrogate points and
-// the FP64 J2 residual, where the history words in flight are worth more than a fourth wave: 141 us
-// at 64^3 with four waves and 13 spilled registers, 126 with three)
+// the FP64 residuals of laws with stored words, where what is in flight is worth more than a fourth wave: J2
+// at 64^3 141 us with four waves and 13 spilled registers, 126 with three; Neo-Hookean at 128^3 491 and 472)
 template <typename T, int OP, int MS, int LPE> constexpr int elem_waves() {
   if (LPE == 1 && (sizeof(T) == 8 || MS == MS_J2)) return 2;
-  return MS == MS_SUR ? 2 : (OP == OP_RESID && MS == MS_J2 && sizeof(T) == 8 ? 3 : 4);
+  return MS == MS_SUR ? 2 : (OP == OP_RESID && MS != MS_LINEAR && sizeof(T) == 8 ? 3 : 4);
 }
 
 // ACC32 (FP32 problems only): the nodal sums accumulate in FP32 LDS as well; by default they
