@@ -1774,15 +1774,17 @@ __global__ __launch_bounds__(256) void tangent_rows_kernel(TanArgs a, T* vals, i
 }
 
 // About a tile per CU: below that the longer chain of a tile costs more than its fewer instructions save (FP64 J2,
-// rows against tiles: 14^3 24 and 29 us, 16^3 28 and 30, 18^3 36 and 34, 20^3 40 and 38).
-constexpr int64_t TS_MIN_TILES = 240;
+// rows against tiles: 16^3 25 and 29 us, 18^3 35 and 33, 20^3 40 and 37; FP32 Neo-Hookean 18^3 31 and 29).  FP32
+// linear problems, whose rows are cheapest, wait for a second tile on a CU: 18^3 8.4 and 9.8, 20^3 11.0 and 10.6.
+constexpr int64_t TS_MIN_TILES = 240, TS_MIN_TILES_F32_LINEAR = 257;
 template <typename T>
 static void launch_tangent_csr_t(const fe_problem* p, T* v, int apply_bc, hipStream_t s) {
   const TanArgs a = tan_args(p);
   const int np1 = p->n + 1;
   const int64_t tiles = (int64_t)((np1 + TS_X - 1) / TS_X) * ((np1 + TS_Y - 1) / TS_Y) * ((np1 + TS_Z - 1) / TS_Z);
   const bool sur = p->model_set == MS_J2 && p->lin_sur;
-  if (sur || tiles < TS_MIN_TILES) {
+  const int64_t min_tiles = sizeof(T) == 4 && p->model_set == MS_LINEAR ? TS_MIN_TILES_F32_LINEAR : TS_MIN_TILES;
+  if (sur || tiles < min_tiles) {
     const dim3 grid((unsigned)((int64_t)np1 * np1 * ((np1 + TR_NODES - 1) / TR_NODES))), block(256);
     switch (p->model_set) {
       case MS_J2: timed_launch((tangent_rows_kernel<T, MS_J2>), grid, block, 0, s, a, v, apply_bc); break;
