@@ -595,7 +595,15 @@ int fe_csr_indices(fe_problem* p, int32_t* row_ptr, int32_t* col_idx, void* stre
 // sorted gather into the CSR values: n_el x 576 reals, allocated on the first tangent.
 static int ensure_ke(fe_problem* p) {
   if (!p->general || p->ke) return FE_OK;
-  return alloc(&p->ke, real_size(p) * 576 * (size_t)p->n_el);
+  const size_t bytes = real_size(p) * 576 * (size_t)p->n_el;
+  int st = alloc(&p->ke, bytes);
+  if (st && p->gen_elf) {  // make room: the solvers can do without their element forces
+    free_dev(p->gen_elf);
+    p->gen_elf = nullptr;
+    (void)hipGetLastError();
+    st = alloc(&p->ke, bytes);
+  }
+  return st;
 }
 
 int fe_tangent_csr(fe_problem* p, const void* u, const void* state_in, void* vals, int apply_bc, void* stream) {
