@@ -356,9 +356,6 @@ hipError_t bicg_step(const fe_problem* p, int stage, void* x, hipStream_t s);
 // path adjoint through the return map (FP64 problems): see fe_vjp_path
 hipError_t launch_path_vjp(const fe_problem* p, const void* u, const void* hist, const void* c, const void* mu_in,
                            void* mu_out, void* u_bar, void* s_bar, hipStream_t s);
-// network forward + Jacobian over a device-counted list (blocks beyond *count return)
-hipError_t launch_mlp_forward_counted(const float* W, const float* x, float* y, float* jac, int64_t cap,
-                                      const unsigned int* count, hipStream_t s);
 
 // CSR CG pieces: one iteration = cg_pre (direction), cg_operator (q = A p, p.Ap partials),
 // cg_vectors (scalars and updates)

@@ -82,34 +82,22 @@ __global__ __launch_bounds__(KB) void gm_setup_kernel(int64_t n, const T* b, T* 
   }
 }
 
-// part[i][blockIdx] = (V_i, w) for i < nv (V_i = V + i n).  Tiles of 8 vectors keep the
-// accumulators in registers; w is re-read once per tile.
+// part[blockIdx] = this workgroup's share of (v, w).
 template <typename T>
-__global__ __launch_bounds__(KB) void gm_dots_kernel(int64_t n, const T* V, int nv, const T* w, double* part,
-                                                     const int* stop) {
+__global__ __launch_bounds__(KB) void gm_dot_kernel(int64_t n, const T* v, const T* w, double* part, const int* stop) {
   if (stop && *stop) return;
-  __shared__ double sh[8][KB / 64];
-  for (int i0 = 0; i0 < nv; i0 += 8) {
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int64_t d = (int64_t)blockIdx.x * KB + threadIdx.x; d < n; d += (int64_t)gridDim.x * KB) {
-      const double wd = (double)w[d];
+  __shared__ double sh[KB / 64];
+  double acc = 0;
+  for (int64_t d = (int64_t)blockIdx.x * KB + threadIdx.x; d < n; d += (int64_t)gridDim.x * KB)
+    acc += (double)v[d] * (double)w[d];
+  acc = wave_sum_last(acc);
+  if ((threadIdx.x & 63) == WAVE_LAST) sh[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0;
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (i0 + u < nv) acc[u] += (double)V[(int64_t)(i0 + u) * n + d] * wd;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double t = wave_sum_last(acc[u]);
-      if ((threadIdx.x & 63) == WAVE_LAST) sh[u][threadIdx.x >> 6] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < 8 && i0 + (int)threadIdx.x < nv) {
-      double t = 0;
-#pragma unroll
-      for (int q = 0; q < KB / 64; ++q) t += sh[threadIdx.x][q];
-      part[(int64_t)(i0 + threadIdx.x) * gridDim.x + blockIdx.x] = t;
-    }
-    __syncthreads();
+    for (int q = 0; q < KB / 64; ++q) t += sh[q];
+    part[blockIdx.x] = t;
   }
 }
 
@@ -461,8 +449,8 @@ hipError_t gm_step_t(const fe_problem* p, int stage, int j, const void* b, void*
       hipLaunchKernelGGL(gm_givens_kernel, dim3(1), dim3(KB), 0, s, p->gm_part, gs_grid(p), p->gm_dev, j, stop);
       break;
     case GM_START:  // w holds the residual: ||w|| -> beta, g = beta e_1
-      hipLaunchKernelGGL(gm_dots_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, work_w<T>(p), 1, work_w<T>(p),
-                         p->gm_part, nullptr);
+      hipLaunchKernelGGL(gm_dot_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, work_w<T>(p), work_w<T>(p), p->gm_part,
+                         (const int*)nullptr);
       hipLaunchKernelGGL(gm_beta_kernel, dim3(1), dim3(KB), 0, s, p->gm_part, GM_GRID, p->gm_dev);
       break;
     case GM_FINISH:  // cycle end: y = R^-1 g, x += M^-1 V y
@@ -657,12 +645,12 @@ hipError_t ipcg_step_t(const fe_problem* p, int stage, long k, const void* b, vo
       break;
     case IPCG_FIRST_DIRECTION:  // (r, z) partials, then p = z
     case IPCG_DIRECTION:
-      hipLaunchKernelGGL(gm_dots_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, r, 1, z, part_rz, stop);
+      hipLaunchKernelGGL(gm_dot_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, r, z, part_rz, stop);
       hipLaunchKernelGGL(ipcg_direction_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, z, pp, q, part_rz, GM_GRID,
                          p->ipcg, stage == IPCG_FIRST_DIRECTION ? 0L : k);
       break;
     case IPCG_UPDATE:  // (p, q) partials, then the step
-      hipLaunchKernelGGL(gm_dots_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, pp, 1, q, part_pq, stop);
+      hipLaunchKernelGGL(gm_dot_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, pp, q, part_pq, stop);
       hipLaunchKernelGGL(ipcg_update_kernel<T>, dim3(GM_GRID), dim3(KB), 0, s, n, pp, q, static_cast<T*>(x), r,
                          part_pq, GM_GRID, p->ipcg, k, part_rr);
       break;
