@@ -369,7 +369,7 @@ def general_leg(n, reps=20):
     (J2 matrix) on the plain grid fed through the general path, and on a distorted, renumbered mesh
     of the same size, linearised at an affine strain eps_xx = 0.01.  Reports per-kernel times from the
     library's own events (residual, matrix-free K*u, CSR mat-vec), the whole fe_tangent_csr call
-    (matrix-core element Jacobians plus the sorted gather) from stream events, one CG iteration, and
+    (element Jacobians plus the row assembly) from stream events, one CG iteration, and
     the one-time symbolic set-up."""
     import torch
     from paper_2604_22087_amd import fe, inputs

@@ -1,5 +1,6 @@
 // HIP kernels of libfe for general hex8 meshes (fe_problem_create_hex8): any conforming mesh
-// of 8-node bricks given by device coordinates [3][n_nodes] and connectivity [8][n_el].
+// of 8-node bricks given by device coordinates [3][n_nodes] (kept as [n_nodes][3]) and
+// connectivity [8][n_el].
 //
 // Element kernels run one lane per (element, Gauss point): a 256-lane workgroup holds 32
 // elements x 8 points, the 8 lanes of an element sit side by side in one wave.
@@ -9,7 +10,8 @@
 //   3. the constitutive law gives the stress, pushed back to the 8 nodes (w detJ B^T sigma);
 //   4. the 8 lanes of an element sum their nodal forces by recursive halving (three lane
 //      exchanges of 12, 6 and 3 values, no atomics), after which lane p holds node p's total
-//      and adds it to the global vector with one hardware FP atomic per component.
+//      and adds it to the global vector with one hardware FP atomic per component, or, inside
+//      the solvers, stores it for a gather by node (gen_gather_kernel, gen_cg_node_kernel).
 //
 // The sparse Jacobian follows the sort-and-combine assembly of the paper (Sec. III-B):
 //   symbolic (once per mesh): every element contributes its 64 node pairs; pairs are
@@ -17,10 +19,10 @@
 //   code), so the whole list is ordered by the int64 key (row, column); runs of equal keys
 //   are the duplicates, their first positions give the node-pair pattern, and the sorted
 //   element codes of each run say which element blocks sum into that pair;
-//   numeric (per tangent): the 36 node-pair blocks of each element's symmetric Jacobian
-//   K_e = sum_q B_q^T D_q B_q w detJ are written to a per-element buffer; a gather then sums
-//   every pair's run in sorted order into the CSR values (deterministic: the same bits on
-//   every run).
+//   numeric (per tangent): each element's Jacobian K_e = sum_q B_q^T D_q B_q w detJ is symmetric,
+//   so its 36 node-pair blocks a <= b are formed, and all 64 written to a per-element buffer; a
+//   wave per node then sums every pair's run in sorted order into the CSR values (deterministic:
+//   the same bits on every run).
 #include "fe_internal.hpp"
 #include "fe_device.hpp"
 
@@ -697,7 +699,7 @@ template <typename T> __global__ void gen_mask_one_kernel(int64_t n, const uint8
 //   Neo-Hookean   lam h_a h_b^T + (mu - lam ln J) h_b h_a^T + mu (g_a . g_b) I,  h = F^-T g
 // with the physical basis gradients g: 33 multiply-adds per point and pair, which needs neither
 // the 6 x 6 (9 x 9) moduli nor the padding of a 24 x 24 matrix to matrix-core tiles.  K_e is
-// symmetric, so only the 36 pairs a <= b are formed and kept.
+// symmetric, so only the 36 pairs a <= b are formed; their transposes are written with them.
 // A workgroup takes TEL elements: one lane per (element, point) forms the gradients into LDS, then
 // one lane per (element, 2 x 2 tile of nodes) sums its four blocks, and the blocks leave through LDS
 // in whole lines.  Output: ke[e][a][b][i][k] = K_e[(a, i), (b, k)] (576 reals).
@@ -1382,7 +1384,7 @@ static hipError_t gen_elem_t(const fe_problem* p, const ElemArgs& a, const int* 
 }
 
 hipError_t gen_launch_elem(const fe_problem* p, int op, const ElemArgs& a, const int* stop, hipStream_t s) {
-  if (op == OP_CG_APPLY) return hipErrorInvalidValue;  // general meshes run the unfused CG
+  if (op == OP_CG_APPLY) return hipErrorInvalidValue;  // (CG has launches of its own: gen_cgs_operator, gen_cgs_update)
   if (p->prec == FE_F64) {
     if (op == OP_RESID) return gen_elem_t<double, OP_RESID>(p, a, stop, s);
     if (op == OP_APPLY) return gen_elem_t<double, OP_APPLY>(p, a, stop, s);

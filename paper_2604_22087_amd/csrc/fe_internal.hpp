@@ -118,7 +118,7 @@ struct BicgCtrl {
 constexpr int BICG_GRID = 512;       // workgroups of the BiCGStab vector kernels (= partial slots)
 
 // words of the compact J2 tangent per Gauss point; the stored array is followed by TANGENT_PAD zero
-// words, which the operator reads at elastic points
+// words, which the FP64 operator reads at elastic points
 constexpr int J2_TANGENT_WORDS = 6;
 // slots (one cache line each) of the stress integral: with one, the atomic adds of the workgroups queue up on a
 // line (FP32 linear 128^3, 16384 workgroups: 226 us a mean stress, 92 so)
@@ -381,12 +381,12 @@ hipError_t ipcg_step(const fe_problem* p, int stage, long k, const void* b, void
                      hipStream_t s);
 void* ipcg_vec(const fe_problem* p, int v);
 // node-block ILU(0) in 8-colour order (fe_ilu.hip): factor from the CSR matrix, apply
-// z = (L U)^-1 r (r may equal z; 16 launches, which return at once when *stop is set)
+// z = (L U)^-1 r (r may equal z; 7 launches, which return at once when *stop is set)
 size_t ilu_words(const fe_problem* p);
 hipError_t ilu_setup(const fe_problem* p, const int32_t* rp, const int32_t* ci, const void* v, hipStream_t s);
 hipError_t ilu_apply(const fe_problem* p, const void* r, void* z, const int* stop, hipStream_t s);
 // matrix-free single-reduction CG: init, then one fused operator launch j = 0, 1, ... per
-// iteration (its last workgroup computes the scalars of the next launch)
+// iteration (every workgroup forms alpha and beta from the slot sums of the launch before)
 hipError_t cgs_init(const fe_problem* p, const void* b, void* x, double rtol, int max_it, hipStream_t s);
 hipError_t cgs_operator(const fe_problem* p, void* x, long j, hipStream_t s);
 hipError_t cgs_flush(const fe_problem* p, void* x, int iters, hipStream_t s);  // after the stop: completes x

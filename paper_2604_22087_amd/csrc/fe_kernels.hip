@@ -456,7 +456,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   const int ph = valid ? (int)a.phase[e] : 0;
   const T* tang_c = static_cast<const T*>(a.tangent);
   T tq0[NPT];
-  // FP32 Neo-Hookean K u: the first point's ten words as well (64^3 32.2 -> 30.4 us, 80^3 63.5 -> 62.0; the
+  // FP32 Neo-Hookean K u: the first point's ten words as well (64^3 32.2 -> 31.4 us, 80^3 63.5 -> 61.7; the
   // CG launch, whose staging is longer, lost by it: 128^3 292 -> 300)
   constexpr bool NH_EARLY = MS == MS_NH && OP == OP_APPLY && sizeof(T) == 4;
   T nw[NHB][10];
