@@ -13,8 +13,8 @@ before the timed region; each step restarts the ramp from zero.
 value = whole-step K*u throughput: dofs x operator applications / step time.
 The dominant kernel (the single-reduction CG launch: vector updates, M^-1,
 matrix-free K*u and three dot products, one launch per iteration) is timed live
-with HIP events recorded by the library on the stream it runs on (every 16th
-launch of each solve); its algorithmic bytes per launch are the compulsory
+with HIP events recorded by the library on the stream it runs on (one of every 16
+launches of each solve, even and odd ones in turn); its algorithmic bytes per launch are the compulsory
 traffic at the linearisation in force (r, w, s, p, x, M^-1 read; r, s, p, x, w and
 the cleared next w written; phase ids; stored tangent values read).
 
@@ -46,7 +46,7 @@ FIBER = (230.0, 0.2)
 MATRIX = (3.5, 0.35, 0.05, 0.1)
 
 
-# inside the timed region only every k-th CG operator launch carries an event pair (each
+# inside the timed region only one of every k CG operator launches carries an event pair (each
 # pair costs several microseconds of issue time, about 10% of a 64^3 iteration)
 CG_TIMING_STRIDE = 16
 
