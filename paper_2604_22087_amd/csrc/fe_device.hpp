@@ -139,10 +139,13 @@ __device__ __forceinline__ bool cg_coefficients(CgCtrl* w, const CgHist& c, long
 // Sums d, g, rr of the [3][CGS_SLOTS] slots of the launch before, over a workgroup of W waves:
 // lane values v[k] = slot k * 64 W + threadIdx (64 slots per wave, so the 12 wave sums are four
 // each of d, g and rr, in a fixed order); sh holds at least 12 doubles, synchronised on return.
+// False after a stop.  Tested only after the barrier: in the launch that stops, workgroup 0 writes the
+// status while waves of later workgroups read it, and those of one workgroup that still read CG_RUNNING
+// need the sums of the others, to stop by them too instead of going on to x and r.
 template <int W> constexpr int cg_slots_per_lane() { return (12 + W - 1) / W; }
 template <int W>
-__device__ __forceinline__ void cg_slot_sums(const double v[cg_slots_per_lane<W>()], double* sh, double& d, double& g,
-                                             double& rr) {
+__device__ __forceinline__ bool cg_slot_sums(const double v[cg_slots_per_lane<W>()], int status, double* sh, double& d,
+                                             double& g, double& rr) {
   static_assert(CGS_SLOTS == 256, "four waves per reduced quantity");
   const int wave = threadIdx.x >> 6;
 #pragma unroll
@@ -151,6 +154,7 @@ __device__ __forceinline__ void cg_slot_sums(const double v[cg_slots_per_lane<W>
     if ((threadIdx.x & 63) == WAVE_LAST && k * W + wave < 12) sh[k * W + wave] = t;
   }
   __syncthreads();
+  if (status != CG_RUNNING) return false;
   d = g = rr = 0;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
@@ -159,6 +163,7 @@ __device__ __forceinline__ void cg_slot_sums(const double v[cg_slots_per_lane<W>
     rr += sh[8 + w];
   }
   __syncthreads();  // sh may be reused
+  return true;
 }
 
 // Wavefront-aggregated append: lanes with pred set get consecutive slots of *counter

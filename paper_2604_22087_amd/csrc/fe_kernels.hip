@@ -287,6 +287,7 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick<LP
       if (br.wave + k * EWAVES < 12) acc_v[k] = a.cg_acc_in[k * EBLOCK + threadIdx.x];
   }
   // requested with everything else: one wait instead of a test of the status word before any load
+  // (that test: see cg_slot_sums)
   const CgHist ctl = cg_history(a.ctrl, a.cg_j);
   T alpha = 0, beta = 0;
   const bool two = a.cg_j >= 2 && (a.cg_j & 1) == 0;  // p and x advance
@@ -332,13 +333,17 @@ __device__ __forceinline__ bool cg_stage_brick(const ElemArgs& a, const Brick<LP
       xo[t] = X[dof];
     }
   }
-  early();
-  if (ctl.status) return false;  // the solve has stopped
+  // FP32 requests its stored words before the scalar step, FP64 after it (FP64 J2, before / after: 64^3
+  // 34.2 / 33.1 us, 128^3 345 / 329: registers).  One lane per element: no sum is scheduled among the
+  // requests (FP32 linear 64^3 21.1 -> 20.0 us, J2 128^3 236 -> 228).
+  if constexpr (sizeof(T) == 4) early();
+  if constexpr (LPE == 1) __builtin_amdgcn_sched_barrier(0);
   if (prev) {  // run redundantly by every workgroup: no inter-workgroup synchronisation in a launch
     double d, gs, rs;
-    cg_slot_sums<EWAVES>(acc_v, sh, d, gs, rs);
+    if (!cg_slot_sums<EWAVES>(acc_v, ctl.status, sh, d, gs, rs)) return false;  // (launch 0 follows no stop)
     if (!cg_coefficients<T>(a.ctrl, ctl, a.cg_j, d, gs, rs, alpha, beta)) return false;
   }
+  if constexpr (sizeof(T) == 8) early();
   const T alpha2 = T(ctl.alpha), beta2 = T(ctl.beta);
 #pragma unroll
   for (int t = 0; t < ROW_IT; ++t) {
@@ -425,7 +430,7 @@ __global__ __launch_bounds__(EBLOCK) __attribute__((amdgpu_waves_per_eu(elem_wav
   constexpr bool PARK = sizeof(T) == 8 && MS != MS_LINEAR && LPE == 2;
   __shared__ T s_park[PARK ? 9 : 1][PARK ? EBLOCK : 1];
 
-  if (OP != OP_CG_APPLY && stop && *stop) return;  // (the CG launch tests its status after requesting its data)
+  if (OP != OP_CG_APPLY && stop && *stop) return;  // (the CG launch: see cg_slot_sums)
   const int n = a.n;
   const int ntx = (n + TX - 1) / TX, nty = (n + TY - 1) / TY, ntz = (n + TZ - 1) / TZ;
   const int nb = ntx * nty * ntz;
